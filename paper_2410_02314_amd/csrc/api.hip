@@ -73,7 +73,7 @@ struct dl_net {
     float *d_head = nullptr;        // w [5][C] then b [5]
     float *d_bias = nullptr;        // [nb][2][C]
     void *d_wpk = nullptr;          // packed conv weights [nb][2][...]
-    float *d_wscale = nullptr;      // FP8 per-output-channel weight scales [nb][2][C]
+    float *d_wscale = nullptr;      // per-output-channel weight scales (FP8, FP32) [nb][2][C]
     int *d_dil = nullptr;           // dilations [nb]
     size_t wpk_stride = 0;
     int packed_precision = -1;
@@ -832,7 +832,7 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
         a.tr = g.trb[b];
         a.in_phase = lay == net->dil[b] && lay > 1;
         a.out_shift = __builtin_ctz((unsigned)lay);
-        if (net->cfg.precision == DL_FP8) a.wscale = net->d_wscale + (size_t)(b * 2) * C;
+        a.wscale = net->d_wscale + (size_t)(b * 2) * C;
         a.in = x;
         a.out = a1;
         a.res = nullptr;
@@ -852,7 +852,7 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
         a.out_shift = __builtin_ctz((unsigned)lay_next);
         a.wpk = static_cast<char *>(net->d_wpk) + (size_t)(b * 2 + 1) * net->wpk_stride;
         a.bias = net->d_bias + (size_t)(b * 2 + 1) * C;
-        if (net->cfg.precision == DL_FP8) a.wscale = net->d_wscale + (size_t)(b * 2 + 1) * C;
+        a.wscale = net->d_wscale + (size_t)(b * 2 + 1) * C;
         if (lists) {
             a.list = lists + (size_t)(2 * b + 1) * g.max_tiles;
             a.list_count = lcount + 2 * b + 1;
@@ -2551,6 +2551,7 @@ int dl_debug_conv_layer(dl_net *net, const float *d_in, const float *d_res, int 
     a.out = d_out;
     a.wpk = static_cast<char *>(net->d_wpk) + (size_t)(blk * 2 + which) * net->wpk_stride;
     a.bias = net->d_bias + (size_t)(blk * 2 + which) * net->C;
+    a.wscale = net->d_wscale + (size_t)(blk * 2 + which) * net->C;
     a.tr = g.trb[blk];
     const int maxg = conv_max_grid(net->C, net->cfg.precision, g.trb[blk], net->ncu);
     int grid = (int)std::min<int64_t>(g.tiles[blk], maxg);

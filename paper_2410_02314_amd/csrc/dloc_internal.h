@@ -232,7 +232,7 @@ struct ConvArgs {
     void *out;               // NHWC output (or null when the head is fused)
     const void *wpk;         // packed weights
     const float *bias;       // [C]
-    const float *wscale;     // FP8: per-output-channel weight scale [C]
+    const float *wscale;     // per output channel [C]: FP8 the weight scale, FP32 (to 48 channels) the weights' power of two
     const float *head;       // fused head: w [nh][C] then b [nh]; null = no head
     float *maps;             // fused head output, planar [nh][h][w] per frame
     int nh;                  // head outputs: 5, or 10 with the uncertainty planes
@@ -253,7 +253,7 @@ int conv_max_grid(int C, int precision, int tr, int ncu);
 // does the conv kernel of this channel count and form fit in LDS (both tile heights)?
 bool conv_supported(int C, int precision, int nh);
 size_t conv_packed_bytes(int C, int precision);
-// pack one 3x3 C->C layer W [C][C][3][3]; FP8 also writes scale[C]
+// pack one 3x3 C->C layer W [C][C][3][3]; FP8 and FP32 (to 48 channels) also write scale[C]
 void pack_conv_weights(int C, int precision, const float *W, void *dst, float *scale);
 
 // ---- dense-connection networks (kernels_dense.hip) ----

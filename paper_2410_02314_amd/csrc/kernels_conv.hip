@@ -23,10 +23,10 @@
 //
 // GEMM view: M = output channels (blocks of 16), N = pixels (blocks of 16),
 // K = 9 taps x C input channels.
-//   FP32  v_mfma_f32_16x16x4_f32; lane group kq takes channels 16 g + 4 kq + s
-//         (s = MFMA step), so one float4 feeds 4 steps.  Weights live in LDS
-//         when they fit beside the tile (C <= 48 with 8-row tiles); otherwise
-//         they are read from L2 one K iteration ahead.
+//   FP32  (64 channels; fewer run in kernels_split.hip) v_mfma_f32_16x16x4_f32;
+//         lane group kq takes channels 16 g + 4 kq + s (s = MFMA step), so one
+//         float4 feeds 4 steps.  The weights (147 KB) do not fit in LDS beside
+//         a tile and are read from L2 one K iteration ahead.
 //   BF16  v_mfma_f32_16x16x32_bf16 (FP32 accumulation); K is cut into chunks
 //         of 8 channels of one tap and lane group kq of step m takes chunk
 //         4 m + kq (one 16-byte LDS read).  Weights live in LDS.
@@ -51,7 +51,7 @@
 // BF16 and FP8 pass each wave's output row (and residual) through LDS so they
 // move in whole 16-byte lanes; every store is a buffer store whose offset is
 // out of range for pixels off the frame, so the epilogue has no branches.
-#include "dloc_internal.h"
+#include "conv_common.h"
 
 #include <cmath>
 #include <cstring>
@@ -61,21 +61,7 @@ namespace dloc {
 
 namespace {
 
-constexpr int NXCD = 8;
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-
-// Buffer resource over nbytes at base (raw addressing: stride 0, offsets in
-// bytes).  A store whose offset lies past nbytes is dropped by the hardware,
-// which lets the epilogue store without a branch around pixels off the frame.
-constexpr uint32_t BUF_DWORD3 = 0x00020000u;
-constexpr int BUF_OOB = (int)0x80000000u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(void *base, uint32_t nbytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)nbytes, (int)BUF_DWORD3);
-}
 
 // Dword stride of one lattice point in the LDS tile.  gfx950's LDS serves a
 // 16-byte read (ds_read_b128) of the 64 lanes in groups whose banks collide
@@ -84,17 +70,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(void *base, uint32_t 
 // FP32 and BF16 kernels (every C in 16..64: zero read conflicts at 8 mod 16,
 // about 4 extra cycles per read at 4 or 12 mod 16, 12 or more at 0 mod 16).
 constexpr int stride_8_mod_16(int dw) { return dw + ((8 - dw % 16) + 16) % 16; }
-constexpr int align16(int b) { return (b + 15) / 16 * 16; }
-
-__device__ __forceinline__ v4f relu4(v4f v)
-{
-    v4f r;
-    r[0] = fmaxf(v[0], 0.f); r[1] = fmaxf(v[1], 0.f);
-    r[2] = fmaxf(v[2], 0.f); r[3] = fmaxf(v[3], 0.f);
-    return r;
-}
-
-
 // storage of the activations in HBM: FP32, BF16, or FP8 (e4m3 codes plus
 // one scale byte per 32-channel group of a point, dloc_internal.h)
 template <int P> struct Store {
@@ -145,7 +120,7 @@ template <int C, int P> struct KPlan;
 template <int C> struct KPlan<C, DL_FP32> {
     static constexpr int NIT = 9 * (C / 16);
     static constexpr int BYTES = 9 * C * C * 4;
-    static constexpr int LDS_W = BYTES;           // in LDS when the tile leaves room (see Lds)
+    static constexpr int LDS_W = 0;               // read from L2
     static constexpr int LESZ = 4;                // LDS bytes per channel
 };
 template <int C> struct KPlan<C, DL_BF16> {
@@ -200,10 +175,7 @@ struct Lds {
     static constexpr int NPT = (TR + 2) * PW;
     static constexpr int TBYTES = align16(NPT * PS);
     static constexpr int EXTRA = C * 4 + (NHL * C + NHL) * 4 + C * 4 + 64;  // bias, head, scales, alignment
-    // FP32 keeps its weights in LDS when they fit beside the tile (C <= 48 at
-    // 8 rows); otherwise each K iteration reads them from L2, one ahead
-    static constexpr bool LDSW_FP32 = TBYTES + KPlan<C, P>::BYTES + EXTRA <= 160 * 1024;
-    static constexpr int LDSW = P == DL_FP32 ? (LDSW_FP32 ? KPlan<C, P>::BYTES : 0) : KPlan<C, P>::LDS_W;
+    static constexpr int LDSW = KPlan<C, P>::LDS_W;
     static constexpr int WOFF = TBYTES;
     static constexpr int BOFF = WOFF + LDSW;                           // bias [C]
     static constexpr int HOFF = BOFF + C * 4;                          // head [NHL C + NHL]
@@ -219,14 +191,6 @@ struct Lds {
     static constexpr int DOFF = align16(OOFF + TR * OWAVE);            // two decoded-tile slots
     static constexpr int TOTAL = DOFF + 2 * 64;
     static constexpr bool FITS = TOTAL <= 160 * 1024;   // else no kernel exists for this shape
-};
-
-// a decoded tile: origin (y0, x0) and size of its frame, where its input
-// sits (point (ii, jj) of the tile is activation point a0 + ii rs + jj cs of
-// the frame), and the frame's map and activation offsets
-struct TileDec {
-    int y0, x0, h, w, a0, rs, cs;
-    int64_t px, act;
 };
 
 // --------------------------------------------------------------- kernel
@@ -267,7 +231,7 @@ k_conv(ConvArgs a, Geometry geo)
     }
     // FP32: the weights of K iteration 0, read ahead of every tile (the last
     // iteration of a tile reads them for the next)
-    constexpr bool GW = P == DL_FP32 && !L::LDSW_FP32;
+    constexpr bool GW = P == DL_FP32;
     v4f awn[GW ? NB : 1];
     if constexpr (GW)
 #pragma unroll
@@ -306,61 +270,13 @@ k_conv(ConvArgs a, Geometry geo)
     // resource over the frame, and points off the frame take an out-of-range
     // offset, which reads as zero.
     TileDec n{};
-    auto decode = [&](int64_t ti) {
-        TileDec r;
-        const int64_t t = a.list ? (int64_t)ld_const(a.list + ti) : ti;
-        const int f = find_frame(a.fd, nfr, t, [blk](const FrameDesc &d) { return ld_const(&d.tile_start[blk]); });
-        const FrameDesc *fd = a.fd + f;      // fields read in place: tile_start is indexed by the block
-        r.h = ld_const(&fd->h);
-        r.w = ld_const(&fd->w);
-        r.px = ld_const(&fd->px_off);
-        r.act = ld_const(&fd->act_off);
-        decode_tile(r.h, r.w, t - ld_const(&fd->tile_start[blk]), dd, TR, TC, blk == geo.minor_blk, geo.strip, r.y0,
-                    r.x0);
-        if (a.in_phase) {
-            const int hd = (r.h + dd - 1) / dd, wd = (r.w + dd - 1) / dd;
-            const int py = r.y0 % dd, px = r.x0 % dd;
-            r.a0 = ((py * dd + px) * hd + r.y0 / dd) * wd + r.x0 / dd;
-            r.rs = wd;
-            r.cs = 1;
-        } else {
-            r.a0 = r.y0 * r.w + r.x0;
-            r.rs = dd * r.w;
-            r.cs = dd;
-        }
-        return r;
-    };
+    auto decode = [&](int64_t ti) { return decode_conv_tile(a, geo, nfr, TR, TC, ti); };
     // Wave 0 alone decodes tiles (the scalar unit is shared by the CU's
     // waves): it publishes the tile after next in one of two LDS slots from
     // inside its MFMA loop, and every wave picks it up after the next loop-top
     // barrier.  A slot is rewritten only after every wave has passed the
     // barrier that follows its last reading.
     int *sdec = reinterpret_cast<int *>(sT + L::DOFF);
-    auto publish = [&](int sl, const TileDec &r) {
-        if (lane == 0) {
-            int4 *q = reinterpret_cast<int4 *>(sdec + 16 * sl);
-            q[0] = int4{r.y0, r.x0, r.h, r.w};
-            q[1] = int4{r.a0, r.rs, r.cs, 0};
-            q[2] = int4{(int)(uint32_t)r.px, (int)(r.px >> 32), (int)(uint32_t)r.act, (int)(r.act >> 32)};
-        }
-    };
-    auto pickup = [&](int sl) {
-        const int4 *q = reinterpret_cast<const int4 *>(sdec + 16 * sl);
-        const int4 u0 = q[0], u1 = q[1], u2 = q[2];
-        TileDec r;
-        r.y0 = __builtin_amdgcn_readfirstlane(u0.x);
-        r.x0 = __builtin_amdgcn_readfirstlane(u0.y);
-        r.h = __builtin_amdgcn_readfirstlane(u0.z);
-        r.w = __builtin_amdgcn_readfirstlane(u0.w);
-        r.a0 = __builtin_amdgcn_readfirstlane(u1.x);
-        r.rs = __builtin_amdgcn_readfirstlane(u1.y);
-        r.cs = __builtin_amdgcn_readfirstlane(u1.z);
-        r.px = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(u2.x) |
-               ((int64_t)__builtin_amdgcn_readfirstlane(u2.y) << 32);
-        r.act = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(u2.z) |
-                ((int64_t)__builtin_amdgcn_readfirstlane(u2.w) << 32);
-        return r;
-    };
     // the tile's input into registers: point (ii, jj) of the tile is
     // activation point a0 + ii rs + jj cs of the frame (off-frame points take
     // an out-of-range offset and read zero)
@@ -397,7 +313,7 @@ k_conv(ConvArgs a, Geometry geo)
     if (ti < t1) {
         n = decode(ti);
         issue(n);
-        if (wave == 0) publish(0, decode(ti + nslot < t1 ? ti + nslot : ti));
+        if (wave == 0) publish_tile(sdec, lane, decode(ti + nslot < t1 ? ti + nslot : ti));
     }
     // the first tile's data is waited for here, outside the loop: the
     // compiler's wait at the loop top then only has to cover the loop's own
@@ -454,14 +370,13 @@ k_conv(ConvArgs a, Geometry geo)
         // waits for the next tile's loads, instead of waiting for everything.
         const bool row_ok = yo < H;
         // BF16/FP8 without the head: output (and residual) pass through this
-        // wave's LDS staging row and move in whole 16-byte lanes.  The fused
-        // head layer and FP32 with weights in LDS load the residual in the
-        // MFMA layout before the next tile's input (EARLY_RES); FP32 with
-        // weights in L2 has no registers to spare and loads it in the
-        // epilogue, one pixel block at a time.
+        // wave's LDS staging row and move in whole 16-byte lanes.  Split BF16
+        // and the fused head layer load the residual in the MFMA layout before
+        // the next tile's input (EARLY_RES); FP32 has no registers to spare
+        // and loads it in the epilogue, one pixel block at a time.
         constexpr bool F32IO = P == DL_FP32 || P == DL_BF16X3;      // FP32 activations in HBM
         constexpr bool STAGE = !F32IO && !HEAD;
-        constexpr bool EARLY_RES = RES && (!F32IO ? HEAD : P == DL_BF16X3 || L::LDSW_FP32);
+        constexpr bool EARLY_RES = RES && (!F32IO ? HEAD : P == DL_BF16X3);
         constexpr int CPX = L::OPX / 16;                    // 16-byte chunks per staged pixel
         constexpr int NRC = STAGE ? TC * CPX / 64 : 1;      // chunks per lane
         static_assert(!STAGE || (TC * CPX) % 64 == 0, "staging chunks per lane");
@@ -508,34 +423,25 @@ k_conv(ConvArgs a, Geometry geo)
                 }
             }
         };
-        // FP32 with weights and tile in LDS and the register budget of two
-        // waves per SIMD (see its MFMA loop below)
-        constexpr bool PREF = P == DL_FP32 && !GW && min_waves<P, TR_>() == 2;
         // the residual (early forms) and the next tile's input.  Past the
         // last tile the current one is read again (and not used), so no branch
         // separates the residual loads from the prefetch and the wait for them
-        // stays exact.  FP32 with weights in L2 (4-row tiles, no register room
-        // for that) skips the read.  PREF issues these after the first K step's
-        // MFMAs, so the matrix unit works while they go out; the other forms
-        // issue them before their K loop.
-        auto pre_loads = [&]() {
-            if constexpr (EARLY_RES) load_res(0);
-            __builtin_amdgcn_sched_barrier(0);   // residual loads stay ahead of the prefetch
-            if constexpr (GW) {
-                if (ti + nslot < t1) {
-                    n = pickup(par);
-                    issue(n);
-                }
-            } else {
-                n = pickup(par);                 // the next tile, or this one again past the last
+        // stays exact.  FP32 (4-row tiles, no register room for that) skips
+        // the read.
+        if constexpr (EARLY_RES) load_res(0);
+        __builtin_amdgcn_sched_barrier(0);       // residual loads stay ahead of the prefetch
+        if constexpr (GW) {
+            if (ti + nslot < t1) {
+                n = pickup_tile(sdec + 16 * par);
                 issue(n);
             }
-            // keep the scheduler from sinking these loads below the MFMAs they
-            // are meant to overlap
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        if constexpr (!PREF) pre_loads();
-
+        } else {
+            n = pickup_tile(sdec + 16 * par);    // the next tile, or this one again past the last
+            issue(n);
+        }
+        // keep the scheduler from sinking these loads below the MFMAs they
+        // are meant to overlap
+        __builtin_amdgcn_sched_barrier(0);
 
         v4f acc[NB][PB];
 #pragma unroll
@@ -567,48 +473,12 @@ k_conv(ConvArgs a, Geometry geo)
         auto ahead = [&]() {
             if (wave == 0 && ti + nslot < t1) {
                 const int64_t t2 = ti + 2 * nslot;
-                publish(par ^ 1, decode(t2 < t1 ? t2 : ti + nslot));
+                publish_tile(sdec + 16 * (par ^ 1), lane, decode(t2 < t1 ? t2 : ti + nslot));
             }
         };
-        // PREF: the operands of K step it + 1 are read while the MFMAs of step
-        // it run (the reads past the last step fetch step 0 again and are not
-        // used), so the MFMAs wait only for reads issued one step earlier
-        if constexpr (PREF) {
-            constexpr int G = C / 16, NIT = KPlan<C, P>::NIT;
-            const v4f *sW = reinterpret_cast<const v4f *>(sT + L::WOFF);
-            auto operands = [&](int it, v4f (&aw)[NB], v4f (&bv)[PB]) {
-                const int tap = it / G, gg = it - (it / G) * G;
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) aw[nb] = sW[(it * NB + nb) * 64 + lane];
-#pragma unroll
-                for (int p = 0; p < PB; ++p)
-                    bv[p] = *reinterpret_cast<const v4f *>(pt_addr(p, tap) + (gg * 16 + kq * 4) * 4);
-            };
-            v4f aw[NB], bv[PB];
-            operands(0, aw, bv);
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                v4f an[NB], bn[PB];
-                operands(it + 1 < NIT ? it + 1 : 0, an, bn);
-                __builtin_amdgcn_sched_barrier(0);   // issued before this step's MFMAs
-                if (it == NIT / 2) ahead();
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                        for (int p = 0; p < PB; ++p)
-                            acc[nb][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[nb][s], bv[p][s], acc[nb][p], 0, 0, 0);
-                if (it == 0) pre_loads();
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) aw[nb] = an[nb];
-#pragma unroll
-                for (int p = 0; p < PB; ++p) bv[p] = bn[p];
-            }
-        } else if constexpr (P == DL_FP32) {
+        if constexpr (P == DL_FP32) {
             constexpr int G = C / 16, NIT = KPlan<C, P>::NIT;
             const v4f *gw = static_cast<const v4f *>(a.wpk);
-            const v4f *sW = reinterpret_cast<const v4f *>(sT + L::WOFF);
 #pragma unroll 1
             for (int tap = 0; tap < 9; ++tap) {
                 if (tap == 4) ahead();
@@ -616,16 +486,12 @@ k_conv(ConvArgs a, Geometry geo)
                 for (int gg = 0; gg < G; ++gg) {
                     const int it = tap * G + gg;
                     v4f aw[NB];
-                    if constexpr (GW) {             // weights from L2, one K step ahead
+                    // weights from L2, one K step ahead
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) aw[nb] = awn[nb];
-                        const int itn = it + 1 < NIT ? it + 1 : 0;
+                    for (int nb = 0; nb < NB; ++nb) aw[nb] = awn[nb];
+                    const int itn = it + 1 < NIT ? it + 1 : 0;
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) awn[nb] = gw[(itn * NB + nb) * 64 + lane];
-                    } else {
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) aw[nb] = sW[(it * NB + nb) * 64 + lane];
-                    }
+                    for (int nb = 0; nb < NB; ++nb) awn[nb] = gw[(itn * NB + nb) * 64 + lane];
                     v4f bv[PB];
 #pragma unroll
                     for (int p = 0; p < PB; ++p)
@@ -1054,6 +920,7 @@ void conv_tile_shape(int C, int precision, int rows, int *tr, int *tc)
 
 bool conv_supported(int C, int precision, int nh)
 {
+    if (split_takes(C, precision)) return true;
     if (precision == DL_FP32) return fits_p<DL_FP32>(C, nh);
     if (precision == DL_BF16) return fits_p<DL_BF16>(C, nh);
     if (precision == DL_FP8) return fits_p<DL_FP8>(C, nh);
@@ -1063,6 +930,7 @@ bool conv_supported(int C, int precision, int nh)
 
 size_t conv_packed_bytes(int C, int precision)
 {
+    if (split_takes(C, precision)) return split_packed_bytes(C);
     const int NB = C / 16, NCH = 9 * (C / 8);
     if (precision == DL_FP32) return (size_t)9 * C * C * 4;
     if (precision == DL_BF16) return (size_t)((NCH + 3) / 4) * NB * 64 * 16;
@@ -1073,6 +941,7 @@ size_t conv_packed_bytes(int C, int precision)
 
 void pack_conv_weights(int C, int precision, const float *W, void *dst, float *scale)
 {
+    if (split_takes(C, precision)) return split_pack_weights(C, W, dst, scale);
     const int NB = C / 16;
     auto wt = [&](int oc, int c, int tap) { return W[((size_t)oc * C + c) * 9 + tap]; };
     if (precision == DL_FP32) {
@@ -1148,8 +1017,9 @@ void pack_conv_weights(int C, int precision, const float *W, void *dst, float *s
 
 int conv_max_grid(int C, int precision, int tr, int ncu)
 {
+    if (split_takes(C, precision)) return split_max_grid(C, tr, ncu);
     int b = 1;
-    if (precision == DL_FP32) b = bpc_p<DL_FP32>(C, tr);
+    if (precision == DL_FP32) b = tr == 4 ? blocks_per_cu<64, DL_FP32, 4>() : blocks_per_cu<64, DL_FP32, 8>();
     else if (precision == DL_BF16) b = bpc_p<DL_BF16>(C, tr);
     else if (precision == DL_BF16X3) b = bpc_p<DL_BF16X3>(C, tr);
     else b = bpc_p<DL_FP8>(C, tr);
@@ -1158,7 +1028,8 @@ int conv_max_grid(int C, int precision, int tr, int ncu)
 
 hipError_t launch_conv(int C, int precision, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
 {
-    if (precision == DL_FP32) return launch_p<DL_FP32>(C, a, g, grid, s);
+    if (split_takes(C, precision)) return launch_split(C, a, g, grid, s);
+    if (precision == DL_FP32) return C == 64 ? launch_cp<64, DL_FP32>(a, g, grid, s) : hipErrorInvalidValue;
     if (precision == DL_BF16) return launch_p<DL_BF16>(C, a, g, grid, s);
     if (precision == DL_FP8) return launch_p<DL_FP8>(C, a, g, grid, s);
     if (precision == DL_BF16X3) return launch_p<DL_BF16X3>(C, a, g, grid, s);

@@ -1,0 +1,582 @@
+// 3x3 dilated convolution layers of the FP32 form (to 48 channels) on the
+// FP16 matrix cores (gfx950).
+//
+// Operation: as kernels_conv.hip (paper Sec. 3.2.1, dilated convolution; Sec.
+// 3.2, per-pixel head): y[p][o] = b[o] + sum_{tap, c} W[o][c][tap] *
+// x[p + d off(tap)][c], optional residual, ReLU, optional fused 1x1 head.
+//
+// Products.  Every FP32 operand is held as two FP16 halves, hi = f16(v 2^s) and
+// lo = f16((v 2^s - hi) 2^11): 22 significant bits and the sign of lo.  A
+// product is taken as wh xh + (wh xl + wl xh) 2^-11, the two sums in FP32
+// accumulators of their own.  The operand error (2^-23 of the value at most)
+// lies below the rounding of an FP32 accumulation over 9 C products, and here
+// a sum is rounded once per 32 products instead of once per product: on whole
+// nets the error against 64-bit arithmetic is 2.3e-7 of the maps' norm (48
+// channels, 10 layers), and was 3.9e-7 with v_mfma_f32_16x16x4_f32.
+// Three FP16 MFMAs take 3/16 of the cycles of the FP32 MFMAs they replace.
+//   Range: s is 0 while the largest input of a tile lies in [2^-5, 2^15), else
+// the multiple of 20 that brings it there (exact powers of two); values down
+// to 2^-14 after scaling keep all 22 bits, smaller ones 2^-36 absolute, i.e. at
+// most 2^-31 of the tile's largest.  Weights are scaled by a power of two per
+// output channel.  A tile holding an infinity or a value of 2^75 or more, or
+// nothing but values below 2^-65 (or any tile of a layer whose weights are of
+// such magnitudes) takes plain FP32 FMAs instead (slow_tile), so those come out
+// as in FP32; NaNs propagate by themselves.
+//
+// Tiling.  Tiles, persistent workgroups, XCD ranges and the register prefetch
+// of the next tile as in kernels_conv.hip.  TR x 32 output points per tile and
+// four waves: wave w computes columns 16 (w & 1) .. + 15 of rows R (w >> 1) ..
+// + R - 1, R = TR / 2, for all output channels.  One K step takes 32 values of
+// one tap row u: an input row's fragment is read from LDS once per step and
+// multiplied into the (up to three) output rows it belongs to, and a weight
+// fragment once for the wave's R rows.  Per K step of three tap rows a wave of
+// an 8-row tile reads 18 + 12 KB (C = 48) for 108 MFMAs, 69 bytes per clock
+// and CU at full MFMA rate of the LDS's 128; one row of 32 pixels per wave
+// (the layout of kernels_conv.hip) would read 139.
+//
+// LDS.  hi and lo values in planes of 16 channels, 32 bytes per point and
+// plane: a point stride of 8 dwords, which a 16-byte read of 16 points x 2
+// channel halves serves without bank conflicts, and no padding, so that
+// weights (86 KB) and tile (65 KB) of 48 channels fit beside each other, and
+// two workgroups of 32 channels (80 KB each) on a CU.
+//
+// Measured (4 x 2048^2 points, mean launch without head): 48 channels 5.11 ms
+// with FP32 MFMAs, 2.32 ms here; 32 channels 2.40 ms, 1.15 ms here.  What is
+// left above the HBM bytes' 1.5 ms (48 channels, at the 5.2 TB/s of a copy) is
+// the conversion and the epilogue, which one wave per SIMD does not overlap
+// with its MFMAs.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <type_traits>
+#include <vector>
+
+#include "conv_common.h"
+
+namespace dloc {
+
+namespace {
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+
+constexpr int TC = 32, PW = TC + 2, NTH = 256;
+
+// K plan: per tap row u, 3 taps x C channels in chunks of 8 (tap column major),
+// taken four at a time; with 2 chunks left over (C = 16 or 48) two closing
+// steps share them among the tap rows: step 0 holds those of u = 0 (lane
+// groups 0, 1) and u = 1 (2, 3), step 1 those of u = 2 and zero weights
+template <int C> struct SPlan {
+    static constexpr int CH8 = C / 8, NB = C / 16;
+    static constexpr int FULL = 3 * CH8 / 4;
+    static constexpr bool HALF = 3 * CH8 % 4 != 0;
+    static constexpr int NSTEP = 3 * FULL + (HALF ? 2 : 0);      // weight steps
+    static constexpr int WBYTES = NSTEP * NB * 2 * 64 * 16;      // hi and lo fragments
+};
+
+template <int C, int TR, int NH> struct SLds {
+    static constexpr int NPT = (TR + 2) * PW;
+    static constexpr int PLANE = NPT * 32;                       // 16 channels of every point
+    static constexpr int LO = PLANE * (C / 16);                  // lo planes after the hi planes
+    static constexpr int WOFF = 2 * LO;
+    static constexpr int BOFF = WOFF + SPlan<C>::WBYTES;         // bias [C]
+    static constexpr int SOFF = BOFF + C * 4;                    // weight scales [C]
+    static constexpr int HOFF = SOFF + C * 4;                    // head [NH C + NH]
+    static constexpr int MOFF = align16(HOFF + (NH * C + NH) * 4);   // wave maxima [4]
+    static constexpr int TOTAL = MOFF + 16;
+    static constexpr bool FITS = TOTAL <= 160 * 1024;
+};
+
+// waves per SIMD the register budget is sized for: two workgroups of up to 32
+// channels share a CU (4-row tiles of 48 channels do not fit twice beside
+// their weights)
+template <int C> constexpr int split_waves() { return C <= 32 ? 2 : 1; }
+
+__device__ __forceinline__ uint32_t pack_h2(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, (h2{(_Float16)a, (_Float16)b}));
+}
+
+// largest |v| over the wave's lanes (v >= 0), in every lane
+__device__ __forceinline__ float wave_max(float v)
+{
+    int x = __float_as_int(v);           // non-negative floats order as integers
+#define DLOC_DPP_MAX(ctrl, rmask) x = max(x, __builtin_amdgcn_update_dpp(0, x, ctrl, rmask, 0xF, false))
+    DLOC_DPP_MAX(0x111, 0xF);            // row_shr:1
+    DLOC_DPP_MAX(0x112, 0xF);            // row_shr:2
+    DLOC_DPP_MAX(0x114, 0xF);            // row_shr:4
+    DLOC_DPP_MAX(0x118, 0xF);            // row_shr:8
+    DLOC_DPP_MAX(0x142, 0xA);            // row_bcast:15 into rows 1, 3
+    DLOC_DPP_MAX(0x143, 0xC);            // row_bcast:31 into rows 2, 3
+#undef DLOC_DPP_MAX
+    return __int_as_float(__builtin_amdgcn_readlane(x, 63));
+}
+
+// One tile in plain FP32 FMAs, a thread per output point, in tap and channel
+// order, from HBM and the unpacked weights: the rare tile whose values the FP16
+// halves cannot hold (an infinity, or a magnitude past their scaling).
+template <int C, int TR, int NH>
+__device__ __forceinline__ void slow_tile(const ConvArgs &a, const TileDec &n, const float *gw, const float *sB,
+                                          const float *sH)
+{
+    const int dd = a.d, row = threadIdx.x / TC, col = threadIdx.x % TC;
+    const int yo = n.y0 + dd * row, xo = n.x0 + dd * col;
+    if (row >= TR || yo >= n.h || xo >= n.w) return;
+    const float *gx = static_cast<const float *>(a.in) + n.act * C;
+    const int64_t ipt = n.a0 + (int64_t)row * n.rs + col * n.cs;
+    const int osh = a.out_shift, om = (1 << osh) - 1;
+    const int64_t opt = n.act + ((((yo & om) << osh) + (xo & om)) * (int64_t)((n.h + om) >> osh) + (yo >> osh)) *
+                                    ((n.w + om) >> osh) + (xo >> osh);
+    float hh[NH > 0 ? NH : 1] = {};
+#pragma unroll 1
+    for (int oc = 0; oc < C; ++oc) {
+        float s = 0.f;
+#pragma unroll 1
+        for (int tap = 0; tap < 9; ++tap) {
+            const int u = tap / 3 - 1, v = tap % 3 - 1, yy = yo + dd * u, xx = xo + dd * v;
+            if ((unsigned)yy >= (unsigned)n.h || (unsigned)xx >= (unsigned)n.w) continue;
+            const float *xp = gx + (ipt + u * n.rs + v * n.cs) * C;
+#pragma unroll 1
+            for (int c = 0; c < C; ++c) s = fmaf(gw[(oc * C + c) * 9 + tap], xp[c], s);
+        }
+        s += sB[oc];
+        if (a.res) s += static_cast<const float *>(a.res)[(n.act + ipt) * C + oc];
+        s = fmaxf(s, 0.f);
+        if constexpr (NH == 0) static_cast<float *>(a.out)[opt * C + oc] = s;
+#pragma unroll
+        for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc] * s;
+    }
+#pragma unroll
+    for (int q = 0; q < NH; ++q)
+        a.maps[NH * n.px + ((int64_t)q * n.h + yo) * n.w + xo] = hh[q] + sH[NH * C + q];
+}
+
+template <int C, int TR, bool RES, int NH>
+__global__ void __launch_bounds__(NTH, (split_waves<C>()))
+k_split(ConvArgs a, Geometry geo)
+{
+    constexpr bool HEAD = NH > 0;
+    using L = SLds<C, TR, (NH > 5 ? NH : 5)>;
+    using K = SPlan<C>;
+    constexpr int NB = K::NB, R = TR / 2, NPT = L::NPT;
+    extern __shared__ v4f smem[];
+    char *sT = reinterpret_cast<char *>(smem);
+    float *sB = reinterpret_cast<float *>(sT + L::BOFF);
+    float *sS = reinterpret_cast<float *>(sT + L::SOFF);
+    float *sH = reinterpret_cast<float *>(sT + L::HOFF);
+    float *sM = reinterpret_cast<float *>(sT + L::MOFF);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps row state scalar
+    const int j = lane & 15, kq = lane >> 4, kh = kq >> 1;
+    const int strip = wave & 1, row0 = (wave >> 1) * R;
+    const int dd = a.d, blk = a.blk;
+
+    {
+        const v4f *gw = static_cast<const v4f *>(a.wpk);
+        v4f *sW = reinterpret_cast<v4f *>(sT + L::WOFF);
+#pragma unroll 6
+        for (int i = tid; i < K::WBYTES / 16; i += NTH) sW[i] = gw[i];
+    }
+    for (int i = tid; i < C; i += NTH) {
+        sB[i] = a.bias[i];
+        sS[i] = a.wscale[i];
+    }
+    // a layer whose weights the FP16 halves cannot hold has scale 0
+    const bool slow_layer = ld_const(a.wscale) == 0.f;
+    if (HEAD)
+        for (int i = tid; i < NH * C + NH; i += NTH) sH[i] = a.head[i];
+
+    const int64_t T = a.list ? (int64_t)ld_const(a.list_count)
+                      : geo.dyn ? ld_const(geo.dyn + DYN_TILES + blk) : geo.tiles[blk];
+    const int nfr = geo.dyn ? (int)ld_const(geo.dyn + DYN_NF) : geo.nf;
+    const int xcd = blockIdx.x % NXCD, slot = blockIdx.x / NXCD, nslot = gridDim.x / NXCD;
+    const int64_t chunk = (T + NXCD - 1) / NXCD;
+    const int64_t t0 = (int64_t)xcd * chunk;
+    const int64_t t1 = t0 + chunk < T ? t0 + chunk : T;
+
+    // the next tile's input in registers (off-frame points take an
+    // out-of-range buffer offset and read zero)
+    constexpr int SCH = C / 4;               // 16-byte source chunks per point
+    constexpr int NQ = NPT * SCH;
+    constexpr int NPF = (NQ + NTH - 1) / NTH;
+    // chunk k + PER of a thread is channel group and point of chunk k, DPT points on
+    constexpr int PER = C == 48 ? 3 : 1, DPT = PER * NTH / SCH;
+    static_assert(PER * NTH % SCH == 0 && SCH % 4 == 0, "staging pattern");
+    v4f pf[NPF];
+    TileWalk walk;
+    auto decode = [&](int64_t ti) { return walk.tile(a, geo, nfr, TR, TC, ti); };
+    // byte offsets of this thread's chunks from the tile's first halo point:
+    // they depend on the frame's row stride alone
+    int off[NPF], off_rs = -1;
+    auto issue = [&](const TileDec &r) {
+        if (r.rs != off_rs) {
+            off_rs = r.rs;
+#pragma unroll
+            for (int k = 0; k < NPF; ++k) {
+                const int q = tid + k * NTH, pt = q / SCH;
+                off[k] = (pt / PW * r.rs + (pt - pt / PW * PW) * r.cs) * (C * 4) + (q - pt * SCH) * 16;
+            }
+        }
+        const __amdgpu_buffer_rsrc_t rin = buf_rsrc(
+            const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * (C * 4), 0x7FFFFFFFu);
+        // an interior tile's points all lie in the frame
+        if (r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w) {
+#pragma unroll
+            for (int k = 0; k < NPF; ++k)
+                pf[k] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    rin, (k + 1) * NTH <= NQ || tid + k * NTH < NQ ? off[k] : BUF_OOB, 0, 0));
+        } else {
+            int tv = tid;
+            asm volatile("" : "+v"(tv));     // (worked out here, not kept in registers over the whole loop)
+#pragma unroll
+            for (int k = 0; k < NPF; ++k) {
+                const int q = tv + k * NTH, pt = q / SCH;
+                const int y = r.y0 + dd * (pt / PW - 1), x = r.x0 + dd * (pt - pt / PW * PW - 1);
+                const bool ok = (q < NQ) & ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
+                pf[k] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rin, ok ? off[k] : BUF_OOB, 0, 0));
+            }
+        }
+    };
+
+    // n: the current tile; nx: the next one (past the last, the current one
+    // again: its input is loaded and not used)
+    TileDec n{}, nx{};
+    int64_t ti = t0 + slot;
+    if (ti < t1) {
+        nx = decode(ti);
+        issue(nx);
+    }
+    // the first tile's data is waited for outside the loop, so that the wait at
+    // the loop top covers the loop's own path only
+#pragma unroll
+    for (int k = 0; k < NPF; ++k) asm volatile("" : : "v"(pf[k]));
+
+    // LDS addresses: this lane's MFMA operand (point (row0, 16 strip + j) of the
+    // tile, channel half kq & 1 of plane 0; its weight fragment) and this
+    // thread's staging chunks
+    const char *xb = sT + (row0 * PW + 16 * strip + j) * 32 + (kq & 1) * 16;
+    const char *wb = sT + L::WOFF + lane * 16;
+    char *stage[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int q = tid + k * NTH, pt = q / SCH, ch = q - pt * SCH;
+        stage[k] = sT + (ch >> 2) * L::PLANE + pt * 32 + (ch & 3) * 8;
+    }
+    // offset of chunk pair q (16 channels of one tap) of a tap row
+    auto pair_off = [](int q) { return (2 * q / K::CH8) * 32 + (2 * q % K::CH8 / 2) * L::PLANE; };
+
+    for (; ti < t1; ti += nslot) {
+        n = nx;
+        nx = decode(ti + nslot < t1 ? ti + nslot : ti);
+        const int Y0 = n.y0, X0 = n.x0, H = n.h, W = n.w;
+
+        // the tile's largest magnitude sets its power of two
+        float mx = 0.f;
+#pragma unroll
+        for (int k = 0; k < NPF; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pf[k][r]));
+        mx = wave_max(mx);
+        if (lane == 0) sM[wave] = mx;
+        __syncthreads();   // the previous tile's LDS reads are done (and weights staged, maxima written)
+        const v4f mv = *reinterpret_cast<const v4f *>(sM);
+        const uint32_t mb = (uint32_t)__builtin_amdgcn_readfirstlane(
+            __float_as_int(fmaxf(fmaxf(mv[0], mv[1]), fmaxf(mv[2], mv[3]))));
+        const int me = (int)(mb >> 23) - 127;            // floor(log2), -127 for zero and subnormals
+        const bool slow = slow_layer | (me >= 75) | ((me < -65) & (mb != 0));
+        const int sexp = slow || mb == 0 ? 0 : 20 * ((14 - me + 200) / 20 - 10);
+        auto convert = [&](auto scaled) {
+            const float sc = __int_as_float((127 + sexp) << 23);
+#pragma unroll
+            for (int k = 0; k < NPF; ++k) {
+                if ((k + 1) * NTH > NQ && tid + k * NTH >= NQ) continue;
+                char *d = stage[k % PER] + k / PER * (DPT * 32);
+                const v4f v = decltype(scaled)::value ? pf[k] * sc : pf[k];
+                uint2 hi{pack_h2(v[0], v[1]), pack_h2(v[2], v[3])};
+                asm("" : "+v"(hi.x), "+v"(hi.y));              // (one conversion for hi and for v - hi)
+                const h2 a0 = __builtin_bit_cast(h2, hi.x), a1 = __builtin_bit_cast(h2, hi.y);
+                const uint2 lo{
+                    pack_h2(fmaf((float)a0[0], -2048.f, v[0] * 2048.f), fmaf((float)a0[1], -2048.f, v[1] * 2048.f)),
+                    pack_h2(fmaf((float)a1[0], -2048.f, v[2] * 2048.f), fmaf((float)a1[1], -2048.f, v[3] * 2048.f))};
+                *reinterpret_cast<uint2 *>(d) = hi;
+                *reinterpret_cast<uint2 *>(d + L::LO) = lo;
+            }
+        };
+        if (sexp) convert(std::true_type{});
+        else convert(std::false_type{});
+        __syncthreads();
+
+        // the residual at this wave's output points (off-frame points read
+        // zero), then the next tile's input: in order, so waiting for the
+        // residual does not wait for the prefetch
+        v4f rr[RES ? R : 1][RES ? NB : 1];
+        const int xo = X0 + dd * (16 * strip + j);
+        if constexpr (RES) {
+            const __amdgpu_buffer_rsrc_t rres =
+                buf_rsrc(const_cast<char *>(static_cast<const char *>(a.res)) + n.act * (C * 4), 0x7FFFFFFFu);
+#pragma unroll
+            for (int y = 0; y < R; ++y) {
+                const bool ok = (Y0 + dd * (row0 + y) < H) & (xo < W);
+                const int o = (n.a0 + (row0 + y) * n.rs + (16 * strip + j) * n.cs) * (C * 4) + kq * 16;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    rr[y][nb] = __builtin_bit_cast(
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rres, (ok ? o : BUF_OOB) + nb * 64, 0, 0));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        issue(nx);
+        __builtin_amdgcn_sched_barrier(0);
+        if (slow) {
+            slow_tile<C, TR, NH>(a, n, reinterpret_cast<const float *>(static_cast<const char *>(a.wpk) + K::WBYTES), sB, sH);
+            continue;
+        }
+
+        v4f acc[R][NB], acx[R][NB];                       // wh xh; the cross sums
+#pragma unroll
+        for (int y = 0; y < R; ++y)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[y][nb] = acx[y][nb] = v4f{0.f, 0.f, 0.f, 0.f};
+        // Operands, hi and lo.  x: the fragments of K step m, one per input row
+        // (the closing steps: one per output row); two sets alternate where the
+        // register budget is one wave per SIMD, so that step m + 1 is read
+        // while the MFMAs of step m run; likewise w, weight step s.
+        constexpr int XSETS = split_waves<C>() == 1 ? 2 : 1, WSETS = XSETS;
+        v4f x[XSETS][R + 2][2], w[WSETS][NB][2];
+        auto load_x = [&](int m) {
+            const bool closing = m >= K::FULL;           // rows y (u = 0) and y + 1 (u = 1); then row y + 2 (u = 2)
+            const char *p = xb + (closing ? pair_off(2 * K::FULL) + (m == K::FULL ? kh * (PW * 32) : 2 * (PW * 32))
+                                          : kh ? pair_off(2 * m + 1) : pair_off(2 * m));
+#pragma unroll
+            for (int y = 0; y < (closing ? R : R + 2); ++y) {
+                x[m % XSETS][y][0] = *reinterpret_cast<const v4f *>(p + y * (PW * 32));
+                x[m % XSETS][y][1] = *reinterpret_cast<const v4f *>(p + y * (PW * 32) + L::LO);
+            }
+        };
+        auto load_w = [&](int s) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) w[s % WSETS][nb][h] = *reinterpret_cast<const v4f *>(wb + ((s * NB + nb) * 2 + h) * 1024);
+        };
+        load_x(0);
+        load_w(0);
+#pragma unroll
+        for (int s = 0; s < K::NSTEP; ++s) {
+            const int m = s < 3 * K::FULL ? s / 3 : s - 2 * K::FULL, u = s < 3 * K::FULL ? s % 3 : 0;
+            const bool more = s + 1 < K::NSTEP;
+            const int mn = s + 1 < 3 * K::FULL ? (s + 1) / 3 : s + 1 - 2 * K::FULL;     // x set of the next step
+            if (XSETS == 1 && s > 0 && (m >= K::FULL || u == 0)) load_x(m);
+            if (WSETS == 1 && s > 0) load_w(s);
+            if (WSETS == 2 && more) load_w(s + 1);
+            if (XSETS == 2 && more && mn != m) load_x(mn);
+            __builtin_amdgcn_sched_barrier(0);       // issued before this step's MFMAs
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int y = 0; y < R; ++y)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const v4f wv = w[s % WSETS][nb][t == 2], xv = x[m % XSETS][y + u][t == 1];
+                        v4f &d = t > 0 ? acx[y][nb] : acc[y][nb];
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, wv), __builtin_bit_cast(v8h, xv),
+                                                                   d, 0, 0, 0);
+                    }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
+        // epilogue: D row = output channel 16 nb + 4 kq + r, column = pixel j.
+        // Stores go through a buffer resource; pixels past the frame edge take
+        // an out-of-range offset and are dropped.
+        const int osh = a.out_shift, om = (1 << osh) - 1;
+        const int ohd = (H + om) >> osh, owd = (W + om) >> osh;
+        const __amdgpu_buffer_rsrc_t orow =
+            buf_rsrc(HEAD ? nullptr : static_cast<char *>(a.out) + n.act * (C * 4), HEAD ? 0u : 0x7FFFFFFFu);
+        const float ts = __int_as_float((127 - sexp) << 23);
+        v4f bias[NB], scl[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            bias[nb] = *reinterpret_cast<const v4f *>(sB + nb * 16 + kq * 4);
+            scl[nb] = *reinterpret_cast<const v4f *>(sS + nb * 16 + kq * 4) * ts;
+        }
+#pragma unroll
+        for (int y = 0; y < R; ++y) {
+            const int yo = Y0 + dd * (row0 + y);
+            const bool ok = (yo < H) & (xo < W);
+            const int opt = ((((yo & om) << osh) + (xo & om)) * ohd + (yo >> osh)) * owd + (xo >> osh);
+            float hh[NH > 0 ? NH : 1];                        // head partial sums of this lane's channels
+#pragma unroll
+            for (int q = 0; q < (NH > 0 ? NH : 1); ++q) hh[q] = 0.f;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const int oc = nb * 16 + kq * 4;
+                v4f v = acc[y][nb];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    v[r] = fmaf(fmaf(acx[y][nb][r], 0x1p-11f, v[r]), scl[nb][r], bias[nb][r]);
+                    if constexpr (RES) v[r] += rr[y][nb][r];
+                }
+                v = relu4(v);
+                if constexpr (!HEAD) {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), orow,
+                                                           (ok ? opt * (C * 4) + kq * 16 : BUF_OOB) + nb * 64, 0, 0);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc + r] * v[r];
+                }
+            }
+            if constexpr (HEAD) {
+                // the four lane groups hold disjoint channel subsets of the pixel
+#pragma unroll
+                for (int q = 0; q < NH; ++q) {
+                    hh[q] += __shfl_xor(hh[q], 16);
+                    hh[q] += __shfl_xor(hh[q], 32);
+                }
+                if (ok) {
+                    const int64_t plane = (int64_t)H * W;
+                    float *mp = a.maps + NH * n.px + (int64_t)yo * W + xo;
+                    // lane group kq writes planes kq, kq + 4, kq + 8
+#pragma unroll
+                    for (int q = 0; q < NH; ++q)
+                        if ((q & 3) == kq) mp[q * plane] = hh[q] + sH[NH * C + q];
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------- launchers
+template <int C, int TR, bool RES, int NH>
+hipError_t launch_k(const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
+{
+    using L = SLds<C, TR, (NH > 5 ? NH : 5)>;
+    static_assert(L::FITS, "LDS of the split kernel");
+    auto kern = k_split<C, TR, RES, NH>;
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, L::TOTAL);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(NTH), L::TOTAL, s, a, g);
+    return hipGetLastError();
+}
+
+template <int C, int TR>
+hipError_t launch_tr(const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
+{
+    if (a.head) return a.nh == 10 ? launch_k<C, TR, true, 10>(a, g, grid, s) : launch_k<C, TR, true, 5>(a, g, grid, s);
+    if (a.res) return launch_k<C, TR, true, 0>(a, g, grid, s);
+    return launch_k<C, TR, false, 0>(a, g, grid, s);
+}
+
+template <int C, int TR>
+int blocks_per_cu()
+{
+    int nb = 0;
+    auto kern = k_split<C, TR, true, 0>;
+    constexpr size_t sh = SLds<C, TR, 5>::TOTAL;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, NTH, sh) != hipSuccess) nb = 1;
+    return nb > 0 ? nb : 1;
+}
+
+// an FP16 value's bits (round to nearest even; |f| < 2^15) and the value of such bits
+uint16_t f16_bits(float f)
+{
+    uint32_t u;
+    std::memcpy(&u, &f, 4);
+    const uint32_t sign = (u >> 16) & 0x8000u;
+    u &= 0x7FFFFFFFu;
+    if (u >= 0x38800000u) return (uint16_t)(sign | (((u + 0xFFFu + ((u >> 13) & 1u)) >> 13) - (112u << 10)));
+    float t;                                   // below 2^-14: steps of 2^-24, as those of 0.5 + |f|
+    std::memcpy(&t, &u, 4);
+    t += 0.5f;
+    std::memcpy(&u, &t, 4);
+    return (uint16_t)(sign | (u - 0x3F000000u));
+}
+float f16_value(uint16_t h)
+{
+    const uint32_t m = h & 0x7FFFu, u = (m + (112u << 10)) << 13;
+    float f;
+    if (m >= 0x400u) std::memcpy(&f, &u, 4);
+    else f = (float)m * 0x1p-24f;
+    return h & 0x8000u ? -f : f;
+}
+
+}  // namespace
+
+bool split_takes(int C, int precision) { return C <= 48 && precision == DL_FP32; }
+
+// the fragments, then the layer's FP32 weights as they are
+size_t split_packed_bytes(int C)
+{
+    const size_t w = C == 16 ? SPlan<16>::WBYTES : C == 32 ? SPlan<32>::WBYTES : SPlan<48>::WBYTES;
+    return w + (size_t)9 * C * C * 4;
+}
+
+void split_pack_weights(int C, const float *W, void *dst, float *scale)
+{
+    const int CH8 = C / 8, NB = C / 16, FULL = 3 * CH8 / 4, NSTEP = 3 * FULL + (3 * CH8 % 4 ? 2 : 0);
+    uint16_t *o = static_cast<uint16_t *>(dst);
+    std::vector<float> up(C, 1.f);
+    bool fit = true;
+    for (int oc = 0; oc < C; ++oc) {               // max |w up| in [1, 2), up a power of two in 2^-60 .. 2^60
+        float mx = 0.f;
+        for (int k = 0; k < C * 9; ++k) mx = std::fmax(mx, std::fabs(W[(size_t)oc * C * 9 + k]));
+        const int e = mx > 0.f ? std::min(60, std::max(-60, -std::ilogb(mx))) : 0;
+        fit &= mx == 0.f || (mx >= 0x1p-60f && mx < 0x1p75f);
+        up[oc] = std::ldexp(1.f, e);
+        scale[oc] = std::ldexp(1.f, -e);
+    }
+    if (!fit) std::fill(scale, scale + C, 0.f);    // every tile in plain FP32
+    for (int st = 0; st < NSTEP; ++st)
+        for (int kq = 0; kq < 4; ++kq) {
+            // tap row and chunk (of that row's 3 C / 8) of these lanes' 8 values; u = 3: zero weights
+            int u, i;
+            if (st < 3 * FULL) {
+                u = st % 3;
+                i = 4 * (st / 3) + kq;
+            } else {
+                u = st == 3 * FULL ? kq >> 1 : kq < 2 ? 2 : 3;
+                i = 4 * FULL + (kq & 1);
+            }
+            const int v = i / CH8, c0 = (i % CH8) * 8;
+            for (int oc = 0; oc < C; ++oc) {
+                uint16_t *f = o + ((size_t)((st * NB + oc / 16) * 2) * 64 + kq * 16 + oc % 16) * 8;
+                const float *w = W + ((size_t)oc * C + c0) * 9 + 3 * (u < 3 ? u : 0) + v;
+                for (int e = 0; e < 8; ++e) {
+                    const float ws = u < 3 && fit ? w[9 * e] * up[oc] : 0.f;
+                    const uint16_t hb = f16_bits(ws);
+                    f[e] = hb;
+                    f[512 + e] = f16_bits((ws - f16_value(hb)) * 2048.f);
+                }
+            }
+        }
+    std::memcpy(o + (size_t)NSTEP * NB * 1024, W, (size_t)9 * C * C * 4);
+}
+
+int split_max_grid(int C, int tr, int ncu)
+{
+    switch (C) {
+    case 16: return ncu * (tr == 4 ? blocks_per_cu<16, 4>() : blocks_per_cu<16, 8>());
+    case 32: return ncu * (tr == 4 ? blocks_per_cu<32, 4>() : blocks_per_cu<32, 8>());
+    default: return ncu * (tr == 4 ? blocks_per_cu<48, 4>() : blocks_per_cu<48, 8>());
+    }
+}
+
+hipError_t launch_split(int C, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
+{
+    switch (C) {
+    case 16: return a.tr == 4 ? launch_tr<16, 4>(a, g, grid, s) : launch_tr<16, 8>(a, g, grid, s);
+    case 32: return a.tr == 4 ? launch_tr<32, 4>(a, g, grid, s) : launch_tr<32, 8>(a, g, grid, s);
+    case 48: return a.tr == 4 ? launch_tr<48, 4>(a, g, grid, s) : launch_tr<48, 8>(a, g, grid, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace dloc
