@@ -816,7 +816,7 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
     {
         StageTimer t(net, DL_STAGE_STEM, s);
         HIPCHK(net, launch_stem(C, d_fd, g, net->d_stem, net->d_stem + C * 9, net->cfg.offset, scale, net->d_cam,
-                                a0, net->cfg.precision, keep, stem_r, s));
+                                a0, net->cfg.precision, conv_planar(C, net->cfg.precision), keep, stem_r, s));
     }
     void *x = a0, *xn = p.ws + p.act2;      // block input, block output (alternating)
     for (int b = 0; b < net->nb; ++b) {
@@ -830,6 +830,8 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
         a.d = net->dil[b];
         a.blk = b;
         a.tr = g.trb[b];
+        a.pstride = 64;
+        a.gstride = g.total_act * 64;
         a.in_phase = lay == net->dil[b] && lay > 1;
         a.out_shift = __builtin_ctz((unsigned)lay);
         a.wscale = net->d_wscale + (size_t)(b * 2) * C;
@@ -2553,6 +2555,8 @@ int dl_debug_conv_layer(dl_net *net, const float *d_in, const float *d_res, int 
     a.bias = net->d_bias + (size_t)(blk * 2 + which) * net->C;
     a.wscale = net->d_wscale + (size_t)(blk * 2 + which) * net->C;
     a.tr = g.trb[blk];
+    a.pstride = 4 * net->C;              // the caller's plain NHWC
+    a.gstride = 64;
     const int maxg = conv_max_grid(net->C, net->cfg.precision, g.trb[blk], net->ncu);
     int grid = (int)std::min<int64_t>(g.tiles[blk], maxg);
     grid = std::max(8, grid / 8 * 8);

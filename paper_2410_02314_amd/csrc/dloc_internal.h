@@ -216,8 +216,10 @@ hipError_t launch_enumerate(const void *in, const EnumArgs &e, FrameDesc *fd, in
 // and group scales)
 // cam: per-pixel {offset, gain * in_scale} of the sensor (every frame of
 // the batch is sensor-sized), or null for the scalar offset and scale
+// planar: FP32 output in planes of 16 channels (64 bytes per point, g.total_act
+// points per plane) instead of C channels per point
 hipError_t launch_stem(int C, const FrameDesc *fd, const Geometry &g, const float *w, const float *b,
-                       float offset, float scale, const float2 *cam, void *act, int precision,
+                       float offset, float scale, const float2 *cam, void *act, int precision, bool planar,
                        const uint8_t *keep, int radius, hipStream_t s);
 hipError_t launch_zero_u32(uint32_t *p, int64_t n, hipStream_t s);
 // gated runs: keep[t] = logit[t] > tau_gate; then one compacted list of conv
@@ -244,12 +246,18 @@ struct ConvArgs {
     int in_phase;            // input and residual in phase layout d (1) or plain NHWC (0)
     int out_shift;           // output in phase layout 1 << out_shift (0: plain NHWC)
     int tr;                  // tile rows of this layer (4 or 8)
+    // FP32 to 48 channels: bytes from a point to the next and from a group of
+    // 16 channels to the next (64 and total_act * 64 in the group-planar layout
+    // the net's layers use, 4 C and 64 in plain NHWC)
+    int64_t pstride, gstride;
 };
 hipError_t launch_conv(int C, int precision, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s);
 // tile shape of the conv kernel: rows = 4 or 8; 0 picks the form's default
 // (8, except FP32 with C > 48: 4)
 void conv_tile_shape(int C, int precision, int rows, int *tr, int *tc);
 int conv_max_grid(int C, int precision, int tr, int ncu);
+// does the net keep this form's activations in planes of 16 channels?
+bool conv_planar(int C, int precision);
 // does the conv kernel of this channel count and form fit in LDS (both tile heights)?
 bool conv_supported(int C, int precision, int nh);
 size_t conv_packed_bytes(int C, int precision);

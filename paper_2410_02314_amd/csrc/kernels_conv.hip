@@ -1026,6 +1026,8 @@ int conv_max_grid(int C, int precision, int tr, int ncu)
     return b * ncu;
 }
 
+bool conv_planar(int C, int precision) { return split_takes(C, precision); }
+
 hipError_t launch_conv(int C, int precision, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
 {
     if (split_takes(C, precision)) return launch_split(C, a, g, grid, s);

@@ -25,7 +25,8 @@ namespace {
 // scale byte (region at scale_off).
 constexpr int SSEG = 1024;
 
-template <int C, int P>
+// scale_off: FP8 as above; PLANAR (FP32): floats per plane of 16 channels
+template <int C, int P, bool PLANAR>
 __global__ void __launch_bounds__(256)
 k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *__restrict__ dyn,
        const float *__restrict__ w, const float *__restrict__ b, float offset, float scale,
@@ -85,8 +86,11 @@ k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *
                 sneed[threadIdx.x] = xs < W && near_kept(keep, fd, y, y, xs, min(W - 1, xs + 63), radius);
             }
             __syncthreads();
-            for (int i = threadIdx.x; i < n * IPX; i += 256) {
-                const int px = i / IPX, q = i - (i / IPX) * IPX;
+            // items: all of a pixel's, pixel by pixel, or (PLANAR) a plane's four
+            constexpr int IPP = PLANAR ? 4 : IPX;
+            for (int qg = 0; qg < IPX; qg += IPP)
+            for (int i = threadIdx.x; i < n * IPP; i += 256) {
+                const int px = i / IPP, q = qg + i - (i / IPP) * IPP;
                 const int x = x0 + px;
                 if (!sneed[px >> 6]) continue;
                 float xin[9];
@@ -94,7 +98,8 @@ k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *
                 for (int u = 0; u < 3; ++u)
 #pragma unroll
                     for (int v = 0; v < 3; ++v) xin[u * 3 + v] = sx[u][px + v];
-                const int64_t base = (fd.act_off + (int64_t)y * W + x) * C + q * CQ;   // plain NHWC
+                const int64_t pt = fd.act_off + (int64_t)y * W + x;
+                const int64_t base = PLANAR ? (q >> 2) * scale_off + pt * 16 + (q & 3) * CQ : pt * C + q * CQ;
                 float o[CQ];
 #pragma unroll
                 for (int k = 0; k < CQ; ++k) o[k] = sb[q * CQ + k];
@@ -118,7 +123,6 @@ k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *
                             uint4{fp8_pack4(o[0], o[1], o[2], o[3], sv), fp8_pack4(o[4], o[5], o[6], o[7], sv),
                                   fp8_pack4(o[8], o[9], o[10], o[11], sv), fp8_pack4(o[12], o[13], o[14], o[15], sv)};
                         if ((q & 1) == 0) {
-                            const int64_t pt = fd.act_off + (int64_t)y * W + x;
                             static_cast<uint8_t *>(act)[scale_off + 2 * pt + (q >> 1)] = (uint8_t)sbyte;
                         }
                     }
@@ -136,19 +140,22 @@ k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *
 
 template <int C>
 hipError_t stem_c(const FrameDesc *fd, const Geometry &g, const float *w, const float *b, float offset,
-                  float scale, const float2 *cam, void *act, int precision, const uint8_t *keep, int radius,
-                  hipStream_t s)
+                  float scale, const float2 *cam, void *act, int precision, bool planar, const uint8_t *keep,
+                  int radius, hipStream_t s)
 {
     const unsigned grid = (unsigned)std::min<int64_t>(g.total_rows, 8192);
     const int64_t soff = g.total_act * C;        // FP8: byte offset of the group scales
     if (precision == DL_FP8)
-        hipLaunchKernelGGL((k_stem<C, DL_FP8>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
+        hipLaunchKernelGGL((k_stem<C, DL_FP8, false>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
                            scale, cam, act, soff, keep, radius);
     else if (precision == DL_BF16)
-        hipLaunchKernelGGL((k_stem<C, DL_BF16>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
+        hipLaunchKernelGGL((k_stem<C, DL_BF16, false>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
                            scale, cam, act, soff, keep, radius);
+    else if (planar && C <= 48)
+        hipLaunchKernelGGL((k_stem<C, DL_FP32, C <= 48>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
+                           scale, cam, act, g.total_act * 16, keep, radius);
     else
-        hipLaunchKernelGGL((k_stem<C, DL_FP32>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
+        hipLaunchKernelGGL((k_stem<C, DL_FP32, false>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
                            scale, cam, act, soff, keep, radius);
     return hipGetLastError();
 }
@@ -602,14 +609,14 @@ hipError_t launch_active_lists(const FrameDesc *fd, const Geometry &g, const uin
 }
 
 hipError_t launch_stem(int C, const FrameDesc *fd, const Geometry &g, const float *w, const float *b,
-                       float offset, float scale, const float2 *cam, void *act, int precision,
+                       float offset, float scale, const float2 *cam, void *act, int precision, bool planar,
                        const uint8_t *keep, int radius, hipStream_t s)
 {
     switch (C) {
-    case 16: return stem_c<16>(fd, g, w, b, offset, scale, cam, act, precision, keep, radius, s);
-    case 32: return stem_c<32>(fd, g, w, b, offset, scale, cam, act, precision, keep, radius, s);
-    case 48: return stem_c<48>(fd, g, w, b, offset, scale, cam, act, precision, keep, radius, s);
-    case 64: return stem_c<64>(fd, g, w, b, offset, scale, cam, act, precision, keep, radius, s);
+    case 16: return stem_c<16>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
+    case 32: return stem_c<32>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
+    case 48: return stem_c<48>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
+    case 64: return stem_c<64>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -23,28 +23,37 @@
 // such magnitudes) takes plain FP32 FMAs instead (slow_tile), so those come out
 // as in FP32; NaNs propagate by themselves.
 //
-// Tiling.  Tiles, persistent workgroups, XCD ranges and the register prefetch
-// of the next tile as in kernels_conv.hip.  TR x 32 output points per tile and
-// four waves: wave w computes columns 16 (w & 1) .. + 15 of rows R (w >> 1) ..
-// + R - 1, R = TR / 2, for all output channels.  One K step takes 32 values of
-// one tap row u: an input row's fragment is read from LDS once per step and
-// multiplied into the (up to three) output rows it belongs to, and a weight
-// fragment once for the wave's R rows.  Per K step of three tap rows a wave of
-// an 8-row tile reads 18 + 12 KB (C = 48) for 108 MFMAs, 69 bytes per clock
-// and CU at full MFMA rate of the LDS's 128; one row of 32 pixels per wave
-// (the layout of kernels_conv.hip) would read 139.
+// Tiling.  Tiles, persistent workgroups and XCD ranges as in kernels_conv.hip:
+// TR x 32 output points per tile.  A wave computes 16 columns of R rows for all
+// output channels.  One K step takes 32 values of one tap row u: an input row's
+// fragment is read from LDS once per step and multiplied into the (up to three)
+// output rows it belongs to, and a weight fragment once for the wave's R rows.
 //
-// LDS.  hi and lo values in planes of 16 channels, 32 bytes per point and
-// plane: a point stride of 8 dwords, which a 16-byte read of 16 points x 2
-// channel halves serves without bank conflicts, and no padding, so that
-// weights (86 KB) and tile (65 KB) of 48 channels fit beside each other, and
-// two workgroups of 32 channels (80 KB each) on a CU.
+// Activations in HBM and LDS lie in planes of 16 channels, 64 bytes per point
+// and plane in HBM: a wave stores 16 points x 16 channels as 1 KB of whole
+// lines, and a group's tile rows are contiguous.  (In NHWC with 48 channels
+// those stores are 64-byte pieces 192 bytes apart: 2.33 ms against 2.18.)  In
+// LDS a plane holds 32 bytes per point, hi or lo: a point stride of 8 dwords,
+// which a 16-byte read of 16 points x 2 channel halves serves without bank
+// conflicts, and no padding.
 //
-// Measured (4 x 2048^2 points, mean launch without head): 48 channels 5.11 ms
-// with FP32 MFMAs, 2.32 ms here; 32 channels 2.40 ms, 1.15 ms here.  What is
-// left above the HBM bytes' 1.5 ms (48 channels, at the 5.2 TB/s of a copy) is
-// the conversion and the epilogue, which one wave per SIMD does not overlap
-// with its MFMAs.
+// Two kernels:
+//   k_split (16 and 32 channels) stages a tile's hi and lo planes at once, four
+// waves of R = TR / 2 rows; weights and tile take 80 KB (32 channels, 8 rows),
+// so two workgroups share a CU and hide each other's conversion and epilogue.
+//   k_pipe (48 channels) has 86 KB of weights and room for one workgroup, so it
+// walks K in groups of 16 channels through two LDS buffers: while the MFMAs of
+// one group run, the next group is converted into the other buffer and the
+// loads three groups on are in flight, with one barrier per group.  TR waves of
+// R = 2 rows, two per SIMD.  The tile's exponent is then known group by group:
+// a later group that needs a lower one has the sums so far rescaled.
+//
+// Measured (mean launch without head, 4 x 2048^2 points): 48 channels 5.11 ms
+// with FP32 MFMAs, 2.32 ms as k_split, 2.18 ms as k_pipe; 32 channels 2.40 and
+// 1.15 ms.  Bounds: the HBM bytes take 1.5 and 1.0 ms at the 5.2 TB/s of a copy;
+// the MFMAs of 48 channels 1.4 ms at the 1.66 PFLOP/s that chains of this MFMA
+// sustain with two waves per SIMD (24 cycles each, not 16), and the clock falls
+// from 2.4 to 1.9 GHz under them.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -87,11 +96,6 @@ template <int C, int TR, int NH> struct SLds {
     static constexpr bool FITS = TOTAL <= 160 * 1024;
 };
 
-// waves per SIMD the register budget is sized for: two workgroups of up to 32
-// channels share a CU (4-row tiles of 48 channels do not fit twice beside
-// their weights)
-template <int C> constexpr int split_waves() { return C <= 32 ? 2 : 1; }
-
 __device__ __forceinline__ uint32_t pack_h2(float a, float b)
 {
     return __builtin_bit_cast(uint32_t, (h2{(_Float16)a, (_Float16)b}));
@@ -122,7 +126,7 @@ __device__ __forceinline__ void slow_tile(const ConvArgs &a, const TileDec &n, c
     const int dd = a.d, row = threadIdx.x / TC, col = threadIdx.x % TC;
     const int yo = n.y0 + dd * row, xo = n.x0 + dd * col;
     if (row >= TR || yo >= n.h || xo >= n.w) return;
-    const float *gx = static_cast<const float *>(a.in) + n.act * C;
+    const char *gx = static_cast<const char *>(a.in) + n.act * a.pstride;
     const int64_t ipt = n.a0 + (int64_t)row * n.rs + col * n.cs;
     const int osh = a.out_shift, om = (1 << osh) - 1;
     const int64_t opt = n.act + ((((yo & om) << osh) + (xo & om)) * (int64_t)((n.h + om) >> osh) + (yo >> osh)) *
@@ -135,14 +139,16 @@ __device__ __forceinline__ void slow_tile(const ConvArgs &a, const TileDec &n, c
         for (int tap = 0; tap < 9; ++tap) {
             const int u = tap / 3 - 1, v = tap % 3 - 1, yy = yo + dd * u, xx = xo + dd * v;
             if ((unsigned)yy >= (unsigned)n.h || (unsigned)xx >= (unsigned)n.w) continue;
-            const float *xp = gx + (ipt + u * n.rs + v * n.cs) * C;
+            const char *xp = gx + (ipt + u * n.rs + v * n.cs) * a.pstride;
 #pragma unroll 1
-            for (int c = 0; c < C; ++c) s = fmaf(gw[(oc * C + c) * 9 + tap], xp[c], s);
+            for (int c = 0; c < C; ++c)
+                s = fmaf(gw[(oc * C + c) * 9 + tap], *reinterpret_cast<const float *>(xp + (c >> 4) * a.gstride + (c & 15) * 4), s);
         }
         s += sB[oc];
-        if (a.res) s += static_cast<const float *>(a.res)[(n.act + ipt) * C + oc];
+        const int64_t co = (oc >> 4) * a.gstride + (oc & 15) * 4;
+        if (a.res) s += *reinterpret_cast<const float *>(static_cast<const char *>(a.res) + (n.act + ipt) * a.pstride + co);
         s = fmaxf(s, 0.f);
-        if constexpr (NH == 0) static_cast<float *>(a.out)[opt * C + oc] = s;
+        if constexpr (NH == 0) *reinterpret_cast<float *>(static_cast<char *>(a.out) + opt * a.pstride + co) = s;
 #pragma unroll
         for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc] * s;
     }
@@ -152,7 +158,7 @@ __device__ __forceinline__ void slow_tile(const ConvArgs &a, const TileDec &n, c
 }
 
 template <int C, int TR, bool RES, int NH>
-__global__ void __launch_bounds__(NTH, (split_waves<C>()))
+__global__ void __launch_bounds__(NTH, 2)
 k_split(ConvArgs a, Geometry geo)
 {
     constexpr bool HEAD = NH > 0;
@@ -197,13 +203,9 @@ k_split(ConvArgs a, Geometry geo)
 
     // the next tile's input in registers (off-frame points take an
     // out-of-range buffer offset and read zero)
-    constexpr int SCH = C / 4;               // 16-byte source chunks per point
-    constexpr int NQ = NPT * SCH;
+    constexpr int NQ = NPT * 4;              // 16-byte chunks of 16 channels of the tile's points
     constexpr int NPF = (NQ + NTH - 1) / NTH;
-    // chunk k + PER of a thread is channel group and point of chunk k, DPT points on
-    constexpr int PER = C == 48 ? 3 : 1, DPT = PER * NTH / SCH;
-    static_assert(PER * NTH % SCH == 0 && SCH % 4 == 0, "staging pattern");
-    v4f pf[NPF];
+    v4f pf[NB][NPF];
     TileWalk walk;
     auto decode = [&](int64_t ti) { return walk.tile(a, geo, nfr, TR, TC, ti); };
     // byte offsets of this thread's chunks from the tile's first halo point:
@@ -214,29 +216,34 @@ k_split(ConvArgs a, Geometry geo)
             off_rs = r.rs;
 #pragma unroll
             for (int k = 0; k < NPF; ++k) {
-                const int q = tid + k * NTH, pt = q / SCH;
-                off[k] = (pt / PW * r.rs + (pt - pt / PW * PW) * r.cs) * (C * 4) + (q - pt * SCH) * 16;
+                const int q = tid + k * NTH, pt = q >> 2;
+                off[k] = (pt / PW * r.rs + (pt - pt / PW * PW) * r.cs) * (int)a.pstride + (q & 3) * 16;
             }
         }
-        const __amdgpu_buffer_rsrc_t rin = buf_rsrc(
-            const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * (C * 4), 0x7FFFFFFFu);
+        char *p = const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride;
         // an interior tile's points all lie in the frame
-        if (r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w) {
+        const bool inside = r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w;
+        int o[NPF];
+        if (inside) {
 #pragma unroll
-            for (int k = 0; k < NPF; ++k)
-                pf[k] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
-                                                    rin, (k + 1) * NTH <= NQ || tid + k * NTH < NQ ? off[k] : BUF_OOB, 0, 0));
+            for (int k = 0; k < NPF; ++k) o[k] = (k + 1) * NTH <= NQ || tid + k * NTH < NQ ? off[k] : BUF_OOB;
         } else {
             int tv = tid;
             asm volatile("" : "+v"(tv));     // (worked out here, not kept in registers over the whole loop)
 #pragma unroll
             for (int k = 0; k < NPF; ++k) {
-                const int q = tv + k * NTH, pt = q / SCH;
+                const int q = tv + k * NTH, pt = q >> 2;
                 const int y = r.y0 + dd * (pt / PW - 1), x = r.x0 + dd * (pt - pt / PW * PW - 1);
                 const bool ok = (q < NQ) & ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
-                pf[k] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rin, ok ? off[k] : BUF_OOB, 0, 0));
+                o[k] = ok ? off[k] : BUF_OOB;
             }
         }
+#pragma unroll
+        for (int g = 0; g < NB; ++g)
+#pragma unroll
+            for (int k = 0; k < NPF; ++k)
+                pf[g][k] = __builtin_bit_cast(
+                    v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(p + g * a.gstride, 0x7FFFFFFFu), o[k], 0, 0));
     };
 
     // n: the current tile; nx: the next one (past the last, the current one
@@ -250,19 +257,16 @@ k_split(ConvArgs a, Geometry geo)
     // the first tile's data is waited for outside the loop, so that the wait at
     // the loop top covers the loop's own path only
 #pragma unroll
-    for (int k = 0; k < NPF; ++k) asm volatile("" : : "v"(pf[k]));
+    for (int g = 0; g < NB; ++g)
+#pragma unroll
+        for (int k = 0; k < NPF; ++k) asm volatile("" : : "v"(pf[g][k]));
 
     // LDS addresses: this lane's MFMA operand (point (row0, 16 strip + j) of the
     // tile, channel half kq & 1 of plane 0; its weight fragment) and this
     // thread's staging chunks
     const char *xb = sT + (row0 * PW + 16 * strip + j) * 32 + (kq & 1) * 16;
     const char *wb = sT + L::WOFF + lane * 16;
-    char *stage[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int q = tid + k * NTH, pt = q / SCH, ch = q - pt * SCH;
-        stage[k] = sT + (ch >> 2) * L::PLANE + pt * 32 + (ch & 3) * 8;
-    }
+    char *stage = sT + (tid >> 2) * 32 + (tid & 3) * 8;
     // offset of chunk pair q (16 channels of one tap) of a tap row
     auto pair_off = [](int q) { return (2 * q / K::CH8) * 32 + (2 * q % K::CH8 / 2) * L::PLANE; };
 
@@ -274,9 +278,11 @@ k_split(ConvArgs a, Geometry geo)
         // the tile's largest magnitude sets its power of two
         float mx = 0.f;
 #pragma unroll
-        for (int k = 0; k < NPF; ++k)
+        for (int g = 0; g < NB; ++g)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pf[k][r]));
+            for (int k = 0; k < NPF; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pf[g][k][r]));
         mx = wave_max(mx);
         if (lane == 0) sM[wave] = mx;
         __syncthreads();   // the previous tile's LDS reads are done (and weights staged, maxima written)
@@ -289,10 +295,11 @@ k_split(ConvArgs a, Geometry geo)
         auto convert = [&](auto scaled) {
             const float sc = __int_as_float((127 + sexp) << 23);
 #pragma unroll
-            for (int k = 0; k < NPF; ++k) {
+            for (int i = 0; i < NB * NPF; ++i) {
+                const int g = i % NB, k = i / NB;
                 if ((k + 1) * NTH > NQ && tid + k * NTH >= NQ) continue;
-                char *d = stage[k % PER] + k / PER * (DPT * 32);
-                const v4f v = decltype(scaled)::value ? pf[k] * sc : pf[k];
+                char *d = stage + g * L::PLANE + k * (NTH / 4 * 32);
+                const v4f v = decltype(scaled)::value ? pf[g][k] * sc : pf[g][k];
                 uint2 hi{pack_h2(v[0], v[1]), pack_h2(v[2], v[3])};
                 asm("" : "+v"(hi.x), "+v"(hi.y));              // (one conversion for hi and for v - hi)
                 const h2 a0 = __builtin_bit_cast(h2, hi.x), a1 = __builtin_bit_cast(h2, hi.y);
@@ -313,16 +320,19 @@ k_split(ConvArgs a, Geometry geo)
         v4f rr[RES ? R : 1][RES ? NB : 1];
         const int xo = X0 + dd * (16 * strip + j);
         if constexpr (RES) {
-            const __amdgpu_buffer_rsrc_t rres =
-                buf_rsrc(const_cast<char *>(static_cast<const char *>(a.res)) + n.act * (C * 4), 0x7FFFFFFFu);
+            __amdgpu_buffer_rsrc_t rres[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                rres[nb] = buf_rsrc(const_cast<char *>(static_cast<const char *>(a.res)) + n.act * a.pstride + nb * a.gstride,
+                                    0x7FFFFFFFu);
 #pragma unroll
             for (int y = 0; y < R; ++y) {
                 const bool ok = (Y0 + dd * (row0 + y) < H) & (xo < W);
-                const int o = (n.a0 + (row0 + y) * n.rs + (16 * strip + j) * n.cs) * (C * 4) + kq * 16;
+                const int o = ok ? (n.a0 + (row0 + y) * n.rs + (16 * strip + j) * n.cs) * (int)a.pstride + kq * 16 : BUF_OOB;
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
                     rr[y][nb] = __builtin_bit_cast(
-                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rres, (ok ? o : BUF_OOB) + nb * 64, 0, 0));
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rres[nb], o, 0, 0));
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -338,39 +348,30 @@ k_split(ConvArgs a, Geometry geo)
         for (int y = 0; y < R; ++y)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[y][nb] = acx[y][nb] = v4f{0.f, 0.f, 0.f, 0.f};
-        // Operands, hi and lo.  x: the fragments of K step m, one per input row
-        // (the closing steps: one per output row); two sets alternate where the
-        // register budget is one wave per SIMD, so that step m + 1 is read
-        // while the MFMAs of step m run; likewise w, weight step s.
-        constexpr int XSETS = split_waves<C>() == 1 ? 2 : 1, WSETS = XSETS;
-        v4f x[XSETS][R + 2][2], w[WSETS][NB][2];
+        // operands, hi and lo: x the fragments of K step m, one per input row
+        // (the closing steps: one per output row), w weight step s
+        v4f x[R + 2][2], w[NB][2];
         auto load_x = [&](int m) {
             const bool closing = m >= K::FULL;           // rows y (u = 0) and y + 1 (u = 1); then row y + 2 (u = 2)
             const char *p = xb + (closing ? pair_off(2 * K::FULL) + (m == K::FULL ? kh * (PW * 32) : 2 * (PW * 32))
                                           : kh ? pair_off(2 * m + 1) : pair_off(2 * m));
 #pragma unroll
             for (int y = 0; y < (closing ? R : R + 2); ++y) {
-                x[m % XSETS][y][0] = *reinterpret_cast<const v4f *>(p + y * (PW * 32));
-                x[m % XSETS][y][1] = *reinterpret_cast<const v4f *>(p + y * (PW * 32) + L::LO);
+                x[y][0] = *reinterpret_cast<const v4f *>(p + y * (PW * 32));
+                x[y][1] = *reinterpret_cast<const v4f *>(p + y * (PW * 32) + L::LO);
             }
         };
         auto load_w = [&](int s) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) w[s % WSETS][nb][h] = *reinterpret_cast<const v4f *>(wb + ((s * NB + nb) * 2 + h) * 1024);
+                for (int h = 0; h < 2; ++h) w[nb][h] = *reinterpret_cast<const v4f *>(wb + ((s * NB + nb) * 2 + h) * 1024);
         };
-        load_x(0);
-        load_w(0);
 #pragma unroll
         for (int s = 0; s < K::NSTEP; ++s) {
             const int m = s < 3 * K::FULL ? s / 3 : s - 2 * K::FULL, u = s < 3 * K::FULL ? s % 3 : 0;
-            const bool more = s + 1 < K::NSTEP;
-            const int mn = s + 1 < 3 * K::FULL ? (s + 1) / 3 : s + 1 - 2 * K::FULL;     // x set of the next step
-            if (XSETS == 1 && s > 0 && (m >= K::FULL || u == 0)) load_x(m);
-            if (WSETS == 1 && s > 0) load_w(s);
-            if (WSETS == 2 && more) load_w(s + 1);
-            if (XSETS == 2 && more && mn != m) load_x(mn);
+            if (m >= K::FULL || u == 0) load_x(m);
+            load_w(s);
             __builtin_amdgcn_sched_barrier(0);       // issued before this step's MFMAs
 #pragma unroll
             for (int t = 0; t < 3; ++t)
@@ -378,7 +379,7 @@ k_split(ConvArgs a, Geometry geo)
                 for (int y = 0; y < R; ++y)
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
-                        const v4f wv = w[s % WSETS][nb][t == 2], xv = x[m % XSETS][y + u][t == 1];
+                        const v4f wv = w[nb][t == 2], xv = x[y + u][t == 1];
                         v4f &d = t > 0 ? acx[y][nb] : acc[y][nb];
                         d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, wv), __builtin_bit_cast(v8h, xv),
                                                                    d, 0, 0, 0);
@@ -391,8 +392,11 @@ k_split(ConvArgs a, Geometry geo)
         // an out-of-range offset and are dropped.
         const int osh = a.out_shift, om = (1 << osh) - 1;
         const int ohd = (H + om) >> osh, owd = (W + om) >> osh;
-        const __amdgpu_buffer_rsrc_t orow =
-            buf_rsrc(HEAD ? nullptr : static_cast<char *>(a.out) + n.act * (C * 4), HEAD ? 0u : 0x7FFFFFFFu);
+        __amdgpu_buffer_rsrc_t orow[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            orow[nb] = buf_rsrc(HEAD ? nullptr : static_cast<char *>(a.out) + n.act * a.pstride + nb * a.gstride,
+                                HEAD ? 0u : 0x7FFFFFFFu);
         const float ts = __int_as_float((127 - sexp) << 23);
         v4f bias[NB], scl[NB];
 #pragma unroll
@@ -419,8 +423,8 @@ k_split(ConvArgs a, Geometry geo)
                 }
                 v = relu4(v);
                 if constexpr (!HEAD) {
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), orow,
-                                                           (ok ? opt * (C * 4) + kq * 16 : BUF_OOB) + nb * 64, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), orow[nb],
+                                                           ok ? opt * (int)a.pstride + kq * 16 : BUF_OOB, 0, 0);
                 } else {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
@@ -448,13 +452,379 @@ k_split(ConvArgs a, Geometry geo)
     }
 }
 
+// ---- pipelined by channel group ----
+// LDS: two buffers of one 16-channel group's tile (hi and lo planes), all
+// weights, the per-channel constants, the wave maxima of two groups
+template <int C, int TR, int NH> struct PLds {
+    static constexpr int NPT = (TR + 2) * PW;
+    // (room for the chunks of the threads past the last point)
+    static constexpr int PLANE = (NPT + 16 * TR - 1) / (16 * TR) * (16 * TR) * 32, BUF = 2 * PLANE;
+    static constexpr int WBYTES = C / 16 * 5 * (C / 16) * 2048;
+    static constexpr int WOFF = 2 * BUF;
+    static constexpr int BOFF = WOFF + WBYTES;
+    static constexpr int SOFF = BOFF + C * 4;
+    static constexpr int HOFF = SOFF + C * 4;
+    static constexpr int MOFF = align16(HOFF + (NH * C + NH) * 4);   // wave maxima [2][8]
+    static constexpr int TOTAL = MOFF + 64;
+    static constexpr bool FITS = TOTAL <= 160 * 1024;
+};
+
+template <int C, int TR, bool RES, int NH>
+__global__ void __launch_bounds__(TR * 64, 2)
+k_pipe(ConvArgs a, Geometry geo)
+{
+    constexpr bool HEAD = NH > 0;
+    using L = PLds<C, TR, (NH > 5 ? NH : 5)>;
+    constexpr int R = 2, NTH = TR * 64, NB = C / 16, G = C / 16, NPT = L::NPT;
+    extern __shared__ v4f smem[];
+    char *sT = reinterpret_cast<char *>(smem);
+    float *sB = reinterpret_cast<float *>(sT + L::BOFF);
+    float *sS = reinterpret_cast<float *>(sT + L::SOFF);
+    float *sH = reinterpret_cast<float *>(sT + L::HOFF);
+    float *sM = reinterpret_cast<float *>(sT + L::MOFF);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, kq = lane >> 4, kh = kq >> 1;
+    const int strip = wave & 1, row0 = (wave >> 1) * R;
+    const int dd = a.d, blk = a.blk;
+    {
+        const v4f *gw = static_cast<const v4f *>(a.wpk);
+        v4f *sW = reinterpret_cast<v4f *>(sT + L::WOFF);
+#pragma unroll 6
+        for (int i = tid; i < L::WBYTES / 16; i += NTH) sW[i] = gw[i];
+    }
+    for (int i = tid; i < C; i += NTH) {
+        sB[i] = a.bias[i];
+        sS[i] = a.wscale[i];
+    }
+    const bool slow_layer = ld_const(a.wscale) == 0.f;
+    if (HEAD)
+        for (int i = tid; i < NH * C + NH; i += NTH) sH[i] = a.head[i];
+
+    const int64_t T = a.list ? (int64_t)ld_const(a.list_count)
+                      : geo.dyn ? ld_const(geo.dyn + DYN_TILES + blk) : geo.tiles[blk];
+    const int nfr = geo.dyn ? (int)ld_const(geo.dyn + DYN_NF) : geo.nf;
+    const int xcd = blockIdx.x % NXCD, slot = blockIdx.x / NXCD, nslot = gridDim.x / NXCD;
+    const int64_t chunk = (T + NXCD - 1) / NXCD;
+    const int64_t t0 = (int64_t)xcd * chunk;
+    const int64_t t1 = t0 + chunk < T ? t0 + chunk : T;
+    int64_t ti = t0 + slot;
+    if (ti >= t1) return;
+
+    // staging: chunk k of a thread is 4 channels (16 bytes) of one point of the
+    // group's tile; rows and columns as multiples of d, offsets from the tile's
+    // first halo point (which change with the frame's row stride)
+    constexpr int NQ = NPT * 4, NPF = (NQ + NTH - 1) / NTH;
+    v4f pf[3][NPF];
+    int off[NPF], dy[NPF], dx[NPF], off_rs = -1;
+    char *stage = sT + (tid >> 2) * 32 + (tid & 3) * 8;
+#pragma unroll
+    for (int k = 0; k < NPF; ++k) {
+        const int q = tid + k * NTH, pt = q >> 2;
+        dy[k] = q < NQ ? dd * (pt / PW) : 1 << 30;       // past the last chunk: off every frame
+        dx[k] = dd * (pt - pt / PW * PW);
+    }
+    TileWalk walk;
+    auto decode = [&](int64_t t) { return walk.tile(a, geo, nfr, TR, TC, t < t1 ? t : t1 - 1); };
+    auto offsets = [&](const TileDec &r) {
+        if (r.rs == off_rs) return;
+        off_rs = r.rs;
+#pragma unroll
+        for (int k = 0; k < NPF; ++k) {
+            const int q = tid + k * NTH, pt = q >> 2;
+            off[k] = (pt / PW * r.rs + (pt - pt / PW * PW) * r.cs) * (int)a.pstride + (q & 3) * 16;
+        }
+    };
+    struct Src {
+        char *p;                           // the tile's first halo point, group 0
+        int y, x, h, w;
+    };
+    auto source = [&](const TileDec &r) {
+        return Src{const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride,
+                   r.y0 - dd, r.x0 - dd, r.h, r.w};
+    };
+    auto load = [&](const Src &s, int g, int k) {
+        const bool ok = ((unsigned)(s.y + dy[k]) < (unsigned)s.h) & ((unsigned)(s.x + dx[k]) < (unsigned)s.w);
+        return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(s.p + g * a.gstride, 0x7FFFFFFFu),
+                                                                              ok ? off[k] : BUF_OOB, 0, 0));
+    };
+    auto largest = [&](const v4f (&p)[NPF]) {
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < NPF; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m = fmaxf(m, fabsf(p[k][r]));
+        return wave_max(m);
+    };
+    auto convert = [&](const v4f &p, float sc, char *d) {
+        const v4f v = p * sc;
+        uint2 hi{pack_h2(v[0], v[1]), pack_h2(v[2], v[3])};
+        asm("" : "+v"(hi.x), "+v"(hi.y));                      // (one conversion for hi and for v - hi)
+        const h2 a0 = __builtin_bit_cast(h2, hi.x), a1 = __builtin_bit_cast(h2, hi.y);
+        const uint2 lo{pack_h2(fmaf((float)a0[0], -2048.f, v[0] * 2048.f), fmaf((float)a0[1], -2048.f, v[1] * 2048.f)),
+                       pack_h2(fmaf((float)a1[0], -2048.f, v[2] * 2048.f), fmaf((float)a1[1], -2048.f, v[3] * 2048.f))};
+        *reinterpret_cast<uint2 *>(d) = hi;
+        *reinterpret_cast<uint2 *>(d + L::PLANE) = lo;
+    };
+    // the largest power-of-two step (a multiple of 20) a group of largest
+    // magnitude bits mb allows; 60 for an all-zero group
+    auto fit_exp = [](uint32_t mb) {
+        const int e = (int)(mb >> 23) - 127;
+        return e < -65 ? 60 : e >= 75 ? -60 : 20 * ((14 - e + 200) / 20 - 10);
+    };
+    auto group_max = [&](int b) {
+        const v4f *p = reinterpret_cast<const v4f *>(sM + 8 * b);
+        float m = fmaxf(fmaxf(p[0][0], p[0][1]), fmaxf(p[0][2], p[0][3]));
+        if constexpr (TR == 8) m = fmaxf(m, fmaxf(fmaxf(p[1][0], p[1][1]), fmaxf(p[1][2], p[1][3])));
+        return (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(m));
+    };
+
+    const char *xb = sT + (row0 * PW + 16 * strip + j) * 32 + (kq & 1) * 16;
+    const char *wb = sT + L::WOFF + lane * 16;
+
+    // n: the tile in progress, n1: the next (past the last: the last again, its
+    // input is loaded and not used)
+    TileDec n = decode(ti), n1 = decode(ti + nslot);
+    offsets(n);
+    Src s1 = source(n);
+#pragma unroll
+    for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int k = 0; k < NPF; ++k) pf[g][k] = load(s1, g, k);
+    // group 0 of the first tile into buffer 0, the maxima of groups 0 and 1
+    {
+        const float m0 = largest(pf[0]);
+        if (lane == 0) sM[wave] = m0;
+    }
+    __syncthreads();
+    uint32_t tmax = group_max(0);          // largest magnitude bits of the tile so far
+    int sexp = fit_exp(tmax);
+    {
+        const float sc = __int_as_float((127 + sexp) << 23);
+#pragma unroll
+        for (int k = 0; k < NPF; ++k)
+            convert(pf[0][k], sc, stage + k * (NTH / 4 * 32));
+    }
+    offsets(n1);
+    s1 = source(n1);
+#pragma unroll
+    for (int k = 0; k < NPF; ++k) pf[0][k] = load(s1, 0, k);
+    {
+        const float m1 = largest(pf[1]);
+        if (lane == 0) sM[8 + wave] = m1;
+    }
+
+    int buf = 0;                           // buffer of the group in progress
+    for (; ti < t1; ti += nslot) {
+        const TileDec n2 = decode(ti + 2 * nslot);
+        const Src s2 = source(n2);
+        const int Y0 = n.y0, X0 = n.x0, H = n.h, W = n.w, xo = X0 + dd * (16 * strip + j);
+        v4f acc[R][NB], acx[R][NB];       // wh xh; the cross sums
+#pragma unroll
+        for (int y = 0; y < R; ++y)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[y][nb] = acx[y][nb] = v4f{0.f, 0.f, 0.f, 0.f};
+        v4f rr[RES ? R : 1][RES ? NB : 1];
+        int nexp = 0;                      // the next tile's: its group 0 is converted during this one's last
+        uint32_t nmax = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            __syncthreads();   // group g staged, the other buffer free, the next group's maxima written
+            // the next group's exponent: this tile's (lowered where the group
+            // needs it, the sums so far rescaled), or the next tile's own
+            const uint32_t gm = group_max(buf ^ 1);
+            const int e = fit_exp(gm);
+            int se = e;
+            if (g + 1 < G) {
+                tmax = max(tmax, gm);
+                se = min(sexp, e);
+                if (se < sexp) {
+                    const float f = __int_as_float((127 + se - sexp) << 23);
+#pragma unroll
+                    for (int y = 0; y < R; ++y)
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) {
+                            acc[y][nb] *= f;
+                            acx[y][nb] *= f;
+                        }
+                }
+                sexp = se;
+            } else {
+                nexp = e;
+                nmax = gm;
+                offsets(n2);
+            }
+            const float sc = __int_as_float((127 + se) << 23);
+            const Src &sl = g + 1 < G ? s1 : s2;
+            const int ps = (g + 1) % 3;                  // the set of the next group, then of the group loaded
+            char *sd = stage + (buf ^ 1) * L::BUF;
+            const char *xp = xb + buf * L::BUF;
+            if (RES && g + 1 == G) {
+                __amdgpu_buffer_rsrc_t rres[NB];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    rres[nb] = buf_rsrc(const_cast<char *>(static_cast<const char *>(a.res)) + n.act * a.pstride + nb * a.gstride,
+                                        0x7FFFFFFFu);
+#pragma unroll
+                for (int y = 0; y < R; ++y) {
+                    const bool ok = (Y0 + dd * (row0 + y) < H) & (xo < W);
+                    const int o = ok ? (n.a0 + (row0 + y) * n.rs + (16 * strip + j) * n.cs) * (int)a.pstride + kq * 16 : BUF_OOB;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        rr[y][nb] = __builtin_bit_cast(
+                            v4f, __builtin_amdgcn_raw_buffer_load_b128(rres[nb], o, 0, 0));
+                }
+            }
+            // operands: x[0] rows of the three full steps (then of the second
+            // closing step), x[1] of the first closing step; w alternates
+            v4f x[2][R + 2][2], w[2][NB][2];
+            auto read_x = [&](int set, const char *p, int rows) {
+#pragma unroll
+                for (int y = 0; y < rows; ++y) {
+                    x[set][y][0] = *reinterpret_cast<const v4f *>(p + y * (PW * 32));
+                    x[set][y][1] = *reinterpret_cast<const v4f *>(p + y * (PW * 32) + L::PLANE);
+                }
+            };
+            auto read_w = [&](int st) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        w[st & 1][nb][h] = *reinterpret_cast<const v4f *>(wb + (((g * 5 + st) * NB + nb) * 2 + h) * 1024);
+            };
+            read_w(0);
+            read_x(0, xp + kh * 32, R + 2);
+            float mx = 0.f;
+#pragma unroll
+            for (int c = 0; c < 15; ++c) {
+                const int st = c / 3, t = c % 3;
+                if (t == 0) {
+                    if (st < 4) read_w(st + 1);
+                    if (st == 2) read_x(1, xp + 64 + kh * (PW * 32), R);
+                    if (st == 3) read_x(0, xp + 64 + 2 * (PW * 32), R);
+                }
+#pragma unroll
+                for (int y = 0; y < R; ++y)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const v4f wv = w[st & 1][nb][t == 2], xv = x[st == 3][st < 3 ? y + st : y][t == 1];
+                        v4f &d = t > 0 ? acx[y][nb] : acc[y][nb];
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, wv), __builtin_bit_cast(v8h, xv),
+                                                                   d, 0, 0, 0);
+                    }
+                // between the MFMAs: the next group into the other buffer, the
+                // loads that refill its registers, and the largest value of the
+                // group after it
+                if (c < NPF) convert(pf[ps][c], sc, sd + c * (NTH / 4 * 32));
+                if (c >= NPF && c < 2 * NPF) pf[ps][c - NPF] = load(sl, (g + 1) % G, c - NPF);
+                if (c == 2 * NPF) {
+#pragma unroll
+                    for (int k = 0; k < NPF; ++k)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pf[(g + 2) % 3][k][r]));
+                }
+                if (c == 14) {
+                    mx = wave_max(mx);
+                    if (lane == 0) sM[8 * buf + wave] = mx;
+                }
+#pragma unroll
+                for (int i = 0; i < R * NB; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // an MFMA,
+                    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);     // two VALU operations
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            buf ^= 1;
+        }
+        const int me = (int)(tmax >> 23) - 127;
+        if (slow_layer | (me >= 75) | ((me < -65) & (tmax != 0))) {
+            slow_tile<C, TR, NH>(a, n, reinterpret_cast<const float *>(static_cast<const char *>(a.wpk) + L::WBYTES), sB, sH);
+        } else {
+            const int osh = a.out_shift, om = (1 << osh) - 1;
+            const int ohd = (H + om) >> osh, owd = (W + om) >> osh;
+            __amdgpu_buffer_rsrc_t orow[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                orow[nb] = buf_rsrc(HEAD ? nullptr : static_cast<char *>(a.out) + n.act * a.pstride + nb * a.gstride,
+                                    HEAD ? 0u : 0x7FFFFFFFu);
+            const float ts = __int_as_float((127 - sexp) << 23);
+            v4f bias[NB], scl[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                bias[nb] = *reinterpret_cast<const v4f *>(sB + nb * 16 + kq * 4);
+                scl[nb] = *reinterpret_cast<const v4f *>(sS + nb * 16 + kq * 4) * ts;
+            }
+#pragma unroll
+            for (int y = 0; y < R; ++y) {
+                const int yo = Y0 + dd * (row0 + y);
+                const bool ok = (yo < H) & (xo < W);
+                const int opt = ((((yo & om) << osh) + (xo & om)) * ohd + (yo >> osh)) * owd + (xo >> osh);
+                float hh[NH > 0 ? NH : 1];                        // head partial sums of this lane's channels
+#pragma unroll
+                for (int q = 0; q < (NH > 0 ? NH : 1); ++q) hh[q] = 0.f;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int oc = nb * 16 + kq * 4;
+                    v4f v = acc[y][nb];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        v[r] = fmaf(fmaf(acx[y][nb][r], 0x1p-11f, v[r]), scl[nb][r], bias[nb][r]);
+                        if constexpr (RES) v[r] += rr[y][nb][r];
+                    }
+                    v = relu4(v);
+                    if constexpr (!HEAD) {
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), orow[nb],
+                                                               ok ? opt * (int)a.pstride + kq * 16 : BUF_OOB, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc + r] * v[r];
+                    }
+                }
+                if constexpr (HEAD) {
+                    // the four lane groups hold disjoint channel subsets of the pixel
+#pragma unroll
+                    for (int q = 0; q < NH; ++q) {
+                        hh[q] += __shfl_xor(hh[q], 16);
+                        hh[q] += __shfl_xor(hh[q], 32);
+                    }
+                    if (ok) {
+                        const int64_t plane = (int64_t)H * W;
+                        float *mp = a.maps + NH * n.px + (int64_t)yo * W + xo;
+                        // lane group kq writes planes kq, kq + 4, kq + 8
+#pragma unroll
+                        for (int q = 0; q < NH; ++q)
+                            if ((q & 3) == kq) mp[q * plane] = hh[q] + sH[NH * C + q];
+                    }
+                }
+            }
+        }
+        n = n1;
+        n1 = n2;
+        s1 = s2;
+        sexp = nexp;
+        tmax = nmax;
+    }
+}
+
 // ------------------------------------------------------------- launchers
+template <int C, int TR> constexpr int split_threads() { return C == 48 ? TR * 64 : NTH; }
+
+template <int C, int TR, bool RES, int NH>
+auto kernel_of()
+{
+    if constexpr (C == 48) return k_pipe<C, TR, RES, NH>;
+    else return k_split<C, TR, RES, NH>;
+}
+
 template <int C, int TR, bool RES, int NH>
 hipError_t launch_k(const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
 {
-    using L = SLds<C, TR, (NH > 5 ? NH : 5)>;
+    using L = std::conditional_t<C == 48, PLds<C, TR, (NH > 5 ? NH : 5)>, SLds<C, TR, (NH > 5 ? NH : 5)>>;
     static_assert(L::FITS, "LDS of the split kernel");
-    auto kern = k_split<C, TR, RES, NH>;
+    auto kern = kernel_of<C, TR, RES, NH>();
     static bool attr = false;
     if (!attr) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -462,7 +832,7 @@ hipError_t launch_k(const ConvArgs &a, const Geometry &g, int grid, hipStream_t 
         if (e != hipSuccess) return e;
         attr = true;
     }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NTH), L::TOTAL, s, a, g);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(split_threads<C, TR>()), L::TOTAL, s, a, g);
     return hipGetLastError();
 }
 
@@ -478,10 +848,10 @@ template <int C, int TR>
 int blocks_per_cu()
 {
     int nb = 0;
-    auto kern = k_split<C, TR, true, 0>;
-    constexpr size_t sh = SLds<C, TR, 5>::TOTAL;
+    auto kern = kernel_of<C, TR, true, 0>();
+    constexpr size_t sh = std::conditional_t<C == 48, PLds<C, TR, 5>, SLds<C, TR, 5>>::TOTAL;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, NTH, sh) != hipSuccess) nb = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, split_threads<C, TR>(), sh) != hipSuccess) nb = 1;
     return nb > 0 ? nb : 1;
 }
 
@@ -515,13 +885,15 @@ bool split_takes(int C, int precision) { return C <= 48 && precision == DL_FP32;
 // the fragments, then the layer's FP32 weights as they are
 size_t split_packed_bytes(int C)
 {
-    const size_t w = C == 16 ? SPlan<16>::WBYTES : C == 32 ? SPlan<32>::WBYTES : SPlan<48>::WBYTES;
+    const size_t w = C == 16 ? SPlan<16>::WBYTES : C == 32 ? SPlan<32>::WBYTES : PLds<48, 8, 5>::WBYTES;
     return w + (size_t)9 * C * C * 4;
 }
 
 void split_pack_weights(int C, const float *W, void *dst, float *scale)
 {
-    const int CH8 = C / 8, NB = C / 16, FULL = 3 * CH8 / 4, NSTEP = 3 * FULL + (3 * CH8 % 4 ? 2 : 0);
+    // k_pipe takes K by groups of 16 channels, each with closing steps of its own
+    const int NG = C == 48 ? 3 : 1, CG = C / NG, CH8 = CG / 8, NB = C / 16;
+    const int FULL = 3 * CH8 / 4, NS = 3 * FULL + (3 * CH8 % 4 ? 2 : 0), NSTEP = NG * NS;
     uint16_t *o = static_cast<uint16_t *>(dst);
     std::vector<float> up(C, 1.f);
     bool fit = true;
@@ -536,16 +908,17 @@ void split_pack_weights(int C, const float *W, void *dst, float *scale)
     if (!fit) std::fill(scale, scale + C, 0.f);    // every tile in plain FP32
     for (int st = 0; st < NSTEP; ++st)
         for (int kq = 0; kq < 4; ++kq) {
-            // tap row and chunk (of that row's 3 C / 8) of these lanes' 8 values; u = 3: zero weights
+            // tap row and chunk (of that row's 3 CG / 8) of these lanes' 8 values; u = 3: zero weights
+            const int g = st / NS, sg = st - g * NS;
             int u, i;
-            if (st < 3 * FULL) {
-                u = st % 3;
-                i = 4 * (st / 3) + kq;
+            if (sg < 3 * FULL) {
+                u = sg % 3;
+                i = 4 * (sg / 3) + kq;
             } else {
-                u = st == 3 * FULL ? kq >> 1 : kq < 2 ? 2 : 3;
+                u = sg == 3 * FULL ? kq >> 1 : kq < 2 ? 2 : 3;
                 i = 4 * FULL + (kq & 1);
             }
-            const int v = i / CH8, c0 = (i % CH8) * 8;
+            const int v = i / CH8, c0 = g * CG + (i % CH8) * 8;
             for (int oc = 0; oc < C; ++oc) {
                 uint16_t *f = o + ((size_t)((st * NB + oc / 16) * 2) * 64 + kq * 16 + oc % 16) * 8;
                 const float *w = W + ((size_t)oc * C + c0) * 9 + 3 * (u < 3 ? u : 0) + v;

@@ -97,3 +97,14 @@ def test_weight_magnitudes(scale):
     wts, net = _layer(32, 1, scale)
     y, m = _sums(x, wts["blk0.w1"], 1)
     _check(_run(net, x), np.maximum(y, 0), 32, m, wts["blk0.w1"])
+
+
+@pytest.mark.parametrize("exps", [(-40, 0, 12), (12, -40, 0), (0, 16, 36), (-70, -70, -70), (-30, -70, 10)])
+def test_channel_groups_of_different_magnitude(exps):
+    """48 channels go group by group of 16: a later group that needs another
+    power of two rescales the sums so far."""
+    x = np.random.default_rng(9).standard_normal((1, 19, 75, 48))
+    x = (x * np.repeat([2.0 ** e for e in exps], 16)).astype(np.float32)
+    wts, net = _layer(48, 1)
+    y, m = _sums(x, wts["blk0.w1"], 1)
+    _check(_run(net, x), np.maximum(y, 0), 48, m, wts["blk0.w1"], float(np.abs(x).max()))
