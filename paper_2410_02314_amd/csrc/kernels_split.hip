@@ -632,24 +632,14 @@ k_pipe(ConvArgs a, Geometry geo)
         for (int g = 0; g < G; ++g) {
             __syncthreads();   // group g staged, the other buffer free, the next group's maxima written
             // the next group's exponent: this tile's (lowered where the group
-            // needs it, the sums so far rescaled), or the next tile's own
+            // needs it: the sums are rescaled once this group is in them), or
+            // the next tile's own
             const uint32_t gm = group_max(buf ^ 1);
             const int e = fit_exp(gm);
             int se = e;
             if (g + 1 < G) {
                 tmax = max(tmax, gm);
                 se = min(sexp, e);
-                if (se < sexp) {
-                    const float f = __int_as_float((127 + se - sexp) << 23);
-#pragma unroll
-                    for (int y = 0; y < R; ++y)
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) {
-                            acc[y][nb] *= f;
-                            acx[y][nb] *= f;
-                        }
-                }
-                sexp = se;
             } else {
                 nexp = e;
                 nmax = gm;
@@ -734,6 +724,17 @@ k_pipe(ConvArgs a, Geometry geo)
                     __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);     // two VALU operations
                 }
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if (g + 1 < G && se < sexp) {
+                const float f = __int_as_float((127 + se - sexp) << 23);
+#pragma unroll
+                for (int y = 0; y < R; ++y)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        acc[y][nb] *= f;
+                        acx[y][nb] *= f;
+                    }
+                sexp = se;
             }
             buf ^= 1;
         }
