@@ -141,8 +141,8 @@ struct dl_net {
 
     // dense-connection networks (DLD1 blobs): layers per block and growth
     // (0 for the residual network), the packed weights and biases of every
-    // conv in run order ([block][layer 0 .. L-1, transition]) at float
-    // offsets dense_w / dense_b of d_dense, then the head's (rows padded to 16)
+    // conv in run order ([block][layer 0 .. L-1, transition], the U-Net's) in
+    // d_dense, then the head's (rows padded to 16)
     int dL = 0, dG = 0;
     int unet = 0;                   // U-Net levels after the dense blocks: 0 or 2
 
@@ -159,7 +159,11 @@ struct dl_net {
     int t_step = 0;
     bool t_dirty = false;
     float *d_dense = nullptr;
-    std::vector<size_t> dense_w, dense_b;
+    // per conv in run order, float offsets in d_dense: fragments, bias, scales,
+    // the weights as they are, and (transitions) the FP32 pack of the last
+    // layer's outputs
+    struct DenseConv { size_t w, b, s, raw, own; };
+    std::vector<DenseConv> dense;
     size_t dense_head_w = 0;
 };
 
@@ -559,31 +563,44 @@ int pack_dense(dl_net *net)
 {
     const int C = net->C, L = net->dL, G = net->dG, CT = C + L * G;
     std::vector<float> host;
-    net->dense_w.clear();
-    net->dense_b.clear();
+    net->dense.clear();
     const float *p = net->params.data() + (size_t)C * 9 + C;
-    auto put = [&](int cout, int cin, int taps) {
+    auto room = [&](size_t n) {
+        const size_t o = (host.size() + 63) / 64 * 64;
+        host.resize(o + n);
+        return o;
+    };
+    // own: outputs of the block's last layer among a transition's inputs
+    auto put = [&](int cout, int cin, int taps, int own) {
         const size_t nw = (size_t)cout * cin * taps;
-        const size_t ow = (host.size() + 63) / 64 * 64;
-        host.resize(ow + nw);
-        pack_dense_weights(cout, cin, taps, p, host.data() + ow);
+        dl_net::DenseConv c{};
+        c.w = room(dpipe_weight_bytes(cout, cin - own, taps) / 4);
+        c.s = room(cout);
+        dpipe_pack(cout, cin - own, cin, taps, p, host.data() + c.w, host.data() + c.s);
+        c.raw = room(nw);
+        std::memcpy(host.data() + c.raw, p, sizeof(float) * nw);
+        if (own) {
+            std::vector<float> wo((size_t)cout * own);
+            for (int oc = 0; oc < cout; ++oc)
+                std::memcpy(&wo[(size_t)oc * own], p + (size_t)oc * cin + cin - own, sizeof(float) * own);
+            c.own = room(wo.size());
+            pack_dense_weights(cout, own, 1, wo.data(), host.data() + c.own);
+        }
         p += nw;
-        const size_t ob = (host.size() + 63) / 64 * 64;
-        host.resize(ob + cout);
-        std::memcpy(host.data() + ob, p, sizeof(float) * cout);
+        c.b = room(cout);
+        std::memcpy(host.data() + c.b, p, sizeof(float) * cout);
         p += cout;
-        net->dense_w.push_back(ow);
-        net->dense_b.push_back(ob);
+        net->dense.push_back(c);
     };
     for (int b = 0; b < net->nb; ++b) {
-        for (int i = 0; i < L; ++i) put(G, C + i * G, 9);
-        put(C, CT, 1);
+        for (int i = 0; i < L; ++i) put(G, C + i * G, 9, 0);
+        put(C, CT, 1, G);
     }
     if (net->unet) {                    // d1, d2 (C -> C), u1, u0 (2C -> C)
-        put(C, C, 9);
-        put(C, C, 9);
-        put(C, 2 * C, 9);
-        put(C, 2 * C, 9);
+        put(C, C, 9, 0);
+        put(C, C, 9, 0);
+        put(C, 2 * C, 9, 0);
+        put(C, 2 * C, 9, 0);
     }
     // the head (fused into the last block's last layer) as a 16-row 1x1 conv
     std::vector<float> head16((size_t)16 * C, 0.f);
@@ -688,11 +705,31 @@ int run_gate(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &
     return DL_OK;
 }
 
+// conv k (run order) of the packed dense network
+void dense_weights(const dl_net *net, size_t k, DensePipeArgs &a)
+{
+    const dl_net::DenseConv &c = net->dense[k];
+    a.w = net->d_dense + c.w;
+    a.bias = net->d_dense + c.b;
+    a.scale = net->d_dense + c.s;
+    a.raw = net->d_dense + c.raw;
+}
+
+// the fused head
+void dense_head(const dl_net *net, float *maps, DensePipeArgs &a)
+{
+    a.wh = net->d_dense + net->dense_head_w;
+    a.hraw = net->d_head;
+    a.bh = net->d_head + (size_t)net->nh * net->C;
+    a.nh = net->nh;
+    a.maps = maps;
+}
+
 // The two-stage U-Net on the extractor's output a0 (channels 0 .. C-1 of B0,
-// points of 2C floats at level 0).  Level buffers: B1 [d1 | x] (2C floats per
-// level-1 point; x is pool(a0), later up(d2)), B2 [d2 | pool(d1)] (2C per
-// level-2 point), U1 (C per level-1 point); B0's channels C .. 2C-1 take
-// up(u1), and the last convolution reads [a0, up(u1)] with the head fused.
+// 2C channels at level 0).  Level buffers: B1 [d1 | x] (2C channels at level
+// 1; x is pool(a0), later up(d2)), B2 [d2 | pool(d1)] (2C at level 2), U1 (C at
+// level 1); B0's channels C .. 2C-1 take up(u1), and the last convolution reads
+// [a0, up(u1)] with the head fused.  All in planes of 16 channels.
 int run_unet(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p, float *B0, float *maps,
              hipStream_t s)
 {
@@ -701,98 +738,101 @@ int run_unet(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &
     float *B1 = reinterpret_cast<float *>(p.ws + p.unet);
     float *B2 = B1 + (size_t)C2 * g.lv_pts[1];
     float *U1 = B2 + (size_t)C2 * g.lv_pts[2];
+    const int64_t s0 = g.total_act * 16, s1 = g.lv_pts[1] * 16, s2 = g.lv_pts[2] * 16;   // plane strides
+    const int64_t h = C / 16;                            // planes of C channels
     Geometry g1 = g, g2 = g;
     g1.tiles[0] = g.lv_tiles[1];
     g2.tiles[0] = g.lv_tiles[2];
     const size_t k0 = (size_t)net->nb * (net->dL + 1);   // the U-Net's convs in run order
-    auto conv = [&](const FrameDesc *fd, const Geometry &gg, int blk, const float *in, int cin, float *out, int cso,
+    auto conv = [&](const FrameDesc *fd, const Geometry &gg, int blk, const float *in, int64_t gs, int cin, float *out,
                     size_t k, int fuse) {
-        DenseConvArgs a{};
+        DensePipeArgs a{};
         a.in = in;
-        a.csi = C2;
-        a.cin = cin;
+        a.igs = a.ogs = gs;
+        a.ngroups = cin / 16;
         a.out = out;
-        a.cso = cso;
-        a.co = 0;
-        a.w = net->d_dense + net->dense_w[k];
-        a.bias = net->d_dense + net->dense_b[k];
+        dense_weights(net, k, a);
         a.fd = fd;
         a.d = 1;
         a.blk = blk;
-        if (fuse) {
-            a.wh = net->d_dense + net->dense_head_w;
-            a.bh = net->d_head + (size_t)net->nh * C;
-            a.nh = net->nh;
-            a.maps = maps;
-        }
-        return launch_dconv(C / 16, fuse, 1, a, gg, net->ncu, s);
+        if (fuse) dense_head(net, maps, a);
+        return launch_dpipe(C / 16, fuse, 1, a, gg, net->ncu, s);
     };
     {
         StageTimer t(net, DL_STAGE_UNET, s);
-        HIPCHK(net, launch_pool2(fd0, fd1, n, g.lv_pts[1], B0, C2, B1 + C, C2, C, s));
-        HIPCHK(net, conv(fd1, g1, 0, B1 + C, C, B1, C2, k0, 0));                  // d1
-        HIPCHK(net, launch_pool2(fd1, fd2, n, g.lv_pts[2], B1, C2, B2 + C, C2, C, s));
-        HIPCHK(net, conv(fd2, g2, 0, B2 + C, C, B2, C2, k0 + 1, 0));              // d2
-        HIPCHK(net, launch_up2(fd2, fd1, n, g.lv_pts[1], B2, C2, B1 + C, C2, C, s));
-        HIPCHK(net, conv(fd1, g1, 0, B1, C2, U1, C, k0 + 2, 0));                  // u1
-        HIPCHK(net, launch_up2(fd1, fd0, n, g.lv_pts[0], U1, C, B0 + C, C2, C, s));
+        HIPCHK(net, launch_pool2(fd0, fd1, n, g.lv_pts[1], B0, 16, s0, B1 + h * s1, 16, s1, C, s));
+        HIPCHK(net, conv(fd1, g1, 0, B1 + h * s1, s1, C, B1, k0, 0));                   // d1
+        HIPCHK(net, launch_pool2(fd1, fd2, n, g.lv_pts[2], B1, 16, s1, B2 + h * s2, 16, s2, C, s));
+        HIPCHK(net, conv(fd2, g2, 0, B2 + h * s2, s2, C, B2, k0 + 1, 0));               // d2
+        HIPCHK(net, launch_up2(fd2, fd1, n, g.lv_pts[1], B2, 16, s2, B1 + h * s1, 16, s1, C, s));
+        HIPCHK(net, conv(fd1, g1, 0, B1, s1, C2, U1, k0 + 2, 0));                       // u1
+        HIPCHK(net, launch_up2(fd1, fd0, n, g.lv_pts[0], U1, 16, s1, B0 + h * s0, 16, s0, C, s));
     }
     StageTimer t(net, DL_STAGE_CONV_HEAD, s);
-    HIPCHK(net, conv(fd0, g, net->nb, B0, C2, nullptr, 0, k0 + 3, 3));             // u0 + head
+    HIPCHK(net, conv(fd0, g, net->nb, B0, s0, C2, nullptr, k0 + 3, 3));                  // u0 + head
     return DL_OK;
 }
 
-// Dense networks: stem into channels 0 .. C-1 of buffer A; per block, each
-// layer appends its G channels to A, and the last one, fused with the block's
+// phase layout (log2) of a dense block's planes: its dilation's when that is a
+// power of two, so a tile's lattice rows are contiguous (in plain rows every
+// point of a dilated tile is half a 128-byte line whose other half belongs to
+// another phase's tile: 1590 us against 1008 per unfused layer, 4 x 2048^2)
+int dense_shift(const dl_net *net, int b)
+{
+    const int d = net->dil[b];
+    return (d & (d - 1)) == 0 ? __builtin_ctz((unsigned)d) : 0;
+}
+
+// Dense networks, in planes of 16 channels: stem into channels 0 .. C-1 of
+// buffer A; per block, each layer appends its G channels to A, and the last one, fused with the block's
 // transition, writes the next block's input into B (channels 0 .. C-1), after
 // which A and B swap; in the last block the head is fused after the
 // transition and writes the maps.
 int run_dense(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p, float *maps, hipStream_t s)
 {
-    const int C = net->C, L = net->dL, G = net->dG, CT = C + L * G;
+    const int C = net->C, L = net->dL, G = net->dG;
+    const int64_t gs = g.total_act * 16;                // planes of 16 channels
     float *A = reinterpret_cast<float *>(p.ws + p.act0), *B = reinterpret_cast<float *>(p.ws + p.act2);
     uint32_t *queue = net->cfg.tile_queue ? reinterpret_cast<uint32_t *>(p.ws + p.queue) : nullptr;
     if (queue) HIPCHK(net, launch_zero_u32(queue, (int64_t)net->nb * L * 8, s));
     {
         StageTimer t(net, DL_STAGE_STEM, s);
-        HIPCHK(net, launch_dstem(C, d_fd, g, net->d_stem, net->d_stem + C * 9, net->cfg.offset,
-                                 net->cfg.gain * in_scale_of(net), A, CT, s));
+        HIPCHK(net, launch_stem(C, d_fd, g, net->d_stem, net->d_stem + C * 9, net->cfg.offset,
+                                net->cfg.gain * in_scale_of(net), nullptr, A, DL_FP32, true, dense_shift(net, 0), nullptr,
+                                0, s));
     }
     for (int b = 0; b < net->nb; ++b) {
         const size_t k0 = (size_t)b * (L + 1);          // this block's first conv in run order
         for (int i = 0; i < L; ++i) {
             const bool last = i == L - 1;
             const int fuse = !last ? 0 : b == net->nb - 1 && !net->unet ? 2 : 1;
-            DenseConvArgs a{};
+            DensePipeArgs a{};
             a.in = A;
-            a.csi = CT;
-            a.cin = C + i * G;
-            a.out = A;
-            a.cso = CT;
-            a.co = C + i * G;
-            a.w = net->d_dense + net->dense_w[k0 + i];
-            a.bias = net->d_dense + net->dense_b[k0 + i];
+            a.igs = a.ogs = a.tgs = gs;
+            a.ngroups = (C + i * G) / 16;
+            a.out = A + a.ngroups * gs;
+            dense_weights(net, k0 + i, a);
             a.fd = d_fd;
             a.d = net->dil[b];
             a.blk = b;
+            a.in_shift = dense_shift(net, b);
+            a.out_shift = b + 1 < net->nb ? dense_shift(net, b + 1) : 0;
             if (queue) {
                 a.queue = queue + ((size_t)b * L + i) * 8;
                 a.queue_mode = net->cfg.tile_queue;
             }
             if (fuse) {
-                a.wt = net->d_dense + net->dense_w[k0 + L];
-                a.bt = net->d_dense + net->dense_b[k0 + L];
+                const dl_net::DenseConv &c = net->dense[k0 + L];
+                a.wt = net->d_dense + c.w;
+                a.bt = net->d_dense + c.b;
+                a.st = net->d_dense + c.s;
+                a.traw = net->d_dense + c.raw;
+                a.wtl = net->d_dense + c.own;
                 a.tout = B;
-                a.cst = b == net->nb - 1 ? 2 * C : CT;   // the U-Net's [a0, up(u1)] at level 0
             }
-            if (fuse == 2) {
-                a.wh = net->d_dense + net->dense_head_w;
-                a.bh = net->d_head + (size_t)net->nh * C;
-                a.nh = net->nh;
-                a.maps = maps;
-            }
+            if (fuse == 2) dense_head(net, maps, a);
             StageTimer t(net, fuse == 0 ? DL_STAGE_CONV : fuse == 1 ? DL_STAGE_CONV_1X1 : DL_STAGE_CONV_HEAD, s);
-            HIPCHK(net, launch_dconv(G / 16, fuse, C / 16, a, g, net->ncu, s));
+            HIPCHK(net, launch_dpipe(G / 16, fuse, C / 16, a, g, net->ncu, s));
         }
         std::swap(A, B);
     }
@@ -816,7 +856,7 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
     {
         StageTimer t(net, DL_STAGE_STEM, s);
         HIPCHK(net, launch_stem(C, d_fd, g, net->d_stem, net->d_stem + C * 9, net->cfg.offset, scale, net->d_cam,
-                                a0, net->cfg.precision, conv_planar(C, net->cfg.precision), keep, stem_r, s));
+                                a0, net->cfg.precision, conv_planar(C, net->cfg.precision), 0, keep, stem_r, s));
     }
     void *x = a0, *xn = p.ws + p.act2;      // block input, block output (alternating)
     for (int b = 0; b < net->nb; ++b) {
@@ -1462,13 +1502,13 @@ int train_run_dense(dl_net *net, const uint16_t *d_frames, int n, int h, int w, 
     };
     if (net->unet) {
         const int nbc = C / 16, nbc2 = C2 / 16;
-        HIPCHK(net, launch_pool2(d_fd, fd1, n, P1, F(c0), C2, F(p1), C, C, s));
+        HIPCHK(net, launch_pool2(d_fd, fd1, n, P1, F(c0), C2, 16, F(p1), C, 16, C, s));
         HIPCHK(net, uconv(fd1, g1, 0, F(p1), C, C, F(c1), C2, nbc, pk(pl.ufw[0]), prm + o.ub[0], 1));     // d1
-        HIPCHK(net, launch_pool2(fd1, fd2, n, P2, F(c1), C2, F(p2), C, C, s));
+        HIPCHK(net, launch_pool2(fd1, fd2, n, P2, F(c1), C2, 16, F(p2), C, 16, C, s));
         HIPCHK(net, uconv(fd2, g2, 0, F(p2), C, C, F(d2), C, nbc, pk(pl.ufw[1]), prm + o.ub[1], 1));       // d2
-        HIPCHK(net, launch_up2(fd2, fd1, n, P1, F(d2), C, F(c1) + C, C2, C, s));
+        HIPCHK(net, launch_up2(fd2, fd1, n, P1, F(d2), C, 16, F(c1) + C, C2, 16, C, s));
         HIPCHK(net, uconv(fd1, g1, 0, F(c1), C2, C2, F(u1), C, nbc, pk(pl.ufw[2]), prm + o.ub[2], 1));     // u1
-        HIPCHK(net, launch_up2(fd1, d_fd, n, P, F(u1), C, F(c0) + C, C2, C, s));
+        HIPCHK(net, launch_up2(fd1, d_fd, n, P, F(u1), C, 16, F(c0) + C, C2, 16, C, s));
         HIPCHK(net, uconv(d_fd, g, nb, F(c0), C2, C2, F(u0), C, nbc, pk(pl.ufw[3]), prm + o.ub[3], 1));    // u0
         (void)nbc2;
     }

@@ -123,7 +123,7 @@ struct TileWalk {
     uint32_t rxn, strip;
     UDiv a, b, c, last, dd;             // phase-major: regions, strip tiles, strip and last strip width; minor: d^2, rxn
 
-    __device__ __forceinline__ void frame(const ConvArgs &ca, const Geometry &geo, int nfr, int tr, int tc, int64_t t)
+    template <class Args> __device__ __forceinline__ void frame(const Args &ca, const Geometry &geo, int nfr, int tr, int tc, int64_t t)
     {
         const int blk = ca.blk, d = ca.d;
         const int f = find_frame(ca.fd, nfr, t, [blk](const FrameDesc &x) { return ld_const(&x.tile_start[blk]); });
@@ -151,7 +151,7 @@ struct TileWalk {
             last.set(rxn - (rxn - 1) / strip * strip);
         }
     }
-    __device__ __forceinline__ TileDec tile(const ConvArgs &ca, const Geometry &geo, int nfr, int tr, int tc, int64_t ti)
+    template <class Args> __device__ __forceinline__ TileDec tile(const Args &ca, const Geometry &geo, int nfr, int tr, int tc, int64_t ti)
     {
         const int64_t t = ca.list ? (int64_t)ld_const(ca.list + ti) : ti;
         if (t < ts0 || t >= ts1) frame(ca, geo, nfr, tr, tc, t);

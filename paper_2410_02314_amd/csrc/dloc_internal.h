@@ -59,6 +59,19 @@ __host__ __device__ inline int64_t act_points(int h, int w, int l)
     return (int64_t)l * l * hd * wd;
 }
 
+// The dense networks' phase layout of d = 2^s: as above without the padding --
+// sub-image (py, px) has the ceil((h - py) / d) rows and ceil((w - px) / d)
+// columns its pixels need, so any layout of a frame holds h w points.  Point of
+// pixel (y, x); s = 0: plain rows.
+__host__ __device__ inline int64_t phase_point(int h, int w, int s, int y, int x)
+{
+    const int m = (1 << s) - 1, py = y & m, px = x & m;
+    const int rows = (h - py + m) >> s, cols = (w - px + m) >> s;
+    const int before_r = (h >> s) * py + ((h & m) < py ? h & m : py);      // rows of the phases above py
+    const int before_c = (w >> s) * px + ((w & m) < px ? w & m : px);
+    return (int64_t)before_r * w + (int64_t)rows * before_c + (int64_t)(y >> s) * cols + (x >> s);
+}
+
 struct Geometry {
     int nf = 0;
     int64_t total_px = 0, total_act = 0, total_rows = 0, total_words = 0, gate_tiles = 0;
@@ -217,10 +230,10 @@ hipError_t launch_enumerate(const void *in, const EnumArgs &e, FrameDesc *fd, in
 // cam: per-pixel {offset, gain * in_scale} of the sensor (every frame of
 // the batch is sensor-sized), or null for the scalar offset and scale
 // planar: FP32 output in planes of 16 channels (64 bytes per point, g.total_act
-// points per plane) instead of C channels per point
+// points per plane, in the phase layout of 2^shift) instead of C channels per point
 hipError_t launch_stem(int C, const FrameDesc *fd, const Geometry &g, const float *w, const float *b,
                        float offset, float scale, const float2 *cam, void *act, int precision, bool planar,
-                       const uint8_t *keep, int radius, hipStream_t s);
+                       int shift, const uint8_t *keep, int radius, hipStream_t s);
 hipError_t launch_zero_u32(uint32_t *p, int64_t n, hipStream_t s);
 // gated runs: keep[t] = logit[t] > tau_gate; then one compacted list of conv
 // tiles per layer (tiles within radius[l] of a kept gate tile)
@@ -264,24 +277,23 @@ size_t conv_packed_bytes(int C, int precision);
 // pack one 3x3 C->C layer W [C][C][3][3]; FP8 and FP32 (to 48 channels) also write scale[C]
 void pack_conv_weights(int C, int precision, const float *W, void *dst, float *scale);
 
-// ---- dense-connection networks (kernels_dense.hip) ----
+// ---- dense-connection networks: training (kernels_dense.hip) ----
 // A block's concatenation lives in one plain NHWC buffer of cs floats per
 // point (block input in channels 0 .. C-1, then each layer's growth channels);
 // a layer reads channels 0 .. cin-1 of `in` and writes its 16 NB outputs (+
 // bias, ReLU) from channel co of `out`.  A block's last layer runs fused with
 // its 1x1 transition (CT = cin + 16 NB -> 16 NT, + bias, ReLU), which writes
-// channels 0 .. 16 NT - 1 of `tout` (its own outputs are not stored), and in
-// the last block with the 1x1 head after it (16 NT -> nh planar maps).
-// Tiles: dense_tile_rows() x dense_tile_cols() points of the layer's d-strided
-// lattice (conv_tiles / decode_tile numbering, phase-major, strip 8) in the
-// tile numbering of slot `blk`.
+// channels 0 .. 16 NT - 1 of `tout`.  Tiles: dense_tile_rows() x
+// dense_tile_cols() points of the layer's d-strided lattice (conv_tiles /
+// decode_tile numbering, phase-major, strip 8) in the tile numbering of slot
+// `blk`.
 struct DenseConvArgs {
     const float *in;
     int csi, cin;            // floats per input point, input channels read (multiple of 16)
     float *out;
     int cso, co;             // floats per output point, first output channel
     const float *w;          // packed layer weights (pack_dense_weights, taps 9)
-    const float *bias;       // [16 NB]
+    const float *bias;       // [16 NB], or null
     const FrameDesc *fd;
     int d, blk;
     // fused transition: packed weights (pack_dense_weights, taps 1, cin + 16 NB
@@ -289,28 +301,56 @@ struct DenseConvArgs {
     const float *wt, *bt;
     float *tout;
     int cst;
-    // fused head: packed weights (16 rows, rows >= nh zero; K = 16 NT), bias [nh]
-    const float *wh, *bh;
-    int nh;
-    float *maps;             // planar [nh][h][w] per frame from px_off
-    // tile schedule: null = static ranges per XCD; else 8 zeroed counters, and
-    // queue_mode 1 (one atomic queue per XCD over its range) or 2 (counter 0:
-    // one queue over all tiles)
-    uint32_t *queue;
-    int queue_mode;
-    // training passes (launch_dconv_train): bias may be null; res (points of
-    // rcs floats) is added before the optional ReLU; where mask (points of mcs
-    // floats) is <= 0 the output is 0
+    // res (points of rcs floats) is added before the optional ReLU; where mask
+    // (points of mcs floats) is <= 0 the output is 0
     const float *res, *mask;
     int rcs, mcs, relu;
 };
 int dense_tile_rows();
 int dense_tile_cols();
-// nb_out 1 or 2 (16 or 32 layer outputs); fuse 0 (layer), 1 (+ transition),
-// 2 (+ transition + head), 3 (+ head on the layer's outputs); nt = transition
-// outputs / 16 (1 or 2)
-hipError_t launch_dconv(int nb_out, int fuse, int nt, const DenseConvArgs &a, const Geometry &g, int ncu,
+
+// The same layers in inference (kernels_dsplit.hip): activations in planes of
+// 16 channels, 16 floats per point, *gs floats from a plane to the next; the
+// layer reads planes 0 .. ngroups - 1 of `in` and writes its 16 NB outputs to
+// planes 0 .. NB - 1 of `out` (the transition's to those of `tout`).
+struct DensePipeArgs {
+    const float *in;
+    int64_t igs;
+    int ngroups;             // input channels / 16
+    float *out;
+    int64_t ogs;
+    const void *w;           // dpipe_pack of the layer (9 taps) ...
+    const float *bias, *scale, *raw;     // ... its bias and scales [16 NB], its weights as they are
+    const FrameDesc *fd;
+    int d, blk;
+    // fused transition: dpipe_pack (1 tap) of its first 16 ngroups inputs, bias
+    // and scales [16 NT], its weights as they are, and pack_dense_weights of its
+    // last 16 NB inputs
+    const void *wt;
+    const float *bt, *st, *traw, *wtl;
+    float *tout;
+    int64_t tgs;
+    // fused head: pack_dense_weights (16 rows, rows >= nh zero), bias [nh], its weights as they are
+    const float *wh, *bh, *hraw;
+    int nh;
+    float *maps;
+    // tile schedule: null = static ranges per XCD; else 8 zeroed counters, and
+    // queue_mode 1 (one atomic queue per XCD over its range) or 2 (counter 0:
+    // one queue over all tiles)
+    uint32_t *queue;
+    int queue_mode;
+    int in_shift, out_shift; // phase layouts (phase_point) of in and out, and of tout
+    int wres;                // (set by the launcher) all groups' weights in LDS
+    // (members the tile decoder expects: no tile list, plain layout)
+    static constexpr const int32_t *list = nullptr;
+    static constexpr int in_phase = 0;
+};
+hipError_t launch_dpipe(int nb_out, int fuse, int nt, const DensePipeArgs &a, const Geometry &g, int ncu,
                         hipStream_t s);
+// W [cout][ld][taps], its first cin inputs -> the fragments of k_dpipe; scale
+// [cout]: powers of two (all 0: outside the FP16 halves' range)
+size_t dpipe_weight_bytes(int cout, int cin, int taps);
+void dpipe_pack(int cout, int cin, int ld, int taps, const float *W, void *dst, float *scale);
 // ---- training (kernels_train.hip) ----
 // count square 3x3 convs' flat weights [C][C][9], the i-th at W0 + i src_stride,
 // into the conv kernel's layout, each as itself (dst + 2 i 9 C^2) and as the
@@ -372,24 +412,24 @@ hipError_t launch_1x1_back(int C, const float *g, const float *Wt, int ct, int64
 hipError_t launch_stem_grad(const float *ds, const uint16_t *frames, int n, int h, int w, float offset, float scale,
                             int C, float *gwb, float *part, float *mid, hipStream_t s);
 
-// one plain dense-kernel layer with the training epilogue (see DenseConvArgs),
+// one dense layer (see DenseConvArgs),
 // nb_out 1 .. 5 blocks of 16 outputs
 hipError_t launch_dconv_train(int nb_out, const DenseConvArgs &a, const Geometry &g, int ncu, hipStream_t s);
 // a dense block's last layer (16 outputs, written to out at co) fused with the
-// block's 1x1 transition (nt = its outputs / 16) as in inference, for the
-// training forward pass
+// block's 1x1 transition (nt = its outputs / 16)
 hipError_t launch_dconv_train_fused(int nt, const DenseConvArgs &a, const Geometry &g, int ncu, hipStream_t s);
-// preprocessing + stem 1 -> C (C 16 or 32) + ReLU into channels 0 .. C-1 of points of cs floats
+// preprocessing + stem 1 -> C (C 16 or 32) + ReLU into channels 0 .. C-1 of
+// points of cs floats, for training
 hipError_t launch_dstem(int C, const FrameDesc *fd, const Geometry &g, const float *w, const float *b, float offset,
                         float scale, float *act, int cs, hipStream_t s);
 // U-Net levels (src and dst descriptors of the same frames, npts = the dst
 // level's points): 2 x 2 max pooling to the next level, nearest upsampling
 // to the level above; C channels read from points of scs floats, written to
-// points of dcs floats
+// points of dcs floats; sgs, dgs: floats from 16 channels to the next 16
 hipError_t launch_pool2(const FrameDesc *sfd, const FrameDesc *dfd, int nf, int64_t npts, const float *src, int scs,
-                        float *dst, int dcs, int C, hipStream_t s);
+                        int64_t sgs, float *dst, int dcs, int64_t dgs, int C, hipStream_t s);
 hipError_t launch_up2(const FrameDesc *sfd, const FrameDesc *dfd, int nf, int64_t npts, const float *src, int scs,
-                      float *dst, int dcs, int C, hipStream_t s);
+                      int64_t sgs, float *dst, int dcs, int64_t dgs, int C, hipStream_t s);
 // W [cout][cin][taps] -> the MFMA layout of k_dconv (cout, cin multiples of 16)
 void pack_dense_weights(int cout, int cin, int taps, const float *W, float *dst);
 

@@ -25,13 +25,14 @@ namespace {
 // scale byte (region at scale_off).
 constexpr int SSEG = 1024;
 
-// scale_off: FP8 as above; PLANAR (FP32): floats per plane of 16 channels
+// scale_off: FP8 as above; PLANAR (FP32): floats per plane of 16 channels, whose
+// points lie in the phase layout of 2^shift (phase_point)
 template <int C, int P, bool PLANAR>
 __global__ void __launch_bounds__(256)
 k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *__restrict__ dyn,
        const float *__restrict__ w, const float *__restrict__ b, float offset, float scale,
        const float2 *__restrict__ cam, void *__restrict__ act, int64_t scale_off, const uint8_t *__restrict__ keep,
-       int radius)
+       int radius, int shift)
 {
     if (dyn) {                       // frame count and rows known on the device only
         nf = (int)dyn[DYN_NF];
@@ -98,7 +99,7 @@ k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *
                 for (int u = 0; u < 3; ++u)
 #pragma unroll
                     for (int v = 0; v < 3; ++v) xin[u * 3 + v] = sx[u][px + v];
-                const int64_t pt = fd.act_off + (int64_t)y * W + x;
+                const int64_t pt = fd.act_off + (PLANAR && shift ? phase_point(H, W, shift, y, x) : (int64_t)y * W + x);
                 const int64_t base = PLANAR ? (q >> 2) * scale_off + pt * 16 + (q & 3) * CQ : pt * C + q * CQ;
                 float o[CQ];
 #pragma unroll
@@ -140,23 +141,23 @@ k_stem(const FrameDesc *__restrict__ fdp, int nf, int64_t nrows, const int64_t *
 
 template <int C>
 hipError_t stem_c(const FrameDesc *fd, const Geometry &g, const float *w, const float *b, float offset,
-                  float scale, const float2 *cam, void *act, int precision, bool planar, const uint8_t *keep,
+                  float scale, const float2 *cam, void *act, int precision, bool planar, int shift, const uint8_t *keep,
                   int radius, hipStream_t s)
 {
     const unsigned grid = (unsigned)std::min<int64_t>(g.total_rows, 8192);
     const int64_t soff = g.total_act * C;        // FP8: byte offset of the group scales
     if (precision == DL_FP8)
         hipLaunchKernelGGL((k_stem<C, DL_FP8, false>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
-                           scale, cam, act, soff, keep, radius);
+                           scale, cam, act, soff, keep, radius, 0);
     else if (precision == DL_BF16)
         hipLaunchKernelGGL((k_stem<C, DL_BF16, false>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
-                           scale, cam, act, soff, keep, radius);
+                           scale, cam, act, soff, keep, radius, 0);
     else if (planar && C <= 48)
         hipLaunchKernelGGL((k_stem<C, DL_FP32, C <= 48>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
-                           scale, cam, act, g.total_act * 16, keep, radius);
+                           scale, cam, act, g.total_act * 16, keep, radius, shift);
     else
         hipLaunchKernelGGL((k_stem<C, DL_FP32, false>), dim3(grid), dim3(256), 0, s, fd, g.nf, g.total_rows, g.dyn, w, b, offset,
-                           scale, cam, act, soff, keep, radius);
+                           scale, cam, act, soff, keep, radius, 0);
     return hipGetLastError();
 }
 
@@ -610,13 +611,13 @@ hipError_t launch_active_lists(const FrameDesc *fd, const Geometry &g, const uin
 
 hipError_t launch_stem(int C, const FrameDesc *fd, const Geometry &g, const float *w, const float *b,
                        float offset, float scale, const float2 *cam, void *act, int precision, bool planar,
-                       const uint8_t *keep, int radius, hipStream_t s)
+                       int shift, const uint8_t *keep, int radius, hipStream_t s)
 {
     switch (C) {
-    case 16: return stem_c<16>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
-    case 32: return stem_c<32>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
-    case 48: return stem_c<48>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
-    case 64: return stem_c<64>(fd, g, w, b, offset, scale, cam, act, precision, planar, keep, radius, s);
+    case 16: return stem_c<16>(fd, g, w, b, offset, scale, cam, act, precision, planar, shift, keep, radius, s);
+    case 32: return stem_c<32>(fd, g, w, b, offset, scale, cam, act, precision, planar, shift, keep, radius, s);
+    case 48: return stem_c<48>(fd, g, w, b, offset, scale, cam, act, precision, planar, shift, keep, radius, s);
+    case 64: return stem_c<64>(fd, g, w, b, offset, scale, cam, act, precision, planar, shift, keep, radius, s);
     default: return hipErrorInvalidValue;
     }
 }

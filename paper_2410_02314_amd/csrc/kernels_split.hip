@@ -61,13 +61,11 @@
 #include <vector>
 
 #include "conv_common.h"
+#include "split_common.h"
 
 namespace dloc {
 
 namespace {
-
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
 constexpr int TC = 32, PW = TC + 2, NTH = 256;
 
@@ -95,26 +93,6 @@ template <int C, int TR, int NH> struct SLds {
     static constexpr int TOTAL = MOFF + 16;
     static constexpr bool FITS = TOTAL <= 160 * 1024;
 };
-
-__device__ __forceinline__ uint32_t pack_h2(float a, float b)
-{
-    return __builtin_bit_cast(uint32_t, (h2{(_Float16)a, (_Float16)b}));
-}
-
-// largest |v| over the wave's lanes (v >= 0), in every lane
-__device__ __forceinline__ float wave_max(float v)
-{
-    int x = __float_as_int(v);           // non-negative floats order as integers
-#define DLOC_DPP_MAX(ctrl, rmask) x = max(x, __builtin_amdgcn_update_dpp(0, x, ctrl, rmask, 0xF, false))
-    DLOC_DPP_MAX(0x111, 0xF);            // row_shr:1
-    DLOC_DPP_MAX(0x112, 0xF);            // row_shr:2
-    DLOC_DPP_MAX(0x114, 0xF);            // row_shr:4
-    DLOC_DPP_MAX(0x118, 0xF);            // row_shr:8
-    DLOC_DPP_MAX(0x142, 0xA);            // row_bcast:15 into rows 1, 3
-    DLOC_DPP_MAX(0x143, 0xC);            // row_bcast:31 into rows 2, 3
-#undef DLOC_DPP_MAX
-    return __int_as_float(__builtin_amdgcn_readlane(x, 63));
-}
 
 // One tile in plain FP32 FMAs, a thread per output point, in tap and channel
 // order, from HBM and the unpacked weights: the rare tile whose values the FP16
@@ -289,9 +267,8 @@ k_split(ConvArgs a, Geometry geo)
         const v4f mv = *reinterpret_cast<const v4f *>(sM);
         const uint32_t mb = (uint32_t)__builtin_amdgcn_readfirstlane(
             __float_as_int(fmaxf(fmaxf(mv[0], mv[1]), fmaxf(mv[2], mv[3]))));
-        const int me = (int)(mb >> 23) - 127;            // floor(log2), -127 for zero and subnormals
-        const bool slow = slow_layer | (me >= 75) | ((me < -65) & (mb != 0));
-        const int sexp = slow || mb == 0 ? 0 : 20 * ((14 - me + 200) / 20 - 10);
+        const bool slow = slow_layer | split_misfit(mb);
+        const int sexp = slow || mb == 0 ? 0 : split_exp(mb);
         auto convert = [&](auto scaled) {
             const float sc = __int_as_float((127 + sexp) << 23);
 #pragma unroll
@@ -300,14 +277,7 @@ k_split(ConvArgs a, Geometry geo)
                 if ((k + 1) * NTH > NQ && tid + k * NTH >= NQ) continue;
                 char *d = stage + g * L::PLANE + k * (NTH / 4 * 32);
                 const v4f v = decltype(scaled)::value ? pf[g][k] * sc : pf[g][k];
-                uint2 hi{pack_h2(v[0], v[1]), pack_h2(v[2], v[3])};
-                asm("" : "+v"(hi.x), "+v"(hi.y));              // (one conversion for hi and for v - hi)
-                const h2 a0 = __builtin_bit_cast(h2, hi.x), a1 = __builtin_bit_cast(h2, hi.y);
-                const uint2 lo{
-                    pack_h2(fmaf((float)a0[0], -2048.f, v[0] * 2048.f), fmaf((float)a0[1], -2048.f, v[1] * 2048.f)),
-                    pack_h2(fmaf((float)a1[0], -2048.f, v[2] * 2048.f), fmaf((float)a1[1], -2048.f, v[3] * 2048.f))};
-                *reinterpret_cast<uint2 *>(d) = hi;
-                *reinterpret_cast<uint2 *>(d + L::LO) = lo;
+                split_store(v, L::LO, d);
             }
         };
         if (sexp) convert(std::true_type{});
@@ -557,22 +527,6 @@ k_pipe(ConvArgs a, Geometry geo)
             for (int r = 0; r < 4; ++r) m = fmaxf(m, fabsf(p[k][r]));
         return wave_max(m);
     };
-    auto convert = [&](const v4f &p, float sc, char *d) {
-        const v4f v = p * sc;
-        uint2 hi{pack_h2(v[0], v[1]), pack_h2(v[2], v[3])};
-        asm("" : "+v"(hi.x), "+v"(hi.y));                      // (one conversion for hi and for v - hi)
-        const h2 a0 = __builtin_bit_cast(h2, hi.x), a1 = __builtin_bit_cast(h2, hi.y);
-        const uint2 lo{pack_h2(fmaf((float)a0[0], -2048.f, v[0] * 2048.f), fmaf((float)a0[1], -2048.f, v[1] * 2048.f)),
-                       pack_h2(fmaf((float)a1[0], -2048.f, v[2] * 2048.f), fmaf((float)a1[1], -2048.f, v[3] * 2048.f))};
-        *reinterpret_cast<uint2 *>(d) = hi;
-        *reinterpret_cast<uint2 *>(d + L::PLANE) = lo;
-    };
-    // the largest power-of-two step (a multiple of 20) a group of largest
-    // magnitude bits mb allows; 60 for an all-zero group
-    auto fit_exp = [](uint32_t mb) {
-        const int e = (int)(mb >> 23) - 127;
-        return e < -65 ? 60 : e >= 75 ? -60 : 20 * ((14 - e + 200) / 20 - 10);
-    };
     auto group_max = [&](int b) {
         const v4f *p = reinterpret_cast<const v4f *>(sM + 8 * b);
         float m = fmaxf(fmaxf(p[0][0], p[0][1]), fmaxf(p[0][2], p[0][3]));
@@ -599,12 +553,12 @@ k_pipe(ConvArgs a, Geometry geo)
     }
     __syncthreads();
     uint32_t tmax = group_max(0);          // largest magnitude bits of the tile so far
-    int sexp = fit_exp(tmax);
+    int sexp = split_exp(tmax);
     {
         const float sc = __int_as_float((127 + sexp) << 23);
 #pragma unroll
         for (int k = 0; k < NPF; ++k)
-            convert(pf[0][k], sc, stage + k * (NTH / 4 * 32));
+            split_store(pf[0][k] * sc, L::PLANE, stage + k * (NTH / 4 * 32));
     }
     offsets(n1);
     s1 = source(n1);
@@ -635,7 +589,7 @@ k_pipe(ConvArgs a, Geometry geo)
             // needs it: the sums are rescaled once this group is in them), or
             // the next tile's own
             const uint32_t gm = group_max(buf ^ 1);
-            const int e = fit_exp(gm);
+            const int e = split_exp(gm);
             int se = e;
             if (g + 1 < G) {
                 tmax = max(tmax, gm);
@@ -706,7 +660,7 @@ k_pipe(ConvArgs a, Geometry geo)
                 // between the MFMAs: the next group into the other buffer, the
                 // loads that refill its registers, and the largest value of the
                 // group after it
-                if (c < NPF) convert(pf[ps][c], sc, sd + c * (NTH / 4 * 32));
+                if (c < NPF) split_store(pf[ps][c] * sc, L::PLANE, sd + c * (NTH / 4 * 32));
                 if (c >= NPF && c < 2 * NPF) pf[ps][c - NPF] = load(sl, (g + 1) % G, c - NPF);
                 if (c == 2 * NPF) {
 #pragma unroll
@@ -738,8 +692,7 @@ k_pipe(ConvArgs a, Geometry geo)
             }
             buf ^= 1;
         }
-        const int me = (int)(tmax >> 23) - 127;
-        if (slow_layer | (me >= 75) | ((me < -65) & (tmax != 0))) {
+        if (slow_layer | split_misfit(tmax)) {
             slow_tile<C, TR, NH>(a, n, reinterpret_cast<const float *>(static_cast<const char *>(a.wpk) + L::WBYTES), sB, sH);
         } else {
             const int osh = a.out_shift, om = (1 << osh) - 1;
@@ -854,29 +807,6 @@ int blocks_per_cu()
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, split_threads<C, TR>(), sh) != hipSuccess) nb = 1;
     return nb > 0 ? nb : 1;
-}
-
-// an FP16 value's bits (round to nearest even; |f| < 2^15) and the value of such bits
-uint16_t f16_bits(float f)
-{
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
-    const uint32_t sign = (u >> 16) & 0x8000u;
-    u &= 0x7FFFFFFFu;
-    if (u >= 0x38800000u) return (uint16_t)(sign | (((u + 0xFFFu + ((u >> 13) & 1u)) >> 13) - (112u << 10)));
-    float t;                                   // below 2^-14: steps of 2^-24, as those of 0.5 + |f|
-    std::memcpy(&t, &u, 4);
-    t += 0.5f;
-    std::memcpy(&u, &t, 4);
-    return (uint16_t)(sign | (u - 0x3F000000u));
-}
-float f16_value(uint16_t h)
-{
-    const uint32_t m = h & 0x7FFFu, u = (m + (112u << 10)) << 13;
-    float f;
-    if (m >= 0x400u) std::memcpy(&f, &u, 4);
-    else f = (float)m * 0x1p-24f;
-    return h & 0x8000u ? -f : f;
 }
 
 }  // namespace

@@ -1,0 +1,83 @@
+// FP32 values as two FP16 halves for the FP16 matrix cores (kernels_split.hip,
+// kernels_dsplit.hip): v 2^s = hi + lo 2^-11, hi = f16(v 2^s), lo = f16((v 2^s -
+// hi) 2^11).
+#pragma once
+#include <cstring>
+
+#include "dloc_internal.h"
+
+namespace dloc {
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_h2(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, (h2{(_Float16)a, (_Float16)b}));
+}
+
+// largest |v| over the wave's lanes (v >= 0), in every lane
+__device__ __forceinline__ float wave_max(float v)
+{
+    int x = __float_as_int(v);           // non-negative floats order as integers
+#define DLOC_DPP_MAX(ctrl, rmask) x = max(x, __builtin_amdgcn_update_dpp(0, x, ctrl, rmask, 0xF, false))
+    DLOC_DPP_MAX(0x111, 0xF);            // row_shr:1
+    DLOC_DPP_MAX(0x112, 0xF);            // row_shr:2
+    DLOC_DPP_MAX(0x114, 0xF);            // row_shr:4
+    DLOC_DPP_MAX(0x118, 0xF);            // row_shr:8
+    DLOC_DPP_MAX(0x142, 0xA);            // row_bcast:15 into rows 1, 3
+    DLOC_DPP_MAX(0x143, 0xC);            // row_bcast:31 into rows 2, 3
+#undef DLOC_DPP_MAX
+    return __int_as_float(__builtin_amdgcn_readlane(x, 63));
+}
+
+// four values' halves to LDS: hi at d, lo at d + lo_off
+__device__ __forceinline__ void split_store(const v4f &v, int lo_off, char *d)
+{
+    uint2 hi{pack_h2(v[0], v[1]), pack_h2(v[2], v[3])};
+    asm("" : "+v"(hi.x), "+v"(hi.y));                  // (one conversion for hi and for v - hi)
+    const h2 a0 = __builtin_bit_cast(h2, hi.x), a1 = __builtin_bit_cast(h2, hi.y);
+    const uint2 lo{pack_h2(fmaf((float)a0[0], -2048.f, v[0] * 2048.f), fmaf((float)a0[1], -2048.f, v[1] * 2048.f)),
+                   pack_h2(fmaf((float)a1[0], -2048.f, v[2] * 2048.f), fmaf((float)a1[1], -2048.f, v[3] * 2048.f))};
+    *reinterpret_cast<uint2 *>(d) = hi;
+    *reinterpret_cast<uint2 *>(d + lo_off) = lo;
+}
+
+// The exponent s (a multiple of 20) that brings a largest magnitude of bits mb
+// into [2^-5, 2^15); 60 at most (all zero), -60 at least.
+__device__ __forceinline__ int split_exp(uint32_t mb)
+{
+    const int e = (int)(mb >> 23) - 127;               // floor(log2), -127 for zero and subnormals
+    return e < -65 ? 60 : e >= 75 ? -60 : 20 * ((14 - e + 200) / 20 - 10);
+}
+// ... and whether the halves cannot hold values of that magnitude
+__device__ __forceinline__ bool split_misfit(uint32_t mb)
+{
+    const int e = (int)(mb >> 23) - 127;
+    return (e >= 75) | ((e < -65) & (mb != 0));
+}
+
+// an FP16 value's bits (round to nearest even; |f| < 2^15) and the value of such bits
+inline uint16_t f16_bits(float f)
+{
+    uint32_t u;
+    std::memcpy(&u, &f, 4);
+    const uint32_t sign = (u >> 16) & 0x8000u;
+    u &= 0x7FFFFFFFu;
+    if (u >= 0x38800000u) return (uint16_t)(sign | (((u + 0xFFFu + ((u >> 13) & 1u)) >> 13) - (112u << 10)));
+    float t;                                   // below 2^-14: steps of 2^-24, as those of 0.5 + |f|
+    std::memcpy(&t, &u, 4);
+    t += 0.5f;
+    std::memcpy(&u, &t, 4);
+    return (uint16_t)(sign | (u - 0x3F000000u));
+}
+inline float f16_value(uint16_t h)
+{
+    const uint32_t m = h & 0x7FFFu, u = (m + (112u << 10)) << 13;
+    float f;
+    if (m >= 0x400u) std::memcpy(&f, &u, 4);
+    else f = (float)m * 0x1p-24f;
+    return h & 0x8000u ? -f : f;
+}
+
+}  // namespace dloc
