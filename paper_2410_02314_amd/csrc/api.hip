@@ -77,6 +77,7 @@ struct dl_net {
     int *d_dil = nullptr;           // dilations [nb]
     size_t wpk_stride = 0;
     int packed_precision = -1;
+    bool balanced = false;          // what is packed, and d_stem, d_head, d_bias, hold balance_params
     uint64_t packed_gen = 0;        // counts repacks (graphs check it: they hold d_wpk)
 
     char *ws = nullptr;
@@ -521,14 +522,14 @@ int upload_desc(dl_net *net, const std::vector<FrameDesc> &fd, hipStream_t s, Fr
     return slot;
 }
 
-// stem, head and (residual nets) conv biases from net->params to the device
-int upload_small_weights(dl_net *net)
+// stem, head and (residual nets) conv biases of `params` to the device
+int upload_small_weights(dl_net *net, const std::vector<float> &params)
 {
     const int C = net->C, nb = net->nb;
-    const float *p = net->params.data();
+    const float *p = params.data();
     const size_t nstem = (size_t)C * 9 + C, nhead = (size_t)net->nh * C + net->nh;
     HIPCHK(net, hipMemcpy(net->d_stem, p, nstem * 4, hipMemcpyHostToDevice));
-    HIPCHK(net, hipMemcpy(net->d_head, p + net->params.size() - nhead, nhead * 4, hipMemcpyHostToDevice));
+    HIPCHK(net, hipMemcpy(net->d_head, p + params.size() - nhead, nhead * 4, hipMemcpyHostToDevice));
     if (!net->dL) {
         std::vector<float> bias((size_t)nb * 2 * C);
         const float *q = p + nstem;
@@ -550,21 +551,153 @@ int sync_trained(dl_net *net)
     if (!net->t_dirty) return DL_OK;
     HIPCHK(net, hipDeviceSynchronize());
     HIPCHK(net, hipMemcpy(net->params.data(), net->t_params, net->params.size() * 4, hipMemcpyDeviceToHost));
-    int rc = upload_small_weights(net);
+    int rc = upload_small_weights(net, net->params);
     if (rc) return rc;
+    net->balanced = false;
     net->t_dirty = false;
     net->packed_precision = -1;
     return DL_OK;
 }
 
-// Dense networks: every conv's weights in the k_dconv layout and its bias,
+// A conv of the flat parameters, for balance_params: rows of cin x taps weights,
+// their largest magnitudes, and of each input channel the largest weight
+// relative to its row's.
+struct BalanceConv {
+    float *w, *b;
+    int cout, cin, taps;
+    std::vector<float> top, reach;
+    BalanceConv(float *&p, int cout_, int cin_, int taps_)
+        : w(p), b(p + (size_t)cout_ * cin_ * taps_), cout(cout_), cin(cin_), taps(taps_), top(cout_), reach(cin_, 0.f)
+    {
+        std::vector<float> m(cin);
+        const float *q = w;
+        for (int o = 0; o < cout; ++o) {
+            float r = 0.f;
+            for (int c = 0; c < cin; ++c) {
+                m[c] = 0.f;
+                for (int t = 0; t < taps; ++t, ++q) m[c] = std::max(m[c], std::fabs(*q));
+                r = std::max(r, m[c]);
+            }
+            top[o] = r;
+            const float inv = r >= 0x1p-100f && r < 0x1p100f ? 1.f / r : 0.f;
+            for (int c = 0; c < cin; ++c) reach[c] = std::max(reach[c], m[c] * inv);
+        }
+        p = b + cout;
+    }
+};
+using BalanceReaders = std::vector<std::pair<BalanceConv *, int>>;     // a conv and its first such input channel
+
+// The FP16 pairs of a tile's inputs share an exponent, so a channel far below
+// the others keeps fewer bits; that matters where larger weights make up for
+// it.  A channel whose readers' weights are all below 2^-8 of their rows' is
+// therefore scaled down by a power of two where it is made (weights and bias;
+// the ReLUs, residual sums, pooling and upsampling commute with it) and its
+// readers' weights up: the same network in FP32.  Returns whether any was.
+bool balance_channels(const std::vector<BalanceConv *> &makers, const BalanceReaders &readers)
+{
+    bool any = false;
+    for (int c = 0; c < makers[0]->cout; ++c) {
+        float m = 0.f, small = INFINITY;
+        for (auto &r : readers) m = std::max(m, r.first->reach[r.second + c]);
+        for (auto *k : makers)
+            if (k->top[c] > 0.f) small = std::min(small, k->top[c]);
+        if (!(m > 0.f && m < 0x1p-8f)) continue;
+        const int e = std::min(60, -std::ilogb(m));
+        if (!(std::ldexp(small, -e) >= 0x1p-60f)) continue;       // (the weights would leave the halves' range)
+        for (auto *k : makers) {
+            const size_t row = (size_t)k->cin * k->taps;
+            for (size_t i = 0; i < row; ++i) k->w[c * row + i] = std::ldexp(k->w[c * row + i], -e);
+            k->b[c] = std::ldexp(k->b[c], -e);
+        }
+        for (auto &r : readers)
+            for (int o = 0; o < r.first->cout; ++o)
+                for (int t = 0; t < r.first->taps; ++t) {
+                    float &v = r.first->w[((size_t)o * r.first->cin + r.second + c) * r.first->taps + t];
+                    v = std::ldexp(v, e);
+                }
+        any = true;
+    }
+    return any;
+}
+
+// net->params with every channel balanced; *any: whether they differ
+std::vector<float> balance_params(const dl_net *net, bool *any)
+{
+    std::vector<float> q = net->params;
+    const int C = net->C, L = net->dL, G = net->dG, nb = net->nb;
+    float *p = q.data();
+    std::vector<BalanceConv> k;
+    k.reserve((size_t)nb * (L ? L + 1 : 2) + 6);
+    k.emplace_back(p, C, 1, 9);
+    *any = false;
+    if (!L) {
+        for (int i = 0; i < 2 * nb; ++i) k.emplace_back(p, C, C, 9);
+        k.emplace_back(p, net->nh, C, 1);
+        std::vector<BalanceConv *> makers{&k[0]};       // of the residual stream
+        BalanceReaders readers{{&k[2 * nb + 1], 0}};
+        for (int b = 0; b < nb; ++b) {
+            *any |= balance_channels({&k[2 * b + 1]}, {{&k[2 * b + 2], 0}});
+            makers.push_back(&k[2 * b + 2]);
+            readers.push_back({&k[2 * b + 1], 0});
+        }
+        *any |= balance_channels(makers, readers);
+        return q;
+    }
+    for (int b = 0; b < nb; ++b) {
+        for (int i = 0; i < L; ++i) k.emplace_back(p, G, C + i * G, 9);
+        k.emplace_back(p, C, C + L * G, 1);
+    }
+    const size_t n = k.size();                          // the U-Net's d1, d2, u1, u0, or the head
+    if (net->unet)
+        for (int i = 0; i < 4; ++i) k.emplace_back(p, C, i < 2 ? C : 2 * C, 9);
+    k.emplace_back(p, net->nh, C, 1);
+    for (int b = 0; b <= nb; ++b) {
+        BalanceConv *blk = k.data() + 1 + (size_t)b * (L + 1);
+        BalanceReaders readers;                         // of the block's input, made by the stem or the transition before
+        if (b < nb)
+            for (int i = 0; i <= L; ++i) readers.push_back({blk + i, 0});
+        else if (net->unet) readers = {{&k[n], 0}, {&k[n + 3], 0}};
+        else readers = {{&k[n], 0}};
+        *any |= balance_channels({b ? blk - 1 : &k[0]}, readers);
+        for (int i = 0; i < L && b < nb; ++i) {
+            BalanceReaders later;
+            for (int j = i + 1; j <= L; ++j) later.push_back({blk + j, C + i * G});
+            *any |= balance_channels({blk + i}, later);
+        }
+    }
+    if (net->unet) {
+        *any |= balance_channels({&k[n]}, {{&k[n + 1], 0}, {&k[n + 2], 0}});
+        *any |= balance_channels({&k[n + 1]}, {{&k[n + 2], C}});
+        *any |= balance_channels({&k[n + 2]}, {{&k[n + 3], C}});
+        *any |= balance_channels({&k[n + 3]}, {{&k[n + 4], 0}});
+    }
+    return q;
+}
+
+// The parameters to pack for the net's precision; the small weights on the
+// device become theirs as well.
+int params_to_pack(dl_net *net, std::vector<float> &q)
+{
+    bool any = false;
+    if (net->dL || conv_planar(net->C, net->cfg.precision)) q = balance_params(net, &any);
+    if (!any) q = net->params;
+    if (any || net->balanced) {
+        HIPCHK(net, hipDeviceSynchronize());           // kernels still queued on any stream may read the old ones
+        if (int rc = upload_small_weights(net, q)) return rc;
+    }
+    net->balanced = any;
+    return DL_OK;
+}
+
+// Dense networks: every conv's weights in the layouts of k_dpipe and its bias,
 // in run order, in one device buffer (FP32; packed once).
 int pack_dense(dl_net *net)
 {
     const int C = net->C, L = net->dL, G = net->dG, CT = C + L * G;
-    std::vector<float> host;
+    std::vector<float> host, prm;
+    if (int rc = params_to_pack(net, prm)) return rc;
     net->dense.clear();
-    const float *p = net->params.data() + (size_t)C * 9 + C;
+    const float *p = prm.data() + (size_t)C * 9 + C;
     auto room = [&](size_t n) {
         const size_t o = (host.size() + 63) / 64 * 64;
         host.resize(o + n);
@@ -629,8 +762,9 @@ int ensure_packed(dl_net *net)
     const size_t per = conv_packed_bytes(C, net->cfg.precision);
     const size_t stride = align_up(per);
     std::vector<char> host(stride * net->nb * 2);
-    std::vector<float> wscale((size_t)net->nb * 2 * C, 0.f);
-    const float *p = net->params.data() + (size_t)C * 9 + C;
+    std::vector<float> wscale((size_t)net->nb * 2 * C, 0.f), prm;
+    if (int rc = params_to_pack(net, prm)) return rc;
+    const float *p = prm.data() + (size_t)C * 9 + C;
     for (int b = 0; b < net->nb; ++b)
         for (int k = 0; k < 2; ++k) {
             pack_conv_weights(C, net->cfg.precision, p, host.data() + (size_t)(b * 2 + k) * stride,
@@ -2594,6 +2728,27 @@ int dl_debug_conv_layer(dl_net *net, const float *d_in, const float *d_res, int 
     a.wpk = static_cast<char *>(net->d_wpk) + (size_t)(blk * 2 + which) * net->wpk_stride;
     a.bias = net->d_bias + (size_t)(blk * 2 + which) * net->C;
     a.wscale = net->d_wscale + (size_t)(blk * 2 + which) * net->C;
+    // the layer of a balanced net, as its weights give it: packed for this call
+    struct DevBuf {
+        char *p = nullptr;
+        ~DevBuf()
+        {
+            if (p) (void)hipFree(p);         // (waits for the kernel that reads it)
+        }
+    } own;
+    if (net->balanced) {
+        const int C = net->C;
+        const size_t nw = (size_t)C * C * 9, per = align_up(conv_packed_bytes(C, net->cfg.precision));
+        const float *w = net->params.data() + (size_t)C * 10 + (size_t)(blk * 2 + which) * (nw + C);
+        std::vector<char> host(per + 8 * C);
+        pack_conv_weights(C, net->cfg.precision, w, host.data(), reinterpret_cast<float *>(host.data() + per));
+        std::memcpy(host.data() + per + 4 * C, w + nw, 4 * C);
+        HIPCHK(net, hipMalloc(&own.p, host.size()));
+        HIPCHK(net, hipMemcpy(own.p, host.data(), host.size(), hipMemcpyHostToDevice));
+        a.wpk = own.p;
+        a.wscale = reinterpret_cast<float *>(own.p + per);
+        a.bias = a.wscale + C;
+    }
     a.tr = g.trb[blk];
     a.pstride = 4 * net->C;              // the caller's plain NHWC
     a.gstride = 64;
@@ -2602,6 +2757,7 @@ int dl_debug_conv_layer(dl_net *net, const float *d_in, const float *d_res, int 
     grid = std::max(8, grid / 8 * 8);
     HIPCHK(net, launch_conv(net->C, net->cfg.precision, a, g, grid, s));
     HIPCHK(net, hipEventRecord(net->desc_ev[slot], s));
+    if (own.p) HIPCHK(net, hipStreamSynchronize(s));
     return DL_OK;
 }
 

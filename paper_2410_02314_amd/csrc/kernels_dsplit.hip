@@ -553,14 +553,6 @@ hipError_t launch_nt(int nt, const DensePipeArgs &a, const Geometry &g, int ncu,
     return hipErrorInvalidValue;
 }
 
-// max |w| of an output channel to the power of two that brings it into [1, 2);
-// *fit: false where the FP16 halves cannot hold it
-float channel_scale(float mx, bool *fit)
-{
-    *fit &= mx == 0.f || (mx >= 0x1p-60f && mx < 0x1p75f);
-    return mx > 0.f ? std::ldexp(1.f, std::min(60, std::max(-60, -std::ilogb(mx)))) : 1.f;
-}
-
 }  // namespace
 
 hipError_t launch_dpipe(int nb_out, int fuse, int nt, const DensePipeArgs &a, const Geometry &g, int ncu, hipStream_t s)
@@ -584,13 +576,13 @@ void dpipe_pack(int cout, int cin, int ld, int taps, const float *W, void *dst, 
 {
     const int NB = cout / 16, NS = taps == 9 ? 5 : 1;
     uint16_t *o = static_cast<uint16_t *>(dst);
-    std::vector<float> up(cout);
+    const int row = cin * taps;
+    std::vector<uint16_t> half((size_t)2 * cout * row);    // [oc][hi, lo][weight]
     bool fit = true;
     for (int oc = 0; oc < cout; ++oc) {
-        float mx = 0.f;
-        for (int k = 0; k < cin * taps; ++k) mx = std::fmax(mx, std::fabs(W[(size_t)oc * ld * taps + k]));
-        up[oc] = channel_scale(mx, &fit);
-        scale[oc] = 1.f / up[oc];
+        uint16_t *h = half.data() + (size_t)2 * oc * row;
+        scale[oc] = split_row(W + (size_t)oc * ld * taps, row, h, h + row);
+        fit &= scale[oc] != 0.f;
     }
     if (!fit) std::fill(scale, scale + cout, 0.f);         // every tile in plain FP32
     for (int g = 0; g < cin / 16; ++g)
@@ -605,11 +597,10 @@ void dpipe_pack(int cout, int cin, int ld, int taps, const float *W, void *dst, 
                 const int c0 = g * 16 + (kq & 1) * 8;
                 for (int oc = 0; oc < cout; ++oc) {
                     uint16_t *f = o + ((size_t)(((g * NS + st) * NB + oc / 16) * 2) * 64 + kq * 16 + oc % 16) * 8;
+                    const uint16_t *h = half.data() + (size_t)2 * oc * row + c0 * taps + std::max(tap, 0);
                     for (int e = 0; e < 8; ++e) {
-                        const float w = tap >= 0 && fit ? W[((size_t)oc * ld + c0 + e) * taps + tap] * up[oc] : 0.f;
-                        const uint16_t hb = f16_bits(w);
-                        f[e] = hb;
-                        f[512 + e] = f16_bits((w - f16_value(hb)) * 2048.f);
+                        f[e] = tap >= 0 ? h[e * taps] : 0;
+                        f[512 + e] = tap >= 0 ? h[row + e * taps] : 0;
                     }
                 }
             }

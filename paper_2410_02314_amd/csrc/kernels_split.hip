@@ -825,16 +825,14 @@ void split_pack_weights(int C, const float *W, void *dst, float *scale)
     // k_pipe takes K by groups of 16 channels, each with closing steps of its own
     const int NG = C == 48 ? 3 : 1, CG = C / NG, CH8 = CG / 8, NB = C / 16;
     const int FULL = 3 * CH8 / 4, NS = 3 * FULL + (3 * CH8 % 4 ? 2 : 0), NSTEP = NG * NS;
+    const int row = C * 9;
     uint16_t *o = static_cast<uint16_t *>(dst);
-    std::vector<float> up(C, 1.f);
+    std::vector<uint16_t> half((size_t)2 * C * row);       // [oc][hi, lo][weight]
     bool fit = true;
-    for (int oc = 0; oc < C; ++oc) {               // max |w up| in [1, 2), up a power of two in 2^-60 .. 2^60
-        float mx = 0.f;
-        for (int k = 0; k < C * 9; ++k) mx = std::fmax(mx, std::fabs(W[(size_t)oc * C * 9 + k]));
-        const int e = mx > 0.f ? std::min(60, std::max(-60, -std::ilogb(mx))) : 0;
-        fit &= mx == 0.f || (mx >= 0x1p-60f && mx < 0x1p75f);
-        up[oc] = std::ldexp(1.f, e);
-        scale[oc] = std::ldexp(1.f, -e);
+    for (int oc = 0; oc < C; ++oc) {
+        uint16_t *h = half.data() + (size_t)2 * oc * row;
+        scale[oc] = split_row(W + (size_t)oc * row, row, h, h + row);
+        fit &= scale[oc] != 0.f;
     }
     if (!fit) std::fill(scale, scale + C, 0.f);    // every tile in plain FP32
     for (int st = 0; st < NSTEP; ++st)
@@ -852,12 +850,10 @@ void split_pack_weights(int C, const float *W, void *dst, float *scale)
             const int v = i / CH8, c0 = g * CG + (i % CH8) * 8;
             for (int oc = 0; oc < C; ++oc) {
                 uint16_t *f = o + ((size_t)((st * NB + oc / 16) * 2) * 64 + kq * 16 + oc % 16) * 8;
-                const float *w = W + ((size_t)oc * C + c0) * 9 + 3 * (u < 3 ? u : 0) + v;
+                const uint16_t *h = half.data() + (size_t)2 * oc * row + c0 * 9 + 3 * (u < 3 ? u : 0) + v;
                 for (int e = 0; e < 8; ++e) {
-                    const float ws = u < 3 && fit ? w[9 * e] * up[oc] : 0.f;
-                    const uint16_t hb = f16_bits(ws);
-                    f[e] = hb;
-                    f[512 + e] = f16_bits((ws - f16_value(hb)) * 2048.f);
+                    f[e] = u < 3 ? h[9 * e] : 0;
+                    f[512 + e] = u < 3 ? h[row + 9 * e] : 0;
                 }
             }
         }

@@ -2,6 +2,8 @@
 // kernels_dsplit.hip): v 2^s = hi + lo 2^-11, hi = f16(v 2^s), lo = f16((v 2^s -
 // hi) 2^11).
 #pragma once
+#include <algorithm>
+#include <cmath>
 #include <cstring>
 
 #include "dloc_internal.h"
@@ -57,27 +59,56 @@ __device__ __forceinline__ bool split_misfit(uint32_t mb)
     return (e >= 75) | ((e < -65) & (mb != 0));
 }
 
-// an FP16 value's bits (round to nearest even; |f| < 2^15) and the value of such bits
+// an FP16 value's bits (round to nearest even; |f| < 2^15) and the value of such
+// bits, both without branches: loops over them become vector code
 inline uint16_t f16_bits(float f)
 {
-    uint32_t u;
+    uint32_t u, v;
     std::memcpy(&u, &f, 4);
     const uint32_t sign = (u >> 16) & 0x8000u;
     u &= 0x7FFFFFFFu;
-    if (u >= 0x38800000u) return (uint16_t)(sign | (((u + 0xFFFu + ((u >> 13) & 1u)) >> 13) - (112u << 10)));
     float t;                                   // below 2^-14: steps of 2^-24, as those of 0.5 + |f|
     std::memcpy(&t, &u, 4);
     t += 0.5f;
-    std::memcpy(&u, &t, 4);
-    return (uint16_t)(sign | (u - 0x3F000000u));
+    std::memcpy(&v, &t, 4);
+    const uint32_t n = ((u + 0xFFFu + ((u >> 13) & 1u)) >> 13) - (112u << 10);
+    return (uint16_t)(sign | (u >= 0x38800000u ? n : v - 0x3F000000u));
 }
 inline float f16_value(uint16_t h)
 {
-    const uint32_t m = h & 0x7FFFu, u = (m + (112u << 10)) << 13;
+    const uint32_t u = (uint32_t)(h & 0x7FFFu) << 13 | (uint32_t)(h & 0x8000u) << 16;
     float f;
-    if (m >= 0x400u) std::memcpy(&f, &u, 4);
-    else f = (float)m * 0x1p-24f;
-    return h & 0x8000u ? -f : f;
+    std::memcpy(&f, &u, 4);
+    return f * 0x1p112f;                       // the exponents' biases differ by 112
+}
+
+// A row of n weights as halves of w up, up the power of two in 2^-60 .. 2^60
+// that brings the largest into [1, 2).  Returns 1 / up; 0 (the row's tiles go
+// through plain FP32) where the halves cannot hold it.
+inline float split_row(const float *w, int n, uint16_t *hi, uint16_t *lo)
+{
+    int32_t mb = 0;
+    for (int k = 0; k < n; ++k) {
+        int32_t u;
+        std::memcpy(&u, w + k, 4);
+        mb = std::max(mb, u & 0x7FFFFFFF);
+    }
+    float mx;
+    std::memcpy(&mx, &mb, 4);
+    if (mb && !(mx >= 0x1p-60f && mx < 0x1p75f)) {
+        std::fill(hi, hi + n, (uint16_t)0);
+        std::fill(lo, lo + n, (uint16_t)0);
+        return 0.f;
+    }
+    const int e = mb ? std::min(60, std::max(-60, -std::ilogb(mx))) : 0;
+    const float up = std::ldexp(1.f, e);
+    for (int k = 0; k < n; ++k) {
+        const float ws = w[k] * up;
+        const uint16_t h = f16_bits(ws);
+        hi[k] = h;
+        lo[k] = f16_bits((ws - f16_value(h)) * 2048.f);
+    }
+    return std::ldexp(1.f, -e);
 }
 
 }  // namespace dloc

@@ -59,7 +59,7 @@ def test_magnitudes(e, unet):
     assert map_rel_err(_maps(spec, w, frames), ref).max() <= TOL
 
 
-@pytest.mark.parametrize("e0,e1", [(12, 0), (0, 12), (-12, 0), (0, -12)])
+@pytest.mark.parametrize("e0,e1", [(12, 0), (0, 12), (-12, 0), (0, -12), (30, 30)])
 def test_planes_of_different_magnitude(e0, e1):
     """A layer's input plane 2^e times another's: the sums change their exponent
     at the plane that needs it."""

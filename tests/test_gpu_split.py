@@ -108,3 +108,54 @@ def test_channel_groups_of_different_magnitude(exps):
     wts, net = _layer(48, 1)
     y, m = _sums(x, wts["blk0.w1"], 1)
     _check(_run(net, x), np.maximum(y, 0), 48, m, wts["blk0.w1"], float(np.abs(x).max()))
+
+
+@pytest.mark.parametrize("C", [16, 32, 48])
+def test_unbalanced_channels(C):
+    """Channels scaled by powers of two where they are made and back where they
+    are read, up to 2^60 apart: the same network, and its maps to the FP32
+    path's 1e-4 of |o| + rms against the FP64 oracle; a single layer still runs
+    with the weights as given, and a change to BF16 and back changes nothing."""
+    import oracle
+    import paper_2410_02314_amd as dl
+    from tests.parity import map_rel_err
+    spec = S.NetSpec("X", C, (1, 2), head_outputs=5)
+    w = S.he_normal_weights(spec, 21, bias_std=0.05)
+    frames = S.render_frames(1, 50, 70, "tiny", 22)
+    ref = oracle.net_maps_batch(frames, spec, w)
+    rng = np.random.default_rng(23)
+    stream, hidden = (2.0 ** rng.integers(-30, 31, (n, C)).astype(np.float32) for n in (1, 2))
+    stream = stream[0]
+    w["stem.w"] *= stream[:, None, None, None]
+    w["stem.b"] *= stream
+    for k in (0, 1):
+        h = hidden[k]
+        w[f"blk{k}.w1"] *= h[:, None, None, None] / stream[None, :, None, None]
+        w[f"blk{k}.b1"] *= h
+        w[f"blk{k}.w2"] *= stream[:, None, None, None] / h[None, :, None, None]
+        w[f"blk{k}.b2"] *= stream
+    w["head.w"] /= stream[None, :]
+    net = dl.Net(S.serialize_weights(spec, w), precision="fp32")
+    fr = torch.from_numpy(frames).cuda()
+
+    def maps():
+        m = torch.full((1, 5, 50, 70), float("nan"), dtype=torch.float32, device="cuda")
+        net.maps_device(fr, m)
+        torch.cuda.synchronize()
+        return m.cpu().numpy()
+
+    a = maps()
+    assert map_rel_err(a, ref).max() <= 1e-4
+    x = (rng.standard_normal((1, 12, 40, C)) * stream).astype(np.float32)
+    t = torch.from_numpy(x).cuda()
+    out = torch.empty_like(t)
+    net.debug_conv_layer(t, None, 1, 0, out)
+    torch.cuda.synchronize()
+    y, m = _sums(x, w["blk1.w1"], 2)
+    y, m = y + w["blk1.b1"], m + np.abs(w["blk1.b1"])
+    top = np.abs(x).max() * np.abs(w["blk1.w1"]).max(axis=(1, 2, 3)) * 9 * C
+    assert (np.abs(out.cpu().numpy() - np.maximum(y, 0)) <= 1e-4 * m + 2.0 ** -30 * top).all()
+    net.set_config(precision="bf16")
+    maps()
+    net.set_config(precision="fp32")
+    assert np.array_equal(maps(), a)
