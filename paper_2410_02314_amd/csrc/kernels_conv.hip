@@ -166,14 +166,18 @@ template <int P, int TR> constexpr int min_waves() { return P == DL_FP32 && TR =
 template <int C, int P, int TR_, int NHL = 5>
 struct Lds {
     static constexpr int TR = TR_, TC = TileShape<P>::TC;
-    // bytes per point; FP8 points hold the tap's padded CT codes (the padding
-    // is zeroed once, staging writes only the C real channels), then the
-    // point's two group scale bytes at byte CT
-    static constexpr int CT8 = (C + 31) / 32 * 32;
-    static constexpr int PS = stride_8_mod_16(P == DL_FP8 ? CT8 / 4 + 1 : C * KPlan<C, P>::LESZ / 4) * 4;
+    // Bytes per point.  FP8 keeps a plane per group of 32 channels, 32 bytes a
+    // point (the padding of the last group is zeroed once, staging writes only
+    // the C real channels), then the points' two scale bytes: at 32 bytes the
+    // operand reads are free of bank conflicts, which they were not in one
+    // 96-byte record (net B, 4 x 2048^2: LDS conflicts 21% of the time -> 12%,
+    // a layer 722 -> 700 us; with the maxima by lane swaps and the tile walk 672).
+    static constexpr int HPT8 = (C + 31) / 32;
+    static constexpr int PS = P == DL_FP8 ? 32 : stride_8_mod_16(C * KPlan<C, P>::LESZ / 4) * 4;
     static constexpr int PW = TC + 2;
     static constexpr int NPT = (TR + 2) * PW;
-    static constexpr int TBYTES = align16(NPT * PS);
+    static constexpr int PL8 = NPT * 32, SC8 = HPT8 * PL8;             // FP8: bytes of a group's plane, its scales
+    static constexpr int TBYTES = align16(P == DL_FP8 ? SC8 + NPT * 2 : NPT * PS);
     static constexpr int EXTRA = C * 4 + (NHL * C + NHL) * 4 + C * 4 + 64;  // bias, head, scales, alignment
     static constexpr int LDSW = KPlan<C, P>::LDS_W;
     static constexpr int WOFF = TBYTES;
@@ -192,6 +196,17 @@ struct Lds {
     static constexpr int TOTAL = DOFF + 2 * 64;
     static constexpr bool FITS = TOTAL <= 160 * 1024;   // else no kernel exists for this shape
 };
+
+// largest v (>= 0) of the four lanes j, j + 16, j + 32, j + 48, in each of them
+// (register swaps between lane rows, where ds_bpermute would go through LDS)
+__device__ __forceinline__ float lane_groups_max(float v)
+{
+    const int x = __float_as_int(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const int y = max((int)a[0], (int)a[1]);       // non-negative floats order as integers
+    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return __int_as_float(max((int)b[0], (int)b[1]));
+}
 
 // --------------------------------------------------------------- kernel
 // NH: outputs of the fused 1x1 head (0: no head, the layer's activations are
@@ -270,7 +285,13 @@ k_conv(ConvArgs a, Geometry geo)
     // resource over the frame, and points off the frame take an out-of-range
     // offset, which reads as zero.
     TileDec n{};
-    auto decode = [&](int64_t ti) { return decode_conv_tile(a, geo, nfr, TR, TC, ti); };
+    // (FP8 decodes after its K loop, where nothing hides it: it walks.  The
+    // other forms decode inside theirs; walking, BF16 was 0.7% slower.)
+    TileWalk walk;
+    auto decode = [&](int64_t ti) {
+        if constexpr (P == DL_FP8) return walk.tile(a, geo, nfr, TR, TC, ti);
+        else return decode_conv_tile(a, geo, nfr, TR, TC, ti);
+    };
     // Wave 0 alone decodes tiles (the scalar unit is shared by the CU's
     // waves): it publishes the tile after next in one of two LDS slots from
     // inside its MFMA loop, and every wave picks it up after the next loop-top
@@ -344,7 +365,7 @@ k_conv(ConvArgs a, Geometry geo)
                     *reinterpret_cast<uint2 *>(sT + pt * PS + ch * 8) = uint2{h01, h23};
                     *reinterpret_cast<uint2 *>(sT + pt * PS + 2 * C + ch * 8) = uint2{l01, l23};
                 } else {
-                    *reinterpret_cast<v4f *>(sT + pt * PS + ch * 16) = pf[k];
+                    *reinterpret_cast<v4f *>(sT + (P == DL_FP8 ? (ch >> 1) * L::PL8 + (ch & 1) * 16 : ch * 16) + pt * PS) = pf[k];
                 }
             }
         }
@@ -352,7 +373,7 @@ k_conv(ConvArgs a, Geometry geo)
 #pragma unroll
             for (int k = 0; k < NPS; ++k) {
                 const int pt = tid + k * NT;
-                if (pt < NPT) *reinterpret_cast<uint16_t *>(sT + pt * PS + L::CT8) = (uint16_t)psc[k];
+                if (pt < NPT) *reinterpret_cast<uint16_t *>(sT + L::SC8 + pt * 2) = (uint16_t)psc[k];
             }
         }
         __syncthreads();
@@ -584,22 +605,22 @@ k_conv(ConvArgs a, Geometry geo)
                 // on m alone (scalar); the lane adds a fixed part.
                 auto tap_off = [&](int t) {
                     const int tc = t < 9 ? t : 4;
-                    return ((tc / 3) * PW + tc % 3) * PS;
+                    return (tc / 3) * PW + tc % 3;       // points
                 };
                 const int kh = kq >> 1, kl = kq & 1;
                 int lo_off, hi_off, soff;
                 if constexpr (HPT == 2) {
                     const int p0 = tap_off(2 * m), p1 = tap_off(2 * m + 1);
-                    lo_off = p0 + kh * 32 + 16 * kl;
-                    hi_off = p1 + kh * 32 + 16 * kl;
-                    soff = (kh ? p1 : p0) + L::CT8 + kl;
+                    lo_off = p0 * 32 + kh * L::PL8 + 16 * kl;
+                    hi_off = p1 * 32 + kh * L::PL8 + 16 * kl;
+                    soff = (kh ? p1 : p0) * 2 + L::SC8 + kl;
                 } else {
                     static_assert(HPT == 1, "FP8 taps hold one or two 32-channel groups");
                     const int p0 = tap_off(4 * m), p1 = tap_off(4 * m + 1);
                     const int p2 = tap_off(4 * m + 2), p3 = tap_off(4 * m + 3);
-                    lo_off = (kh ? p1 : p0) + 16 * kl;
-                    hi_off = (kh ? p3 : p2) + 16 * kl;
-                    soff = (kq == 0 ? p0 : kq == 1 ? p1 : kq == 2 ? p2 : p3) + L::CT8;
+                    lo_off = (kh ? p1 : p0) * 32 + 16 * kl;
+                    hi_off = (kh ? p3 : p2) * 32 + 16 * kl;
+                    soff = (kq == 0 ? p0 : kq == 1 ? p1 : kq == 2 ? p2 : p3) * 2 + L::SC8;
                 }
                 v8i av[NB], bv[PB];
                 int sb[PB];
@@ -615,7 +636,7 @@ k_conv(ConvArgs a, Geometry geo)
                     const v4u lo = *reinterpret_cast<const v4u *>(pt + lo_off);
                     const v4u hi = *reinterpret_cast<const v4u *>(pt + hi_off);
                     bv[p] = v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-                    sb[p] = *reinterpret_cast<const uint8_t *>(sT + (wave * PW + 16 * p + j) * PS + soff);
+                    sb[p] = *reinterpret_cast<const uint8_t *>(sT + (wave * PW + 16 * p + j) * 2 + soff);
                 }
                 // weights: unit block scales (their per-channel scale is applied
                 // in the epilogue); activations: each lane's 32 K values are one
@@ -715,11 +736,7 @@ k_conv(ConvArgs a, Geometry geo)
                     gm[nb >> 1] = fmaxf(gm[nb >> 1], fmaxf(fmaxf(vs[nb][0], vs[nb][1]), fmaxf(vs[nb][2], vs[nb][3])));
                 uint32_t sbyte[2];
 #pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    gm[g] = fmaxf(gm[g], __shfl_xor(gm[g], 16));
-                    gm[g] = fmaxf(gm[g], __shfl_xor(gm[g], 32));
-                    sbyte[g] = fp8_scale_byte(gm[g]);
-                }
+                for (int g = 0; g < 2; ++g) sbyte[g] = fp8_scale_byte(lane_groups_max(gm[g]));
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     const v4f v = vs[nb];
