@@ -1551,7 +1551,6 @@ int train_run_dense(dl_net *net, const uint16_t *d_frames, int n, int h, int w, 
     const size_t stats = take((size_t)3 * n), lse = take((size_t)train_lse_floats(h, w, ntruth));
     const size_t term = take((size_t)9 * P + 48 * (size_t)n), occ = take((size_t)(P + 3) / 4);
     const size_t part = take((size_t)nblk * wmax), pb = take((size_t)nblk * 32);
-    const size_t tmp = take((size_t)32 * (wmax + 32) + (size_t)32 * (10 * C + 10));
     const size_t gpart = take((size_t)grad_chunks(P) * (10 * C + 10));
     // the U-Net (level 0 points P, level 1 P1, level 2 P2): c0 = [a0, up(u1)],
     // p1 = pool(a0), c1 = [d1, up(d2)], p2 = pool(d1), d2, u1, u0, and their
@@ -1651,66 +1650,77 @@ int train_run_dense(dl_net *net, const uint16_t *d_frames, int n, int h, int w, 
                                   net->z_scale, net->ph_scale, F(maps), F(stats), F(lse), F(gm), d_loss, F(term),
                                   reinterpret_cast<uint8_t *>(net->t_ws + occ), s));
     // backward
-    float *mid = F(tmp);
-    HIPCHK(net, launch_head_backward(C, F(gm), last, prm + o.head_w, n, h, w, grd + o.head_w, F(gpart), mid, F(gtp),
+    HIPCHK(net, launch_head_backward(C, F(gm), last, prm + o.head_w, n, h, w, grd + o.head_w, F(gpart), F(gtp),
                                      s));
     if (net->unet) {
         // gtp: u0's pre-activation gradient
         const int nbc = C / 16, nbc2 = C2 / 16;
-        HIPCHK(net, launch_wgrad_ex(C, 9, F(gtp), C, F(c0), C2, C2, n, h, w, 1, F(part), F(pb), mid, grd + o.uw[3],
+        HIPCHK(net, launch_wgrad_ex(C, 9, F(gtp), C, F(c0), C2, C2, n, h, w, 1, F(part), F(pb), grd + o.uw[3],
                                     grd + o.ub[3], s));
         HIPCHK(net, uconv(d_fd, g, nb, F(gtp), C, C, F(gc0), C2, nbc2, pk(pl.utr[3]), nullptr, 0));
         HIPCHK(net, launch_up2_back(F(gc0) + C, C2, F(gu1), C, n, h, w, C, s));
         HIPCHK(net, launch_mask_slice(F(gu1), C, 0, F(u1), C, 0, C, P1, F(gu1), C, s));
-        HIPCHK(net, launch_wgrad_ex(C, 9, F(gu1), C, F(c1), C2, C2, n, h1, w1, 1, F(part), F(pb), mid, grd + o.uw[2],
+        HIPCHK(net, launch_wgrad_ex(C, 9, F(gu1), C, F(c1), C2, C2, n, h1, w1, 1, F(part), F(pb), grd + o.uw[2],
                                     grd + o.ub[2], s));
         HIPCHK(net, uconv(fd1, g1, 0, F(gu1), C, C, F(gc1), C2, nbc2, pk(pl.utr[2]), nullptr, 0));
         HIPCHK(net, launch_up2_back(F(gc1) + C, C2, F(gd2), C, n, h1, w1, C, s));
         HIPCHK(net, launch_mask_slice(F(gd2), C, 0, F(d2), C, 0, C, P2, F(gd2), C, s));
-        HIPCHK(net, launch_wgrad_ex(C, 9, F(gd2), C, F(p2), C, C, n, h2, w2, 1, F(part), F(pb), mid, grd + o.uw[1],
+        HIPCHK(net, launch_wgrad_ex(C, 9, F(gd2), C, F(p2), C, C, n, h2, w2, 1, F(part), F(pb), grd + o.uw[1],
                                     grd + o.ub[1], s));
         HIPCHK(net, uconv(fd2, g2, 0, F(gd2), C, C, F(gp2), C, nbc, pk(pl.utr[1]), nullptr, 0));
         // d1's output gradient: from u1 (gc1's first C channels) and through the pooling from d2
         HIPCHK(net, launch_pool2_back(F(c1), C2, F(gp2), C, F(gc1), C2, n, h1, w1, C, s));
         HIPCHK(net, launch_mask_slice(F(gc1), C2, 0, F(c1), C2, 0, C, P1, F(gd1), C, s));
-        HIPCHK(net, launch_wgrad_ex(C, 9, F(gd1), C, F(p1), C, C, n, h1, w1, 1, F(part), F(pb), mid, grd + o.uw[0],
+        HIPCHK(net, launch_wgrad_ex(C, 9, F(gd1), C, F(p1), C, C, n, h1, w1, 1, F(part), F(pb), grd + o.uw[0],
                                     grd + o.ub[0], s));
         HIPCHK(net, uconv(fd1, g1, 0, F(gd1), C, C, F(gp1), C, nbc, pk(pl.utr[0]), nullptr, 0));
         // a0's gradient: from u0 (gc0's first C channels) and through the pooling from d1
         HIPCHK(net, launch_pool2_back(F(c0), C2, F(gp1), C, F(gc0), C2, n, h, w, C, s));
     }
     for (int b = nb - 1; b >= 0; --b) {
-        if (b + 1 < nb)   // the next block's input gradient, where this block's transition was on
-            HIPCHK(net, launch_mask_slice(F(ga), CT, 0, F(A[b + 1]), CT, 0, C, P, F(gtp), C, s));
-        else if (net->unet)   // the U-Net's input gradient, where the last transition was on
+        // gtp: the block's output gradient, where its transition was on (the blocks
+        // before the last: left there by the block after, see below)
+        if (b + 1 == nb && net->unet)
             HIPCHK(net, launch_mask_slice(F(gc0), C2, 0, F(c0), C2, 0, C, P, F(gtp), C, s));
         // the transition: weight gradient (16-row pieces when CT is not a multiple of C), input gradient
         if (CT % C == 0) {
-            HIPCHK(net, launch_wgrad_ex(C, 1, F(gtp), C, F(A[b]), CT, CT, n, h, w, 1, F(part), F(pb), mid,
+            HIPCHK(net, launch_wgrad_ex(C, 1, F(gtp), C, F(A[b]), CT, CT, n, h, w, 1, F(part), F(pb),
                                         grd + o.tw[b], grd + o.tb[b], s));
         } else {
             for (int r = 0; r < C; r += 16)
-                HIPCHK(net, launch_wgrad_ex(16, 1, F(gtp) + r, C, F(A[b]), CT, CT, n, h, w, 1, F(part), F(pb), mid,
+                HIPCHK(net, launch_wgrad_ex(16, 1, F(gtp) + r, C, F(A[b]), CT, CT, n, h, w, 1, F(part), F(pb),
                                             grd + o.tw[b] + (size_t)r * CT, grd + o.tb[b] + r, s));
         }
         HIPCHK(net, launch_1x1_back(C, F(gtp), prm + o.tw[b], CT, P, F(ga), s));
+        // Layer i's output gradient, masked where its ReLU was off, in gl (i even) or
+        // gtp (odd): the last layer's by a pass of its own, the others' by the
+        // transposed convolution of the layer after, which adds their last term
+        // (4.7 us less a layer than a pass each at 8 x 128^2); so is the block's
+        // input's, C channels in gtp.
         for (int i = L - 1; i >= 0; --i) {
             const size_t li = (size_t)b * L + i;
             const int lo = C + i * G;
-            HIPCHK(net, launch_mask_slice(F(ga), CT, lo, F(A[b]), CT, lo, G, P, F(gl), G, s));
-            HIPCHK(net, launch_wgrad_ex(G, 9, F(gl), G, F(A[b]), CT, lo, n, h, w, net->dil[b], F(part), F(pb), mid,
+            float *gi = F(i % 2 ? gtp : gl);
+            if (i == L - 1) HIPCHK(net, launch_mask_slice(F(ga), CT, lo, F(A[b]), CT, lo, G, P, gi, G, s));
+            HIPCHK(net, launch_wgrad_ex(G, 9, gi, G, F(A[b]), CT, lo, n, h, w, net->dil[b], F(part), F(pb),
                                         grd + o.lw[li], grd + o.lb[li], s));
             for (int job : pl.tr[li]) {
                 const PackJob &J = pl.jobs[job];
-                DenseConvArgs a = conv(b, F(gl), G, G, F(ga), CT, J.row0, pk(job), nullptr, F(ga) + J.row0, 0);
+                DenseConvArgs a = conv(b, gi, G, G, F(ga), CT, J.row0, pk(job), nullptr, F(ga) + J.row0, 0);
+                if (J.row0 + J.nrows == lo) {
+                    const int ch = i ? lo - G : 0;               // first channel that is complete with this
+                    a.mask = F(A[b]) + ch;
+                    a.mcs = CT;
+                    a.mask0 = (ch - J.row0) / 16;
+                    a.masked = F(i % 2 ? gl : gtp);
+                    a.mdcs = i ? G : C;
+                }
                 HIPCHK(net, launch_dconv_train(J.nrows / 16, a, g, net->ncu, s));
             }
         }
     }
-    // the stem: its output's gradient where its ReLU was on
-    HIPCHK(net, launch_mask_slice(F(ga), CT, 0, F(A[0]), CT, 0, C, P, F(gtp), C, s));
-    HIPCHK(net, launch_stem_grad(F(gtp), d_frames, n, h, w, net->cfg.offset, scale, C, grd + o.stem_w, F(gpart), mid,
-                                 s));
+    // the stem: its output's gradient where its ReLU was on is in gtp
+    HIPCHK(net, launch_stem_grad(F(gtp), d_frames, n, h, w, net->cfg.offset, scale, C, grd + o.stem_w, F(gpart), s));
     HIPCHK(net, hipEventRecord(net->desc_ev[slot], s));
     return DL_OK;
 }
@@ -1739,7 +1749,6 @@ int train_run(dl_net *net, const uint16_t *d_frames, int n, int h, int w, const 
     const size_t stats = take((size_t)3 * n), lse = take((size_t)train_lse_floats(h, w, ntruth));
     const size_t term = take((size_t)9 * P + 48 * (size_t)n), occ = take((size_t)(P + 3) / 4);
     const size_t part = take((size_t)nblk * 9 * C * C), pb = take((size_t)nblk * C);
-    const size_t tmp = take((size_t)32 * (9 * C * C + C));
     const size_t gpart = take((size_t)grad_chunks(P) * (10 * C + 10));
     if (off > net->t_ws_bytes) {
         HIPCHK(net, hipDeviceSynchronize());
@@ -1793,19 +1802,17 @@ int train_run(dl_net *net, const uint16_t *d_frames, int n, int h, int w, const 
                                   reinterpret_cast<uint8_t *>(net->t_ws + occ), s));
     // backward: du is the gradient at the pre-activation of block b's output
     float *du = F(g0), *dn = F(g1);
-    HIPCHK(net, launch_head_backward(C, F(gm), F(act[nb]), prm + o.head_w, n, h, w, grd + o.head_w, F(gpart),
-                                     F(tmp) + 9 * C * C, du, s));
+    HIPCHK(net, launch_head_backward(C, F(gm), F(act[nb]), prm + o.head_w, n, h, w, grd + o.head_w, F(gpart), du, s));
     for (int b = nb - 1; b >= 0; --b) {
-        HIPCHK(net, launch_wgrad(C, du, F(T[b]), n, h, w, net->dil[b], F(part), F(pb), F(tmp), grd + o.w2[b],
+        HIPCHK(net, launch_wgrad(C, du, F(T[b]), n, h, w, net->dil[b], F(part), F(pb), grd + o.w2[b],
                                  grd + o.b2[b], s));
         HIPCHK(net, conv(b, 1, 1, du, F(dsb), nullptr, nullptr, F(T[b]), 0));            // ds
-        HIPCHK(net, launch_wgrad(C, F(dsb), F(act[b]), n, h, w, net->dil[b], F(part), F(pb), F(tmp), grd + o.w1[b],
+        HIPCHK(net, launch_wgrad(C, F(dsb), F(act[b]), n, h, w, net->dil[b], F(part), F(pb), grd + o.w1[b],
                                  grd + o.b1[b], s));
         HIPCHK(net, conv(b, 0, 1, F(dsb), dn, nullptr, du, F(act[b]), 0));              // (du + W1^T ds) at a_b > 0
         std::swap(du, dn);
     }
-    HIPCHK(net, launch_stem_grad(du, d_frames, n, h, w, net->cfg.offset, scale, C, grd + o.stem_w, F(gpart),
-                                 F(tmp) + 9 * C * C, s));
+    HIPCHK(net, launch_stem_grad(du, d_frames, n, h, w, net->cfg.offset, scale, C, grd + o.stem_w, F(gpart), s));
     HIPCHK(net, hipEventRecord(net->desc_ev[slot], s));
     return DL_OK;
 }

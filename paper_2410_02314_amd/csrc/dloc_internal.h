@@ -302,9 +302,13 @@ struct DenseConvArgs {
     float *tout;
     int cst;
     // res (points of rcs floats) is added before the optional ReLU; where mask
-    // (points of mcs floats) is <= 0 the output is 0
+    // (points of mcs floats) is <= 0 the output is 0.  The mask covers the output
+    // blocks from mask0 on; with `masked` those go there (from channel 0 of points
+    // of mdcs floats) and not to out.
     const float *res, *mask;
-    int rcs, mcs, relu;
+    int rcs, mcs, relu, mask0;
+    float *masked;
+    int mdcs;
 };
 int dense_tile_rows();
 int dense_tile_cols();
@@ -368,21 +372,20 @@ hipError_t launch_train_loss(int C, const float *act, const float *hw, const flo
                              hipStream_t s);
 // head weight/bias gradients (gwb: head.w then head.b) and the gradient at the
 // last block's pre-activation; part: grad_chunks(n h w) x (10 C + 10) floats,
-// mid: 32 x (10 C + 10)
 int grad_chunks(int64_t npx);
 hipError_t launch_head_backward(int C, const float *gm, const float *act, const float *hw, int n, int h, int w,
-                                float *gwb, float *part, float *mid, float *du, hipStream_t s);
+                                float *gwb, float *part, float *du, hipStream_t s);
 // 3x3 weight and bias gradients; part holds nblk x 9 C^2 floats and pb nblk C,
-// nblk = ceil(n h / wgrad_rows_per_block(n, h)); tmp 32 x (9 C^2 + C)
+// nblk = ceil(n h / wgrad_rows_per_block(n, h))
 int wgrad_rows_per_block(int n, int h);
 hipError_t launch_wgrad(int C, const float *dy, const float *x, int n, int h, int w, int d, float *part, float *pb,
-                        float *tmp, float *gW, float *gb, hipStream_t s);
+                        float *gW, float *gb, hipStream_t s);
 // the same for CO (16 or 32) outputs over CI inputs (a multiple of CO) of a
 // 3x3 (taps 9) or 1x1 (taps 1) conv; dy points of dcs floats, x points of xcs
 // floats (channels 0 .. CI-1); gW [CO][CI][taps]; part nblk x CO CI taps, pb
-// nblk CO, tmp 32 x (CO CI taps + CO)
+// nblk CO
 hipError_t launch_wgrad_ex(int CO, int taps, const float *dy, int dcs, const float *x, int xcs, int CI, int n, int h,
-                           int w, int d, float *part, float *pb, float *tmp, float *gW, float *gb, hipStream_t s);
+                           int w, int d, float *part, float *pb, float *gW, float *gb, hipStream_t s);
 // one weight pack: the conv at params + src ([cout][cin][taps]), or (flip) its
 // transposed convolution, rows row0 .. row0 + nrows - 1 (a multiple of 16),
 // into dst .. in the conv kernel's layout; start: the job's first element in
@@ -410,7 +413,7 @@ hipError_t launch_up2_back(const float *g, int gcs, float *out, int ocs, int n, 
 hipError_t launch_1x1_back(int C, const float *g, const float *Wt, int ct, int64_t npx, float *out, hipStream_t s);
 // stem weight/bias gradients (gwb: stem.w then stem.b); part: grad_chunks(n h w) x 10 C
 hipError_t launch_stem_grad(const float *ds, const uint16_t *frames, int n, int h, int w, float offset, float scale,
-                            int C, float *gwb, float *part, float *mid, hipStream_t s);
+                            int C, float *gwb, float *part, hipStream_t s);
 
 // one dense layer (see DenseConvArgs),
 // nb_out 1 .. 5 blocks of 16 outputs

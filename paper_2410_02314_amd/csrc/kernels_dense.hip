@@ -259,8 +259,9 @@ k_dconv(DenseConvArgs a, Geometry geo)
                 const int c0 = nb * 16 + 4 * kq;
                 const v4f rv = a.res && inside ? *reinterpret_cast<const v4f *>(a.res + pt * a.rcs + c0)
                                                : v4f{0.f, 0.f, 0.f, 0.f};
-                const v4f mv = a.mask && inside ? *reinterpret_cast<const v4f *>(a.mask + pt * a.mcs + c0)
-                                                : v4f{1.f, 1.f, 1.f, 1.f};
+                const v4f mv = a.mask && nb >= a.mask0 && inside
+                                   ? *reinterpret_cast<const v4f *>(a.mask + pt * a.mcs + c0 - 16 * a.mask0)
+                                   : v4f{1.f, 1.f, 1.f, 1.f};
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float v = acc[nb][p][r] + sB[c0 + r] + rv[r];
@@ -271,7 +272,10 @@ k_dconv(DenseConvArgs a, Geometry geo)
             if (inside) {
                 float *op = a.out + pt * a.cso + a.co;
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<v4f *>(op + nb * 16 + 4 * kq) = o[nb];
+                for (int nb = 0; nb < NB; ++nb) {
+                    float *q = a.masked && nb >= a.mask0 ? a.masked + pt * a.mdcs - 16 * a.mask0 : op;
+                    *reinterpret_cast<v4f *>(q + nb * 16 + 4 * kq) = o[nb];
+                }
             }
             if constexpr (TR) {
                 // the layer's outputs are the transition's last K groups: in the

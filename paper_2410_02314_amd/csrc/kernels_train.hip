@@ -867,9 +867,12 @@ k_wgrad(const float *__restrict__ dy, int dcs, const float *__restrict__ x, int 
 }
 
 // Sums over nb partials of two arrays at once (ma values of pa and mb of pb
-// per partial), in two fixed-order stages: groups of G = ceil(nb / ng)
-// partials into mid[g][ma + mb], then the ng groups into oa and ob.  Each
-// thread adds its terms in order, eight loads in flight at a time.
+// per partial), in a fixed order: ng = min(32, nb) groups of ceil(nb / ng)
+// partials, a thread each, then the groups' sums by one thread per value from
+// LDS.  A workgroup takes 16 values (64 bytes of a partial).  One launch: as two,
+// with the groups' sums through memory, the pair took 9.4 us of which the second
+// launch was half.  Each thread adds its terms in order, eight loads in flight at
+// a time.
 __device__ __forceinline__ float ordered_sum(const float *__restrict__ src, size_t stride, int cnt)
 {
     float s = 0.f;
@@ -885,28 +888,22 @@ __device__ __forceinline__ float ordered_sum(const float *__restrict__ src, size
     return s;
 }
 
-__global__ void __launch_bounds__(256)
-k_sum_partials_grouped(const float *__restrict__ pa, int ma, const float *__restrict__ pbb, int mb, int nb, int ng,
-                       float *__restrict__ mid)
+__global__ void __launch_bounds__(512)
+k_sum_partials(const float *__restrict__ pa, int ma, const float *__restrict__ pbb, int mb, int nb, int ng,
+               float *__restrict__ oa, float *__restrict__ ob)
 {
-    const int m = ma + mb;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)ng * m) return;
-    const int g = (int)(idx / m), j = (int)(idx - (int64_t)g * m);
-    const int G = (nb + ng - 1) / ng;
-    const int b0 = g * G, b1 = min(nb, b0 + G);
-    const int stride = j < ma ? ma : mb;
-    const float *src = (j < ma ? pa + j : pbb + (j - ma)) + (size_t)b0 * stride;
-    mid[idx] = ordered_sum(src, stride, b1 - b0);
-}
-
-__global__ void __launch_bounds__(256)
-k_sum_partials(const float *__restrict__ mid, int ng, int ma, int mb, float *__restrict__ oa, float *__restrict__ ob)
-{
-    const int m = ma + mb;
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= m) return;
-    const float s = ordered_sum(mid + j, m, ng);
+    __shared__ float sums[32][16];
+    const int jl = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const int j = blockIdx.x * 16 + jl, m = ma + mb;
+    if (j < m && g < ng) {
+        const int G = (nb + ng - 1) / ng;
+        const int b0 = g * G, b1 = min(nb, b0 + G);
+        const int stride = j < ma ? ma : mb;
+        sums[g][jl] = ordered_sum((j < ma ? pa + j : pbb + (j - ma)) + (size_t)b0 * stride, stride, b1 - b0);
+    }
+    __syncthreads();
+    if (g > 0 || j >= m) return;
+    const float s = ordered_sum(&sums[0][jl], 16, ng);
     if (j < ma) oa[j] = s;
     else ob[j - ma] = s;
 }
@@ -956,15 +953,11 @@ k_stem_grad_part(const float *__restrict__ ds, const uint16_t *__restrict__ fram
     }
 }
 
-// the sums over nb partials of ma values (into oa) and mb values (into ob) in
-// two fixed-order stages; mid holds 32 (ma + mb) floats
-void reduce_partials(const float *pa, int ma, float *oa, const float *pbb, int mb, float *ob, int nb, float *mid,
-                     hipStream_t s)
+// the sums over nb partials of ma values (into oa) and mb values (into ob)
+void reduce_partials(const float *pa, int ma, float *oa, const float *pbb, int mb, float *ob, int nb, hipStream_t s)
 {
-    const int ng = std::min(32, nb), m = ma + mb;
-    hipLaunchKernelGGL(k_sum_partials_grouped, dim3((unsigned)(((int64_t)ng * m + 255) / 256)), dim3(256), 0, s, pa,
-                       ma, pbb, mb, nb, ng, mid);
-    hipLaunchKernelGGL(k_sum_partials, dim3((m + 255) / 256), dim3(256), 0, s, mid, ng, ma, mb, oa, ob);
+    hipLaunchKernelGGL(k_sum_partials, dim3((ma + mb + 15) / 16), dim3(512), 0, s, pa, ma, pbb, mb, nb,
+                       std::min(32, nb), oa, ob);
 }
 
 }  // namespace
@@ -1074,7 +1067,7 @@ hipError_t launch_train_loss(int C, const float *act, const float *hw, const flo
 int grad_chunks(int64_t npx) { return (int)((npx + GCHUNK - 1) / GCHUNK); }
 
 hipError_t launch_head_backward(int C, const float *gm, const float *act, const float *hw, int n, int h, int w,
-                                float *gwb, float *part, float *mid, float *du, hipStream_t s)
+                                float *gwb, float *part, float *du, hipStream_t s)
 {
     const int64_t hwpx = (int64_t)h * w, npx = (int64_t)n * hwpx;
     const int nb = grad_chunks(npx);
@@ -1089,7 +1082,7 @@ hipError_t launch_head_backward(int C, const float *gm, const float *act, const 
     } else {
         return hipErrorInvalidValue;
     }
-    reduce_partials(part, 10 * C + 10, gwb, nullptr, 0, nullptr, nb, mid, s);   // head.w then head.b, as in the blob
+    reduce_partials(part, 10 * C + 10, gwb, nullptr, 0, nullptr, nb, s);   // head.w then head.b, as in the blob
     return hipGetLastError();
 }
 
@@ -1100,7 +1093,7 @@ hipError_t launch_head_backward(int C, const float *gm, const float *act, const 
 int wgrad_rows_per_block(int n, int h) { return WG_WAVES * std::max(1, (n * h + 2047) / 2048); }
 
 hipError_t launch_wgrad_ex(int CO, int taps, const float *dy, int dcs, const float *x, int xcs, int CI, int n, int h,
-                           int w, int d, float *part, float *pb, float *tmp, float *gW, float *gb, hipStream_t s)
+                           int w, int d, float *part, float *pb, float *gW, float *gb, hipStream_t s)
 {
     if (!(CO == 16 || CO == 32) || !(taps == 1 || taps == 9) || CI < CO || CI % CO || d < 1) return hipErrorInvalidValue;
     // the kernel's chains (see k_wgrad); their waves are spread over at most
@@ -1129,18 +1122,18 @@ hipError_t launch_wgrad_ex(int CO, int taps, const float *dy, int dcs, const flo
     else
         hipLaunchKernelGGL((k_wgrad<16, 1>), grid, dim3(64 * WG_WAVES), 0, s, dy, dcs, x, xcs, CI, n, h, w, d, nseg,
                            sps, cpw, part, pb);
-    reduce_partials(part, CO * CI * taps, gW, pb, CO, gb, (int)grid.x, tmp, s);
+    reduce_partials(part, CO * CI * taps, gW, pb, CO, gb, (int)grid.x, s);
     return hipGetLastError();
 }
 
 hipError_t launch_wgrad(int C, const float *dy, const float *x, int n, int h, int w, int d, float *part, float *pb,
-                        float *tmp, float *gW, float *gb, hipStream_t s)
+                        float *gW, float *gb, hipStream_t s)
 {
-    return launch_wgrad_ex(C, 9, dy, C, x, C, C, n, h, w, d, part, pb, tmp, gW, gb, s);
+    return launch_wgrad_ex(C, 9, dy, C, x, C, C, n, h, w, d, part, pb, gW, gb, s);
 }
 
 hipError_t launch_stem_grad(const float *ds, const uint16_t *frames, int n, int h, int w, float offset, float scale,
-                            int C, float *gwb, float *part, float *mid, hipStream_t s)
+                            int C, float *gwb, float *part, hipStream_t s)
 {
     const int nb = grad_chunks((int64_t)n * h * w);
     if (C == 32)
@@ -1149,7 +1142,7 @@ hipError_t launch_stem_grad(const float *ds, const uint16_t *frames, int n, int 
         hipLaunchKernelGGL(k_stem_grad_part<16>, dim3(nb), dim3(256), 0, s, ds, frames, n, h, w, offset, scale, part);
     else
         return hipErrorInvalidValue;
-    reduce_partials(part, 10 * C, gwb, nullptr, 0, nullptr, nb, mid, s);   // stem.w then stem.b, as in the blob
+    reduce_partials(part, 10 * C, gwb, nullptr, 0, nullptr, nb, s);   // stem.w then stem.b, as in the blob
     return hipGetLastError();
 }
 
