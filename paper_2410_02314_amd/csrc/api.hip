@@ -7,7 +7,7 @@
 //   (last one with the 1x1 head fused, writing the 5 planar maps) ->
 //   detect (threshold + 3x3 local max, 64-bit masks + per-row counts) ->
 //   scan (row offsets, per-frame counts) -> emit (ordered records).
-#include "dloc_internal.h"
+#include "conv_common.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -1014,6 +1014,26 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
         a.res = nullptr;
         a.wpk = static_cast<char *>(net->d_wpk) + (size_t)(b * 2) * net->wpk_stride;
         a.bias = net->d_bias + (size_t)(b * 2) * C;
+        if (!lists && block_takes(C, net->cfg.precision, g.trb[b], g.tiles[b], net->ncu)) {       // both layers in one kernel
+            BlockArgs ba{};
+            ba.w1 = a.wpk;
+            ba.b1 = a.bias;
+            a.wpk = static_cast<char *>(net->d_wpk) + (size_t)(b * 2 + 1) * net->wpk_stride;
+            a.bias = net->d_bias + (size_t)(b * 2 + 1) * C;
+            a.out = xn;
+            a.out_shift = __builtin_ctz((unsigned)lay_next);
+            if (b == net->nb - 1) {
+                a.head = net->d_head;
+                a.maps = maps;
+                a.nh = net->nh;
+                a.out = nullptr;
+            }
+            ba.c = a;
+            StageTimer t(net, b == net->nb - 1 ? DL_STAGE_CONV_HEAD : DL_STAGE_CONV, s);
+            HIPCHK(net, launch_block(C, ba, g, net->ncu, s));
+            std::swap(x, xn);
+            continue;
+        }
         if (lists) {
             a.list = lists + (size_t)(2 * b) * g.max_tiles;
             a.list_count = lcount + 2 * b;

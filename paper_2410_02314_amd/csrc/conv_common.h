@@ -197,4 +197,13 @@ void split_pack_weights(int C, const float *W, void *dst, float *scale);
 int split_max_grid(int C, int tr, int ncu);
 hipError_t launch_split(int C, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s);
 
+// ---- a residual block's two BF16 layers in one kernel (kernels_block.hip) ----
+struct BlockArgs {
+    ConvArgs c;              // the second layer's; in: the block's input, which is also the residual
+    const void *w1;          // the first layer's packed weights and bias
+    const float *b1;
+};
+bool block_takes(int C, int precision, int tr, int64_t tiles, int ncu);
+hipError_t launch_block(int C, const BlockArgs &a, const Geometry &g, int ncu, hipStream_t s);
+
 }  // namespace dloc
