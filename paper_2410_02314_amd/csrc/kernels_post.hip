@@ -183,15 +183,17 @@ hipError_t stem_c(const FrameDesc *fd, const Geometry &g, const float *w, const 
 // two halo rows aside), with no LDS staging and no barrier until the per-row
 // counts are summed.  Neighbours off the frame or in a gate tile that was
 // skipped are -inf (absent).  The row's count goes to row_counts for the scan.
-constexpr int DBAND = 8, DROWS = DBAND + 2;
+// Bands of 8 rows read the two halo rows least often; where they are fewer than
+// the CUs, bands of 2 (launch_detect_mask).
 
 // GATED: keep is a gate keep map; SIGMA: the uncertainty filter is on
-template <bool GATED, bool SIGMA>
+template <int DBAND, bool GATED, bool SIGMA>
 __global__ void __launch_bounds__(256)
 k_detect_mask(const float *__restrict__ maps, int planes, const FrameDesc *__restrict__ fdp, int bands,
               const int64_t *__restrict__ dyn, float tau, float u_max, const uint8_t *__restrict__ keep,
               uint64_t *__restrict__ mask, uint32_t *__restrict__ row_counts)
 {
+    constexpr int DROWS = DBAND + 2;
     __shared__ uint32_t wcnt[DBAND][4];
     // workgroup = (frame, band): bands per frame from the batch's tallest frame
     const int f = blockIdx.x / bands, band = blockIdx.x - f * bands;
@@ -626,12 +628,20 @@ hipError_t launch_detect_mask(const float *maps, int planes, const FrameDesc *fd
                               float u_max, const uint8_t *keep, uint64_t *mask, uint32_t *row_counts,
                               hipStream_t s)
 {
-    const int bands = (g.maxh + DBAND - 1) / DBAND;
+    // bands of 8 rows, or of 2 while those of 8 are fewer than half the CUs: the
+    // rows of a band are one wave's chain (4 x 128^2, 64 bands of 8: 8.5 us, 256
+    // bands of 2: 4.4)
+    const int64_t blocks8 = (int64_t)((g.maxh + 7) / 8) * g.nf;
+    const int band = blocks8 <= 128 ? 2 : 8, bands = (g.maxh + band - 1) / band;
     const int64_t blocks = (int64_t)bands * g.nf;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const bool sigma = planes == 10 && u_max < INFINITY;
-    auto kern = keep ? (sigma ? k_detect_mask<true, true> : k_detect_mask<true, false>)
-                     : (sigma ? k_detect_mask<false, true> : k_detect_mask<false, false>);
+    auto pick = [&](auto db) {
+        constexpr int DB = decltype(db)::value;
+        return keep ? (sigma ? k_detect_mask<DB, true, true> : k_detect_mask<DB, true, false>)
+                    : (sigma ? k_detect_mask<DB, false, true> : k_detect_mask<DB, false, false>);
+    };
+    auto kern = band == 2 ? pick(std::integral_constant<int, 2>{}) : pick(std::integral_constant<int, 8>{});
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, maps, planes, fd, bands, g.dyn, tau, u_max, keep,
                        mask, row_counts);
     return hipGetLastError();
