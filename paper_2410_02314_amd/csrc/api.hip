@@ -246,6 +246,7 @@ int check_dense_config(dl_net *net, const dl_config *c)
     return DL_OK;
 }
 
+bool gated_run(const dl_net *net) { return (net->cfg.flags & DL_FLAG_GATE) && net->gate_set; }
 int tile_rows_of(const dl_net *net) { return net->cfg.tile_rows ? net->cfg.tile_rows : 0; }
 
 // The conv tiling of a batch: the form's tile (its default rows in g.tr), each
@@ -297,6 +298,24 @@ bool frame_act_fits(const dl_net *net, int h, int w)
     return frame_act_points(net, h, w) * net->C * esz < ((int64_t)1 << 31);
 }
 
+// Rows of the FP32 pair kernels' tiles where neither the config nor the autotuner
+// chose them: 4 instead of 8 while a block's tiles of 8 rows are at most one and a
+// half per CU.  A pass is then a chain of tiles one after another, and a tile of
+// half the size takes less of it (net A: 64^2 82 -> 71 us, 300^2 with 380 tiles
+// 140 -> 123 us; 4 x 256^2 with 1024: 184 -> 188 us).  Not at 48 channels, whose
+// tile of 4 rows costs as much as one of 8, and not with the gate, whose lists the
+// workspace holds per tile.
+void small_tiles(const dl_net *net, int n, const int *hs, const int *ws_, Geometry &g)
+{
+    if (net->dL || net->cfg.tile_rows || net->C > 32 || !conv_planar(net->C, net->cfg.precision) || gated_run(net)) return;
+    for (int b = 0; b < net->nb; ++b) {
+        if (net->tune_rows[b]) continue;
+        int64_t tiles = 0;
+        for (int f = 0; f < n; ++f) tiles += conv_tiles(hs[f], ws_[f], net->dil[b], g.trb[b], g.tc);
+        if (2 * tiles <= 3 * (int64_t)net->ncu) g.trb[b] = 4;
+    }
+}
+
 // Build the frame descriptors of a uniform batch or a ROI list.
 void build_geometry(const dl_net *net, int n, const int *hs, const int *ws_, const uint16_t *const *data,
                     const int64_t *strides, std::vector<FrameDesc> &fd, Geometry &g)
@@ -306,6 +325,7 @@ void build_geometry(const dl_net *net, int n, const int *hs, const int *ws_, con
     g.nf = n;
     set_tiling(net, g);
     g.minor_blk = net->nb - 1;        // its head writes plain planar maps
+    small_tiles(net, n, hs, ws_, g);
     for (int f = 0; f < n; ++f) {
         FrameDesc &d = fd[f];
         std::memset(&d, 0, sizeof d);
@@ -378,7 +398,6 @@ struct Plan {
     size_t pooled = 0, glog = 0, keep = 0, lists = 0, lcount = 0;
 };
 
-bool gated_run(const dl_net *net) { return (net->cfg.flags & DL_FLAG_GATE) && net->gate_set; }
 
 Plan make_plan(const dl_net *net, const Geometry &g, bool ext_maps)
 {
