@@ -9,8 +9,7 @@ A step is one pass of the whole path over the batch: preprocessing + stem,
 10 dilated convolutions (head fused into the last), detection, scan, emit.
 
 Prints ONE JSON line.  Besides the throughput it reports the roofline of the
-dominant kernel (the 3x3 block convolution: MFMA-bound in FP32, HBM-bound in
-BF16 and FP8) from HIP events recorded around each launch on its stream
+dominant kernel (the 3x3 block convolution, against HBM) from HIP events recorded around each launch on its stream
 during the timed steps, the BF16 and FP8 forms measured on the same frames
 (under "forms", with their speedup over FP32), and the FP64 CPU oracle timed
 on a bounded sample of the same workload, which also scores every form's
@@ -32,8 +31,18 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Mpixel/s frame->emitter list: FP32 vs BF16/FP8/gated at oracle-matched recall"
 PEAKS = {"fp32": 157.3, "bf16": 2500.0, "fp8": 5000.0, "bf16x3": 2500.0}   # dense MFMA TFLOP/s, MI355X
-# BF16 MFMA products per algorithmic product: the split-BF16 form takes three
-MFMA_PER_PRODUCT = {"fp32": 1, "bf16": 1, "fp8": 1, "bf16x3": 3}
+# MFMA products per algorithmic product: the split forms take three, split BF16
+# on the BF16 and FP32 (to 48 channels, and the dense networks) on the FP16
+# matrix cores, whose dense peak is the same
+MFMA_PER_PRODUCT = {"fp32": 3, "bf16": 1, "fp8": 1, "bf16x3": 3}
+FP16_PEAK = 2500.0
+
+
+def inference_peak(precision, C):
+    """(MFMA peak in TFLOP/s, products per algorithmic product) of a conv form."""
+    if precision == "fp32":
+        return (FP16_PEAK, 3) if C <= 48 else (PEAKS["fp32"], 1)
+    return PEAKS[precision], MFMA_PER_PRODUCT[precision]
 HBM_PEAK_GBS = 8000.0
 
 
@@ -221,7 +230,7 @@ def net_text(spec):
 
 def dense_roofline(spec, prof, total_px, steps):
     """Roofline of the dense network's dominant kernel, the plain 3x3 dense
-    layer (k_dconv without fusion: the first L - 1 layers of each block; layer
+    layer (k_dpipe without fusion: the first L - 1 layers of each block; layer
     i reads C + i G channels and writes G, so its FLOP and bytes per pixel grow
     with i); achieved = the mean algorithmic FLOP of those nblocks x (L - 1)
     launches / their mean duration.  Each block's last layer runs fused with
@@ -236,14 +245,15 @@ def dense_roofline(spec, prof, total_px, steps):
     flop_launch = 2.0 * 9 * G * (sum(cins) / len(cins)) * total_px
     bytes_launch = 4.0 * (sum(cins) / len(cins) + G) * total_px
     tflops = flop_launch / avg_s / 1e12
-    roof = {"bound": "mfma", "achieved": round(tflops, 2), "peak": PEAKS["fp32"], "unit": "TFLOP/s",
-            "frac": round(tflops / PEAKS["fp32"], 4),
+    gbs = bytes_launch / avg_s / 1e9
+    peak, products = inference_peak("fp32", C)
+    roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(gbs / HBM_PEAK_GBS, 4), "mfma_frac": round(products * tflops / peak, 4),
             "traffic": measured_traffic(dense_traffic_key(spec, total_px), DENSE_SOURCES),
-            "kernel": f"k_dconv fp32 (3x3 dilated dense layer, growth {G} over {cins[0]}..{cins[-1]} input channels; "
+            "kernel": f"k_dpipe fp32 (3x3 dilated dense layer, growth {G} over {cins[0]}..{cins[-1]} input channels; "
                       f"mean of the {nb * (L - 1)} unfused launches)",
             "avg_launch_ms": round(avg_s * 1e3, 3), "flop_per_launch": flop_launch,
-            "algorithmic_bytes_per_launch": round(bytes_launch),
-            "hbm_gb_s": round(bytes_launch / avg_s / 1e9, 1)}
+            "algorithmic_bytes_per_launch": round(bytes_launch), "tflop_s": round(tflops, 2)}
     # the fused last layers: 3x3 over C + (L - 1) G channels, then the 1x1
     # transition CT -> C (and the head C -> nh in the last block)
     cin = C + (L - 1) * G
@@ -256,14 +266,14 @@ def dense_roofline(spec, prof, total_px, steps):
         if head and spec.unet:       # the U-Net's last conv (2C -> C at level 0) with the head
             tf = (2.0 * 9 * 2 * C * C + 2.0 * C * nh) * total_px
             tb = (4.0 * 2 * C + 4.0 * nh) * total_px
-            name = f"k_dconv fp32 fused (U-Net 3x3 {2 * C} -> {C}, head {C} -> {nh})"
+            name = f"k_dpipe fp32 fused (U-Net 3x3 {2 * C} -> {C}, head {C} -> {nh})"
         else:
             tf = (2.0 * 9 * G * cin + 2.0 * CT * C + (2.0 * C * nh if head else 0.0)) * total_px
             tb = (4.0 * (cin + C) + (4.0 * nh - 4.0 * C if head else 0.0)) * total_px
-            name = (f"k_dconv fp32 fused (3x3 {cin} -> {G}, 1x1 transition {CT} -> {C}"
+            name = (f"k_dpipe fp32 fused (3x3 {cin} -> {G}, 1x1 transition {CT} -> {C}"
                     + (f", head {C} -> {nh})" if head else ")"))
         fused.append({"kernel": name, "launches_per_step": t_n // steps, "avg_launch_ms": round(ts * 1e3, 3),
-                      "tflop_s": round(tf / ts / 1e12, 2), "mfma_frac": round(tf / ts / 1e12 / PEAKS["fp32"], 4),
+                      "tflop_s": round(tf / ts / 1e12, 2), "mfma_frac": round(products * tf / ts / 1e12 / peak, 4),
                       "gb_s": round(tb / ts / 1e9, 1)})
     roof["fused_last_layers"] = fused
     if spec.unet and prof["unet"][1]:
@@ -273,7 +283,7 @@ def dense_roofline(spec, prof, total_px, steps):
 
 
 def dense_traffic_key(spec, total_px):
-    return f"k_dconv fp32 unfused net {spec.name} {total_px}px"
+    return f"k_dpipe fp32 unfused net {spec.name} {total_px}px"
 
 
 def measure_form(args, precision, spec, w, d_frames, dl, torch, dev, cam=None):
@@ -352,26 +362,32 @@ def conv_roofline(args, precision, spec, prof, total_px):
     n, side, C = args.frames, args.size, spec.C
     conv_ms, conv_n = prof["conv"]
     avg_s = conv_ms / conv_n * 1e-3
-    flop_launch = 2.0 * 9 * C * C * total_px
+    nb = len(spec.dilations)
+    n_conv = 2 * nb - 1
+    # BF16 runs a block's two layers as one launch at some sizes: the blocks
+    # before the last, and no launch of a layer alone
+    blocks = conv_n == (nb - 1) * args.steps
+    flop_launch = 2.0 * 9 * C * C * total_px * (2 if blocks else 1)
     tflops = flop_launch / avg_s / 1e12
     # bytes per activation point: FP32 / BF16 values, FP8 codes + 2 group scale bytes
     pt_bytes = {"fp32": 4 * C, "bf16": 2 * C, "fp8": C + 2, "bf16x3": 4 * C}[precision]
     # algorithmic HBM bytes of the mean non-head conv launch: input + output for
     # all nine, + the residual for the four second convolutions of blocks 1-4
-    nb = len(spec.dilations)
-    n_conv = 2 * nb - 1
-    bytes_launch = total_px * pt_bytes * (2 * n_conv + (nb - 1)) / n_conv
+    bytes_launch = total_px * pt_bytes * (2 if blocks else (2 * n_conv + (nb - 1)) / n_conv)
     gbs = bytes_launch / avg_s / 1e9
     key = f"k_conv {precision} C={C} {n}x{side}x{side}"
-    if precision == "fp32":
-        roofline = {"bound": "mfma", "achieved": round(tflops, 2), "peak": PEAKS[precision], "unit": "TFLOP/s",
-                    "frac": round(tflops / PEAKS[precision], 4)}
+    peak, products = inference_peak(precision, C)
+    if products == 1 and precision == "fp32":
+        roofline = {"bound": "mfma", "achieved": round(tflops, 2), "peak": peak, "unit": "TFLOP/s",
+                    "frac": round(tflops / peak, 4)}
     else:
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4),
-                    "mfma_frac": round(MFMA_PER_PRODUCT[precision] * tflops / PEAKS[precision], 4)}
-    roofline.update({"traffic": measured_traffic(key),
-                     "kernel": f"k_conv {precision} (3x3 dilated conv, C={C}; mean of the {n_conv} non-head launches)",
+                    "mfma_frac": round(products * tflops / peak, 4), "tflop_s": round(tflops, 2)}
+    name = "k_block" if blocks else "k_conv" if precision != "fp32" or C > 48 else "k_pipe" if C == 48 else "k_split"
+    roofline.update({"traffic": measured_traffic(key, SPLIT_SOURCES if name in ("k_pipe", "k_split") else CONV_SOURCES),
+                     "kernel": f"{name} {precision} (3x3 dilated conv, C={C}; mean of the "
+                               f"{conv_n // args.steps} non-head launches)",
                      "avg_launch_ms": round(avg_s * 1e3, 3), "flop_per_launch": flop_launch,
                      "algorithmic_bytes_per_launch": round(bytes_launch)})
     return roofline, pt_bytes
@@ -441,8 +457,9 @@ def map_errors_on_sample(net, d_frames, ref, torch, dev):
             "map_region": f"{e}x{e}"}
 
 
-CONV_SOURCES = ("kernels_conv.hip", "dloc_internal.h")
-DENSE_SOURCES = ("kernels_dense.hip", "dloc_internal.h")
+CONV_SOURCES = ("kernels_conv.hip", "conv_common.h", "dloc_internal.h")
+SPLIT_SOURCES = ("kernels_split.hip", "split_common.h", "conv_common.h", "dloc_internal.h")
+DENSE_SOURCES = ("kernels_dsplit.hip", "split_common.h", "conv_common.h", "dloc_internal.h")
 
 
 def conv_source_sha256(sources=CONV_SOURCES):

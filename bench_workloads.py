@@ -13,7 +13,7 @@ import time
 
 import numpy as np
 
-from bench import METRIC, PEAKS, cpu_threads, log
+from bench import METRIC, PEAKS, cpu_threads, inference_peak, log
 
 
 def _timed(fn, steps, warmup, stream):
@@ -157,6 +157,9 @@ def rois(args, S):
         flop = 2.0 * 9 * spec.growth * (sum(cins) / len(cins)) * px
     else:
         flop = 2.0 * 9 * spec.C * spec.C * px
+        if conv_n == (len(spec.dilations) - 1) * prof["conv_head"][1]:
+            flop *= 2                                     # BF16: a block's two layers in one launch
+    peak, products = inference_peak(args.precision, spec.C)
     ach = flop / (conv_ms / conv_n * 1e-3) / 1e12
     # load balance: the same net on a uniform batch of about the same pixel
     # count (16 x 2048^2 frames of the same emitter model) in one launch per layer
@@ -177,8 +180,9 @@ def rois(args, S):
            "tile_schedules": schedules,
            "emitters_per_step": int(counts[256].item()),
            "uniform_16x2048sq_mpx_s": round(mpx_uni, 2), "load_balance_efficiency": round(mpx / mpx_uni, 4),
-           "roofline": {"bound": "mfma", "achieved": round(ach, 2), "peak": PEAKS[args.precision],
-                        "unit": "TFLOP/s", "frac": round(ach / PEAKS[args.precision], 4), "traffic": None}})
+           "roofline": {"bound": "mfma", "achieved": round(products * ach, 2), "peak": peak,
+                        "unit": "TFLOP/s", "frac": round(products * ach / peak, 4), "traffic": None,
+                        "algorithmic_tflop_s": round(ach, 2)}})
 
 
 def sparse(args, S):

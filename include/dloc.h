@@ -60,7 +60,10 @@ typedef enum {
 
 /* Arithmetic of the 3x3 block convolutions (preprocessing, stem, head,
  * sigmoid and detection are FP32 in every form):
- *   DL_FP32  FP32 weights, activations and accumulation (the exact form);
+ *   DL_FP32  FP32 weights, activations and accumulation (the exact form; to
+ *            48 channels a product is taken on the FP16 matrix cores from
+ *            pairs of halves, 22 bits each: nearer to the exact sums than
+ *            FP32 products added one by one);
  *   DL_BF16  BF16 weights and stored activations (round to nearest even),
  *            FP32 accumulation, bias, residual and ReLU;
  *   DL_FP8   OCP e4m3 weights with one scale per output channel, and stored
