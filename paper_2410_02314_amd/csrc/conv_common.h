@@ -32,6 +32,63 @@ __device__ __forceinline__ v4f relu4(v4f v)
     return r;
 }
 
+// largest v (>= 0) of the four lanes j, j + 16, j + 32, j + 48, in each of them
+// (register swaps between lane rows, where ds_bpermute would go through LDS)
+__device__ __forceinline__ float lane_groups_max(float v)
+{
+    const int x = __float_as_int(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const int y = max((int)a[0], (int)a[1]);       // non-negative floats order as integers
+    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return __int_as_float(max((int)b[0], (int)b[1]));
+}
+
+// ... and the sum, in the order (own + the lane group beside it) + the other two
+__device__ __forceinline__ float lane_groups_sum(float v)
+{
+    const int x = __float_as_int(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const int y = __float_as_int(__int_as_float((int)a[0]) + __int_as_float((int)a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return __int_as_float((int)b[0]) + __int_as_float((int)b[1]);
+}
+
+// The fused 1x1 head (NH outputs of C channels, weights sH [NH][C]) over a wave's
+// N pixel blocks, channel block by channel block: channels oc .. oc + 3 of the
+// blocks' pixels into their sums.  The weights are read from LDS once for all N
+// blocks (once per block, and with the lane sums through ds_bpermute, the head's
+// layer of net B took, 4 x 2048^2: FP8 1008 us, now 926; BF16 1213, now 1184;
+// FP32 2640, now 2574).
+// head_blocks: how many of N blocks at a time keep the sums in registers (ten
+// outputs, or 64 channels' accumulators, leave room for one).
+template <int NH, int C> constexpr int head_blocks(int N) { return (NH > 5 || C > 48) && C > 16 ? 1 : N; }
+template <int NH, int C, int N>
+__device__ __forceinline__ void head_add(float (&hh)[N][NH], const float *sH, int oc, const v4f (&v)[N])
+{
+    v4f w[NH];
+#pragma unroll
+    for (int q = 0; q < NH; ++q) w[q] = *reinterpret_cast<const v4f *>(sH + q * C + oc);
+#pragma unroll
+    for (int p = 0; p < N; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int q = 0; q < NH; ++q) hh[p][q] += w[q][r] * v[p][r];
+}
+// The four lane groups hold disjoint channels of the pixel; group kq writes
+// planes kq, kq + 4, kq + 8 (mp: the pixel in plane 0).
+template <int NH>
+__device__ __forceinline__ void head_store(float (&h)[NH], const float *bias, float *mp, int64_t plane, int kq, bool ok)
+{
+#pragma unroll
+    for (int q = 0; q < NH; ++q) h[q] = lane_groups_sum(h[q]);
+    if (ok) {
+#pragma unroll
+        for (int q = 0; q < NH; ++q)
+            if ((q & 3) == kq) mp[q * plane] = h[q] + bias[q];
+    }
+}
+
 // a decoded tile: origin (y0, x0) and size of its frame, where its input
 // sits (point (ii, jj) of the tile is activation point a0 + ii rs + jj cs of
 // the frame), and the frame's map and activation offsets

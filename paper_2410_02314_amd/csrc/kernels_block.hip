@@ -285,49 +285,43 @@ k_block(BlockArgs a, Geometry geo)
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
+        auto value = [&](int p, int nb, const uint2 &u) {     // what is stored, as BF16 pairs
+            v4f v = acc[p][nb] + *reinterpret_cast<const v4f *>(sB2 + nb * 16 + kq * 4);
+            v += v4f{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
+                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u)};
+            v = relu4(v);
+            return uint2{bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3])};
+        };
+        if constexpr (HEAD) {
+            constexpr int N = head_blocks<NH, C>(PB);
 #pragma unroll
-        for (int p = 0; p < PB; ++p) {
-            const int xo = X0 + dd * (16 * p + j);
-            float hh[HEAD ? NH : 1];
+            for (int p0 = 0; p0 < PB; p0 += N) {
+                float hh[N][NH] = {};
 #pragma unroll
-            for (int q = 0; q < (HEAD ? NH : 1); ++q) hh[q] = 0.f;
+                for (int nb = 0; nb < NB; ++nb) {
+                    v4f vp[N];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int oc = nb * 16 + kq * 4;
-                v4f v = acc[p][nb] + *reinterpret_cast<const v4f *>(sB2 + oc);
-                uint2 *so = reinterpret_cast<uint2 *>(sO + (16 * p + j) * L::OP + oc * 2);
-                uint2 u;
-                if constexpr (HEAD) u = rr[nb][p];
-                else u = *so;
-                v += v4f{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
-                         __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u)};
-                v = relu4(v);
-                const uint2 pk{bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3])};
-                if constexpr (!HEAD) {
-                    *so = pk;
-                } else {
-                    v = v4f{__uint_as_float(pk.x << 16), __uint_as_float(pk.x & 0xFFFF0000u),
-                            __uint_as_float(pk.y << 16), __uint_as_float(pk.y & 0xFFFF0000u)};
+                    for (int p = 0; p < N; ++p) {
+                        const uint2 pk = value(p0 + p, nb, rr[nb][p0 + p]);
+                        vp[p] = v4f{__uint_as_float(pk.x << 16), __uint_as_float(pk.x & 0xFFFF0000u),
+                                    __uint_as_float(pk.y << 16), __uint_as_float(pk.y & 0xFFFF0000u)};
+                    }
+                    head_add<NH, C>(hh, sH, nb * 16 + kq * 4, vp);
+                }
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc + r] * v[r];
+                for (int p = 0; p < N; ++p) {
+                    const int xo = X0 + dd * (16 * (p0 + p) + j);
+                    head_store(hh[p], sH + NH * C, ca.maps + NH * px_off + (int64_t)yo * W + xo, (int64_t)H * W, kq, xo < W && row_ok);
                 }
             }
-            if constexpr (HEAD) {
+        } else {
 #pragma unroll
-                for (int q = 0; q < NH; ++q) {
-                    hh[q] += __shfl_xor(hh[q], 16);
-                    hh[q] += __shfl_xor(hh[q], 32);
-                }
-                if (xo < W && row_ok) {
-                    const int64_t plane = (int64_t)H * W;
-                    float *mp = ca.maps + NH * px_off + (int64_t)yo * W + xo;
+            for (int p = 0; p < PB; ++p)
 #pragma unroll
-                    for (int q = 0; q < NH; ++q)
-                        if ((q & 3) == kq) mp[q * plane] = hh[q] + sH[NH * C + q];
+                for (int nb = 0; nb < NB; ++nb) {
+                    uint2 *so = reinterpret_cast<uint2 *>(sO + (16 * p + j) * L::OP + (nb * 16 + kq * 4) * 2);
+                    *so = value(p, nb, *so);
                 }
-            }
         }
         if constexpr (!HEAD) {
             const __amdgpu_buffer_rsrc_t orow = buf_rsrc(static_cast<char *>(ca.out) + act * (C * 2), 0x7FFFFFFFu);

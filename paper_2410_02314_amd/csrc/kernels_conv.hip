@@ -197,17 +197,6 @@ struct Lds {
     static constexpr bool FITS = TOTAL <= 160 * 1024;   // else no kernel exists for this shape
 };
 
-// largest v (>= 0) of the four lanes j, j + 16, j + 32, j + 48, in each of them
-// (register swaps between lane rows, where ds_bpermute would go through LDS)
-__device__ __forceinline__ float lane_groups_max(float v)
-{
-    const int x = __float_as_int(v);
-    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    const int y = max((int)a[0], (int)a[1]);       // non-negative floats order as integers
-    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
-    return __int_as_float(max((int)b[0], (int)b[1]));
-}
-
 // --------------------------------------------------------------- kernel
 // NH: outputs of the fused 1x1 head (0: no head, the layer's activations are
 // stored; 5 or 10: the head's maps are stored instead)
@@ -674,6 +663,38 @@ k_conv(ConvArgs a, Geometry geo)
         auto out_point = [&](int xo) { return ((osub + (xo & om)) * ohd + oiy) * owd + (xo >> osh); };
         const __amdgpu_buffer_rsrc_t orow =
             buf_rsrc(HEAD ? nullptr : static_cast<char *>(a.out) + act * C * ESZ, HEAD ? 0u : 0x7FFFFFFFu);
+        if constexpr (HEAD && EARLY_RES) {
+            constexpr int N = head_blocks<NH, C>(PB);
+#pragma unroll
+            for (int p0 = 0; p0 < PB; p0 += N) {
+                float hh[N][NH] = {};                        // head sums of this lane's channels
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int oc = nb * 16 + kq * 4;
+                    v4f vp[N];
+#pragma unroll
+                    for (int p = 0; p < N; ++p) {
+                        v4f v = acc[nb][p0 + p];
+                        if constexpr (P == DL_FP8) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) v[r] *= sS[oc + r];
+                        }
+                        v[0] += sB[oc + 0]; v[1] += sB[oc + 1]; v[2] += sB[oc + 2]; v[3] += sB[oc + 3];
+                        v += Store<P>::unpack(rr[nb][p0 + p]);
+                        v = relu4(v);
+                        // (BF16: the head reads what would be stored)
+                        if constexpr (P == DL_BF16) v = Store<P>::unpack(uint2{bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3])});
+                        vp[p] = v;
+                    }
+                    head_add<NH, C>(hh, sH, oc, vp);
+                }
+#pragma unroll
+                for (int p = 0; p < N; ++p) {
+                    const int xo = X0 + dd * (16 * (p0 + p) + j);
+                    head_store(hh[p], sH + NH * C, a.maps + NH * px_off + (int64_t)yo * W + xo, (int64_t)H * W, kq, xo < W && row_ok);
+                }
+            }
+        } else {
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
             const int xo = X0 + dd * (16 * p + j);
@@ -761,6 +782,7 @@ k_conv(ConvArgs a, Geometry geo)
                         if ((q & 3) == kq) mp[q * plane] = hh[q] + sH[NH * C + q];
                 }
             }
+        }
         }
         if constexpr (STAGE) {
             // the staged row leaves in whole 16-byte lanes; pixels past the

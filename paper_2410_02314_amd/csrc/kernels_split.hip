@@ -374,49 +374,43 @@ k_split(ConvArgs a, Geometry geo)
             bias[nb] = *reinterpret_cast<const v4f *>(sB + nb * 16 + kq * 4);
             scl[nb] = *reinterpret_cast<const v4f *>(sS + nb * 16 + kq * 4) * ts;
         }
+        auto value = [&](int y, int nb) {
+            v4f v = acc[y][nb];
 #pragma unroll
-        for (int y = 0; y < R; ++y) {
-            const int yo = Y0 + dd * (row0 + y);
-            const bool ok = (yo < H) & (xo < W);
-            const int opt = ((((yo & om) << osh) + (xo & om)) * ohd + (yo >> osh)) * owd + (xo >> osh);
-            float hh[NH > 0 ? NH : 1];                        // head partial sums of this lane's channels
+            for (int r = 0; r < 4; ++r) {
+                v[r] = fmaf(fmaf(acx[y][nb][r], 0x1p-11f, v[r]), scl[nb][r], bias[nb][r]);
+                if constexpr (RES) v[r] += rr[y][nb][r];
+            }
+            return relu4(v);
+        };
+        if constexpr (HEAD) {
+            constexpr int N = head_blocks<NH, C>(R);
 #pragma unroll
-            for (int q = 0; q < (NH > 0 ? NH : 1); ++q) hh[q] = 0.f;
+            for (int y0 = 0; y0 < R; y0 += N) {
+                float hh[N][NH] = {};                // head sums of this lane's channels
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int oc = nb * 16 + kq * 4;
-                v4f v = acc[y][nb];
+                for (int nb = 0; nb < NB; ++nb) {
+                    v4f vr[N];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    v[r] = fmaf(fmaf(acx[y][nb][r], 0x1p-11f, v[r]), scl[nb][r], bias[nb][r]);
-                    if constexpr (RES) v[r] += rr[y][nb][r];
+                    for (int y = 0; y < N; ++y) vr[y] = value(y0 + y, nb);
+                    head_add<NH, C>(hh, sH, nb * 16 + kq * 4, vr);
                 }
-                v = relu4(v);
-                if constexpr (!HEAD) {
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), orow[nb],
-                                                           ok ? opt * (int)a.pstride + kq * 16 : BUF_OOB, 0, 0);
-                } else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc + r] * v[r];
+                for (int y = 0; y < N; ++y) {
+                    const int yo = Y0 + dd * (row0 + y0 + y);
+                    head_store(hh[y], sH + NH * C, a.maps + NH * n.px + (int64_t)yo * W + xo, (int64_t)H * W, kq, (yo < H) & (xo < W));
                 }
             }
-            if constexpr (HEAD) {
-                // the four lane groups hold disjoint channel subsets of the pixel
+        } else {
 #pragma unroll
-                for (int q = 0; q < NH; ++q) {
-                    hh[q] += __shfl_xor(hh[q], 16);
-                    hh[q] += __shfl_xor(hh[q], 32);
-                }
-                if (ok) {
-                    const int64_t plane = (int64_t)H * W;
-                    float *mp = a.maps + NH * n.px + (int64_t)yo * W + xo;
-                    // lane group kq writes planes kq, kq + 4, kq + 8
+            for (int y = 0; y < R; ++y) {
+                const int yo = Y0 + dd * (row0 + y);
+                const bool ok = (yo < H) & (xo < W);
+                const int opt = ((((yo & om) << osh) + (xo & om)) * ohd + (yo >> osh)) * owd + (xo >> osh);
 #pragma unroll
-                    for (int q = 0; q < NH; ++q)
-                        if ((q & 3) == kq) mp[q * plane] = hh[q] + sH[NH * C + q];
-                }
+                for (int nb = 0; nb < NB; ++nb)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, value(y, nb)), orow[nb],
+                                                           ok ? opt * (int)a.pstride + kq * 16 : BUF_OOB, 0, 0);
             }
         }
     }
@@ -709,49 +703,43 @@ k_pipe(ConvArgs a, Geometry geo)
                 bias[nb] = *reinterpret_cast<const v4f *>(sB + nb * 16 + kq * 4);
                 scl[nb] = *reinterpret_cast<const v4f *>(sS + nb * 16 + kq * 4) * ts;
             }
+            auto value = [&](int y, int nb) {
+                v4f v = acc[y][nb];
 #pragma unroll
-            for (int y = 0; y < R; ++y) {
-                const int yo = Y0 + dd * (row0 + y);
-                const bool ok = (yo < H) & (xo < W);
-                const int opt = ((((yo & om) << osh) + (xo & om)) * ohd + (yo >> osh)) * owd + (xo >> osh);
-                float hh[NH > 0 ? NH : 1];                        // head partial sums of this lane's channels
+                for (int r = 0; r < 4; ++r) {
+                    v[r] = fmaf(fmaf(acx[y][nb][r], 0x1p-11f, v[r]), scl[nb][r], bias[nb][r]);
+                    if constexpr (RES) v[r] += rr[y][nb][r];
+                }
+                return relu4(v);
+            };
+            if constexpr (HEAD) {
+                constexpr int N = head_blocks<NH, C>(R);
 #pragma unroll
-                for (int q = 0; q < (NH > 0 ? NH : 1); ++q) hh[q] = 0.f;
+                for (int y0 = 0; y0 < R; y0 += N) {
+                    float hh[N][NH] = {};                // head sums of this lane's channels
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const int oc = nb * 16 + kq * 4;
-                    v4f v = acc[y][nb];
+                    for (int nb = 0; nb < NB; ++nb) {
+                        v4f vr[N];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        v[r] = fmaf(fmaf(acx[y][nb][r], 0x1p-11f, v[r]), scl[nb][r], bias[nb][r]);
-                        if constexpr (RES) v[r] += rr[y][nb][r];
+                        for (int y = 0; y < N; ++y) vr[y] = value(y0 + y, nb);
+                        head_add<NH, C>(hh, sH, nb * 16 + kq * 4, vr);
                     }
-                    v = relu4(v);
-                    if constexpr (!HEAD) {
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), orow[nb],
-                                                               ok ? opt * (int)a.pstride + kq * 16 : BUF_OOB, 0, 0);
-                    } else {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int q = 0; q < NH; ++q) hh[q] += sH[q * C + oc + r] * v[r];
+                    for (int y = 0; y < N; ++y) {
+                        const int yo = Y0 + dd * (row0 + y0 + y);
+                        head_store(hh[y], sH + NH * C, a.maps + NH * n.px + (int64_t)yo * W + xo, (int64_t)H * W, kq, (yo < H) & (xo < W));
                     }
                 }
-                if constexpr (HEAD) {
-                    // the four lane groups hold disjoint channel subsets of the pixel
+            } else {
 #pragma unroll
-                    for (int q = 0; q < NH; ++q) {
-                        hh[q] += __shfl_xor(hh[q], 16);
-                        hh[q] += __shfl_xor(hh[q], 32);
-                    }
-                    if (ok) {
-                        const int64_t plane = (int64_t)H * W;
-                        float *mp = a.maps + NH * n.px + (int64_t)yo * W + xo;
-                        // lane group kq writes planes kq, kq + 4, kq + 8
+                for (int y = 0; y < R; ++y) {
+                    const int yo = Y0 + dd * (row0 + y);
+                    const bool ok = (yo < H) & (xo < W);
+                    const int opt = ((((yo & om) << osh) + (xo & om)) * ohd + (yo >> osh)) * owd + (xo >> osh);
 #pragma unroll
-                        for (int q = 0; q < NH; ++q)
-                            if ((q & 3) == kq) mp[q * plane] = hh[q] + sH[NH * C + q];
-                    }
+                    for (int nb = 0; nb < NB; ++nb)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, value(y, nb)), orow[nb],
+                                                               ok ? opt * (int)a.pstride + kq * 16 : BUF_OOB, 0, 0);
                 }
             }
         }
