@@ -403,9 +403,10 @@ Plan make_plan(const dl_net *net, const Geometry &g, bool ext_maps)
 {
     // bytes per activation point: FP32 / BF16 values, or FP8 codes plus two
     // group scale bytes (the scales follow all codes of the buffer)
-    // (dense networks: FP32 concatenations of C + L G channels, two buffers)
+    // (dense networks: FP32 concatenations of C + L G channels, two buffers, one
+    // of which holds the U-Net's level 0, 2 C channels)
     const int prec = net->cfg.precision;
-    const size_t pt_bytes = net->dL                               ? 4 * (size_t)(net->C + net->dL * net->dG)
+    const size_t pt_bytes = net->dL                               ? 4 * (size_t)(net->C + std::max(net->dL * net->dG, net->unet ? net->C : 0))
                             : prec == DL_FP32 || prec == DL_BF16X3 ? 4 * (size_t)net->C
                             : prec == DL_BF16                     ? 2 * (size_t)net->C
                                                                   : net->C + 2;

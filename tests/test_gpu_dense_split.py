@@ -74,3 +74,24 @@ def test_planes_of_different_magnitude(e0, e1):
             for name in [f"blk{b}.l{k}.w" for k in range(i + 1, 3)] + [f"blk{b}.t.w"]:
                 w[name][:, lo:lo + 16] *= np.float32(2.0 ** -e)
     assert map_rel_err(_maps(spec, w, frames), ref).max() <= TOL
+
+
+@pytest.mark.parametrize("dil", [(2,), (4, 1), (8, 3, 2)])
+@pytest.mark.parametrize("n,h,w", [(1, 164, 150), (3, 70, 101)])
+def test_unet_wider_than_the_blocks(dil, n, h, w):
+    """One layer of 16 channels a block: the U-Net's level-0 concatenation (64
+    channels) is wider than a block's (48), in either of the two buffers."""
+    import paper_2410_02314_amd as dl
+    from tests.parity import compare_emitters
+    spec = S.DenseSpec("X", 32, dil, layers=1, growth=16, unet=2)
+    wts = S.he_normal_weights(spec, 53, bias_std=0.1)
+    frames = S.render_frames(n, h, w, "tiny", 54)
+    ref, ref_maps = oracle.localize(frames, spec, wts, return_maps=True)
+    assert map_rel_err(_maps(spec, wts, frames), ref_maps).max() <= TOL
+    net = dl.Net(S.serialize_weights(spec, wts))
+    out = torch.zeros((n * h * w, 8), dtype=torch.int32, device="cuda")
+    counts = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    net.localize_device(torch.from_numpy(frames).cuda(), out, counts)
+    torch.cuda.synchronize()
+    rec = dl.emitters_from_device(out, int(counts[-1]))
+    assert len(ref) > 10 and compare_emitters(rec, ref, ref_maps)["non_exempt_mismatch"] == 0
