@@ -1013,6 +1013,7 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
                                 a0, net->cfg.precision, conv_planar(C, net->cfg.precision), 0, keep, stem_r, s));
     }
     void *x = a0, *xn = p.ws + p.act2;      // block input, block output (alternating)
+    int in_r = stem_r;                      // radius of the next layer's input around kept gate tiles
     for (int b = 0; b < net->nb; ++b) {
         const int maxg = conv_max_grid(C, net->cfg.precision, g.trb[b], net->ncu);
         int grid = (int)std::min<int64_t>(g.tiles[b], maxg);
@@ -1057,6 +1058,9 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
         if (lists) {
             a.list = lists + (size_t)(2 * b) * g.max_tiles;
             a.list_count = lcount + 2 * b;
+            a.keep = keep;
+            a.in_radius = in_r;
+            in_r -= net->dil[b];
         }
         {
             StageTimer t(net, DL_STAGE_CONV, s);
@@ -1072,6 +1076,8 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
         if (lists) {
             a.list = lists + (size_t)(2 * b + 1) * g.max_tiles;
             a.list_count = lcount + 2 * b + 1;
+            a.in_radius = in_r;
+            in_r -= net->dil[b];
         }
         if (b == net->nb - 1) {
             a.head = net->d_head;

@@ -135,17 +135,19 @@ __device__ __forceinline__ void decode_tile(int h, int w, int64_t local, int d, 
 
 // Is any kept gate tile within distance r of the pixel box [y0, y1] x [x0, x1]
 // (inclusive)?  keep == nullptr means every tile is kept.
+__device__ __forceinline__ bool near_kept(const uint8_t *frame_keep, int h, int w, int y0, int y1, int x0, int x1, int r)
+{
+    const int ty0 = max(0, y0 - r) / GATE_TILE, ty1 = min(h - 1, y1 + r) / GATE_TILE;
+    const int tx0 = max(0, x0 - r) / GATE_TILE, tx1 = min(w - 1, x1 + r) / GATE_TILE;
+    for (int ty = ty0; ty <= ty1; ++ty)
+        for (int tx = tx0; tx <= tx1; ++tx)
+            if (frame_keep[ty * (w / GATE_TILE) + tx]) return true;
+    return false;
+}
 __device__ __forceinline__ bool near_kept(const uint8_t *keep, const FrameDesc &d, int y0, int y1, int x0,
                                           int x1, int r)
 {
-    if (!keep) return true;
-    const int ty0 = max(0, y0 - r) / GATE_TILE, ty1 = min(d.h - 1, y1 + r) / GATE_TILE;
-    const int tx0 = max(0, x0 - r) / GATE_TILE, tx1 = min(d.w - 1, x1 + r) / GATE_TILE;
-    const uint8_t *k = keep + d.keep_start;
-    for (int ty = ty0; ty <= ty1; ++ty)
-        for (int tx = tx0; tx <= tx1; ++tx)
-            if (k[ty * d.gtx + tx]) return true;
-    return false;
+    return !keep || near_kept(keep + d.keep_start, d.h, d.w, y0, y1, x0, x1, r);
 }
 
 // Read of memory that no kernel writes while the reader runs (descriptors,
@@ -263,6 +265,10 @@ struct ConvArgs {
     // 16 channels to the next (64 and total_act * 64 in the group-planar layout
     // the net's layers use, 4 C and 64 in plain NHWC)
     int64_t pstride, gstride;
+    // ... in gated runs: the keep flags and the radius around kept tiles within
+    // which the layer before has computed this one's input (see computed())
+    const uint8_t *keep;
+    int in_radius;
 };
 hipError_t launch_conv(int C, int precision, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s);
 // tile shape of the conv kernel: rows = 4 or 8; 0 picks the form's default

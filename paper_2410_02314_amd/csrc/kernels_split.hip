@@ -135,7 +135,7 @@ __device__ __forceinline__ void slow_tile(const ConvArgs &a, const TileDec &n, c
         a.maps[NH * n.px + ((int64_t)q * n.h + yo) * n.w + xo] = hh[q] + sH[NH * C + q];
 }
 
-template <int C, int TR, bool RES, int NH>
+template <int C, int TR, bool RES, int NH, bool GATED>
 __global__ void __launch_bounds__(NTH, 2)
 k_split(ConvArgs a, Geometry geo)
 {
@@ -200,7 +200,7 @@ k_split(ConvArgs a, Geometry geo)
         }
         char *p = const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride;
         // an interior tile's points all lie in the frame
-        const bool inside = r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w;
+        const bool inside = !GATED && r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w;
         int o[NPF];
         if (inside) {
 #pragma unroll
@@ -213,7 +213,7 @@ k_split(ConvArgs a, Geometry geo)
                 const int q = tv + k * NTH, pt = q >> 2;
                 const int y = r.y0 + dd * (pt / PW - 1), x = r.x0 + dd * (pt - pt / PW * PW - 1);
                 const bool ok = (q < NQ) & ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
-                o[k] = ok ? off[k] : BUF_OOB;
+                o[k] = ok && (!GATED || computed(a, r, y, x)) ? off[k] : BUF_OOB;
             }
         }
 #pragma unroll
@@ -433,7 +433,7 @@ template <int C, int TR, int NH> struct PLds {
     static constexpr bool FITS = TOTAL <= 160 * 1024;
 };
 
-template <int C, int TR, bool RES, int NH>
+template <int C, int TR, bool RES, int NH, bool GATED>
 __global__ void __launch_bounds__(TR * 64, 2)
 k_pipe(ConvArgs a, Geometry geo)
 {
@@ -502,16 +502,22 @@ k_pipe(ConvArgs a, Geometry geo)
     };
     struct Src {
         char *p;                           // the tile's first halo point, group 0
-        int y, x, h, w;
+        uint32_t ok;                       // bit k: this thread's point k has a value (else it reads zero)
     };
     auto source = [&](const TileDec &r) {
-        return Src{const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride,
-                   r.y0 - dd, r.x0 - dd, r.h, r.w};
+        Src s{const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride, 0u};
+#pragma unroll
+        for (int k = 0; k < NPF; ++k) {
+            const int y = r.y0 - dd + dy[k], x = r.x0 - dd + dx[k];
+            bool ok = ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
+            if constexpr (GATED) ok = ok && computed(a, r, y, x);
+            s.ok |= ok ? 1u << k : 0u;
+        }
+        return s;
     };
     auto load = [&](const Src &s, int g, int k) {
-        const bool ok = ((unsigned)(s.y + dy[k]) < (unsigned)s.h) & ((unsigned)(s.x + dx[k]) < (unsigned)s.w);
         return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(s.p + g * a.gstride, 0x7FFFFFFFu),
-                                                                              ok ? off[k] : BUF_OOB, 0, 0));
+                                                                              s.ok >> k & 1u ? off[k] : BUF_OOB, 0, 0));
     };
     auto largest = [&](const v4f (&p)[NPF]) {
         float m = 0.f;
@@ -754,19 +760,19 @@ k_pipe(ConvArgs a, Geometry geo)
 // ------------------------------------------------------------- launchers
 template <int C, int TR> constexpr int split_threads() { return C == 48 ? TR * 64 : NTH; }
 
-template <int C, int TR, bool RES, int NH>
+template <int C, int TR, bool RES, int NH, bool GATED = false>
 auto kernel_of()
 {
-    if constexpr (C == 48) return k_pipe<C, TR, RES, NH>;
-    else return k_split<C, TR, RES, NH>;
+    if constexpr (C == 48) return k_pipe<C, TR, RES, NH, GATED>;
+    else return k_split<C, TR, RES, NH, GATED>;
 }
 
-template <int C, int TR, bool RES, int NH>
-hipError_t launch_k(const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
+template <int C, int TR, bool RES, int NH, bool GATED>
+hipError_t launch_g(const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
 {
     using L = std::conditional_t<C == 48, PLds<C, TR, (NH > 5 ? NH : 5)>, SLds<C, TR, (NH > 5 ? NH : 5)>>;
     static_assert(L::FITS, "LDS of the split kernel");
-    auto kern = kernel_of<C, TR, RES, NH>();
+    auto kern = kernel_of<C, TR, RES, NH, GATED>();
     static bool attr = false;
     if (!attr) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -776,6 +782,14 @@ hipError_t launch_k(const ConvArgs &a, const Geometry &g, int grid, hipStream_t 
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(split_threads<C, TR>()), L::TOTAL, s, a, g);
     return hipGetLastError();
+}
+
+// (GATED: the kernels that leave out points no layer computed; the test in the
+// others' load paths costs 2 to 4%, unused)
+template <int C, int TR, bool RES, int NH>
+hipError_t launch_k(const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
+{
+    return a.keep ? launch_g<C, TR, RES, NH, true>(a, g, grid, s) : launch_g<C, TR, RES, NH, false>(a, g, grid, s);
 }
 
 template <int C, int TR>
