@@ -97,6 +97,20 @@ struct TileDec {
     int64_t px, act;
 };
 
+// Byte offsets of a tile's input (stride bytes a point) from its frame's first
+// activation point, modulo 2^32: the tile's first halo point, and from there
+// halo point (row, col).  A frame's points lie within 2^31 bytes of each other,
+// so the sum is exact for every point of the frame, although the first halo point
+// may lie up to 64 rows outside it (dilated plain rows) and the parts may wrap.
+__host__ __device__ inline uint32_t halo_start(int a0, int rs, int cs, uint32_t stride)
+{
+    return ((uint32_t)a0 - (uint32_t)rs - (uint32_t)cs) * stride;
+}
+__host__ __device__ inline uint32_t halo_point(int row, int col, int rs, int cs, uint32_t stride)
+{
+    return ((uint32_t)row * (uint32_t)rs + (uint32_t)col * (uint32_t)cs) * stride;
+}
+
 // tile ti of the layer (of its active list in gated runs), in tr x tc tiles
 __device__ __forceinline__ TileDec decode_conv_tile(const ConvArgs &a, const Geometry &geo, int nfr, int tr, int tc,
                                                     int64_t ti)

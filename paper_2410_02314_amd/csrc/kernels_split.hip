@@ -195,14 +195,17 @@ k_split(ConvArgs a, Geometry geo)
 #pragma unroll
             for (int k = 0; k < NPF; ++k) {
                 const int q = tid + k * NTH, pt = q >> 2;
-                off[k] = (pt / PW * r.rs + (pt - pt / PW * PW) * r.cs) * (int)a.pstride + (q & 3) * 16;
+                off[k] = (int)halo_point(pt / PW, pt - pt / PW * PW, r.rs, r.cs, (uint32_t)a.pstride) + (q & 3) * 16;
             }
         }
-        char *p = const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride;
-        // an interior tile's points all lie in the frame
+        // from the frame's first point, or, an interior tile's points all lying in
+        // the frame, from the first of them
+        char *p = const_cast<char *>(static_cast<const char *>(a.in)) + r.act * a.pstride;
+        const uint32_t start = halo_start(r.a0, r.rs, r.cs, (uint32_t)a.pstride);
         const bool inside = !GATED && r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w;
         int o[NPF];
         if (inside) {
+            p += start;
 #pragma unroll
             for (int k = 0; k < NPF; ++k) o[k] = (k + 1) * NTH <= NQ || tid + k * NTH < NQ ? off[k] : BUF_OOB;
         } else {
@@ -213,7 +216,7 @@ k_split(ConvArgs a, Geometry geo)
                 const int q = tv + k * NTH, pt = q >> 2;
                 const int y = r.y0 + dd * (pt / PW - 1), x = r.x0 + dd * (pt - pt / PW * PW - 1);
                 const bool ok = (q < NQ) & ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
-                o[k] = ok && (!GATED || computed(a, r, y, x)) ? off[k] : BUF_OOB;
+                o[k] = ok && (!GATED || computed(a, r, y, x)) ? (int)((uint32_t)off[k] + start) : BUF_OOB;
             }
         }
 #pragma unroll
@@ -497,15 +500,17 @@ k_pipe(ConvArgs a, Geometry geo)
 #pragma unroll
         for (int k = 0; k < NPF; ++k) {
             const int q = tid + k * NTH, pt = q >> 2;
-            off[k] = (pt / PW * r.rs + (pt - pt / PW * PW) * r.cs) * (int)a.pstride + (q & 3) * 16;
+            off[k] = (int)halo_point(pt / PW, pt - pt / PW * PW, r.rs, r.cs, (uint32_t)a.pstride) + (q & 3) * 16;
         }
     };
     struct Src {
-        char *p;                           // the tile's first halo point, group 0
+        char *p;                           // the frame's first point, group 0
+        uint32_t start;                    // offset of the tile's first halo point
         uint32_t ok;                       // bit k: this thread's point k has a value (else it reads zero)
     };
     auto source = [&](const TileDec &r) {
-        Src s{const_cast<char *>(static_cast<const char *>(a.in)) + (r.act + r.a0 - r.rs - r.cs) * a.pstride, 0u};
+        Src s{const_cast<char *>(static_cast<const char *>(a.in)) + r.act * a.pstride,
+              halo_start(r.a0, r.rs, r.cs, (uint32_t)a.pstride), 0u};
 #pragma unroll
         for (int k = 0; k < NPF; ++k) {
             const int y = r.y0 - dd + dy[k], x = r.x0 - dd + dx[k];
@@ -517,7 +522,7 @@ k_pipe(ConvArgs a, Geometry geo)
     };
     auto load = [&](const Src &s, int g, int k) {
         return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(s.p + g * a.gstride, 0x7FFFFFFFu),
-                                                                              s.ok >> k & 1u ? off[k] : BUF_OOB, 0, 0));
+                                                                              s.ok >> k & 1u ? (int)((uint32_t)off[k] + s.start) : BUF_OOB, 0, 0));
     };
     auto largest = [&](const v4f (&p)[NPF]) {
         float m = 0.f;
