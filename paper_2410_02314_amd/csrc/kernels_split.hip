@@ -14,11 +14,12 @@
 // nets the error against 64-bit arithmetic is 2.3e-7 of the maps' norm (48
 // channels, 10 layers), and was 3.9e-7 with v_mfma_f32_16x16x4_f32.
 // Three FP16 MFMAs take 3/16 of the cycles of the FP32 MFMAs they replace.
-//   Range: s is 0 while the largest input of a tile lies in [2^-5, 2^15), else
-// the multiple of 20 that brings it there (exact powers of two); values down
-// to 2^-14 after scaling keep all 22 bits, smaller ones 2^-36 absolute, i.e. at
-// most 2^-31 of the tile's largest.  Weights are scaled by a power of two per
-// output channel.  A tile holding an infinity or a value of 2^75 or more, or
+//   Range: s brings the largest input of a tile into [2^14, 2^15) (exact powers of
+// two); values down to 2^-28 of it keep all 22 bits, smaller ones are off by 2^-50
+// of it at most.  (While s moved in steps of 20, a tile with one value past 2^15
+// kept 2^-16 absolute: 9.5e-6 of the sums beside it, where FP32 products added one
+// by one give 3.1e-7 and these steps 7.5e-8.)  Weights are scaled in the same way
+// by a power of two per output channel.  A tile holding an infinity or a value of 2^75 or more, or
 // nothing but values below 2^-65 (or any tile of a layer whose weights are of
 // such magnitudes) takes plain FP32 FMAs instead (slow_tile), so those come out
 // as in FP32; NaNs propagate by themselves.
@@ -271,20 +272,14 @@ k_split(ConvArgs a, Geometry geo)
         const uint32_t mb = (uint32_t)__builtin_amdgcn_readfirstlane(
             __float_as_int(fmaxf(fmaxf(mv[0], mv[1]), fmaxf(mv[2], mv[3]))));
         const bool slow = slow_layer | split_misfit(mb);
-        const int sexp = slow || mb == 0 ? 0 : split_exp(mb);
-        auto convert = [&](auto scaled) {
-            const float sc = __int_as_float((127 + sexp) << 23);
+        const int sexp = split_exp(mb);
+        const float sc = __int_as_float((127 + sexp) << 23);
 #pragma unroll
-            for (int i = 0; i < NB * NPF; ++i) {
-                const int g = i % NB, k = i / NB;
-                if ((k + 1) * NTH > NQ && tid + k * NTH >= NQ) continue;
-                char *d = stage + g * L::PLANE + k * (NTH / 4 * 32);
-                const v4f v = decltype(scaled)::value ? pf[g][k] * sc : pf[g][k];
-                split_store(v, L::LO, d);
-            }
-        };
-        if (sexp) convert(std::true_type{});
-        else convert(std::false_type{});
+        for (int i = 0; i < NB * NPF; ++i) {
+            const int g = i % NB, k = i / NB;
+            if ((k + 1) * NTH > NQ && tid + k * NTH >= NQ) continue;
+            split_store(pf[g][k] * sc, L::LO, stage + g * L::PLANE + k * (NTH / 4 * 32));
+        }
         __syncthreads();
 
         // the residual at this wave's output points (off-frame points read

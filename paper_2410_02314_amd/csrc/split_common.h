@@ -45,12 +45,13 @@ __device__ __forceinline__ void split_store(const v4f &v, int lo_off, char *d)
     *reinterpret_cast<uint2 *>(d + lo_off) = lo;
 }
 
-// The exponent s (a multiple of 20) that brings a largest magnitude of bits mb
-// into [2^-5, 2^15); 60 at most (all zero), -60 at least.
+// The exponent s that brings a largest magnitude of bits mb into [2^14, 2^15), so
+// that values down to 2^-28 of it keep 22 bits (below, hi is an FP16 subnormal and
+// the pair is off by 2^-36 / 2^14 = 2^-50 of it at most); within +-60.
 __device__ __forceinline__ int split_exp(uint32_t mb)
 {
     const int e = (int)(mb >> 23) - 127;               // floor(log2), -127 for zero and subnormals
-    return e < -65 ? 60 : e >= 75 ? -60 : 20 * ((14 - e + 200) / 20 - 10);
+    return min(60, max(-60, 14 - e));
 }
 // ... and whether the halves cannot hold values of that magnitude
 __device__ __forceinline__ bool split_misfit(uint32_t mb)
@@ -83,7 +84,7 @@ inline float f16_value(uint16_t h)
 }
 
 // A row of n weights as halves of w up, up the power of two in 2^-60 .. 2^60
-// that brings the largest into [1, 2).  Returns 1 / up; 0 (the row's tiles go
+// that brings the largest into [2^14, 2^15).  Returns 1 / up; 0 (the row's tiles go
 // through plain FP32) where the halves cannot hold it.
 inline float split_row(const float *w, int n, uint16_t *hi, uint16_t *lo)
 {
@@ -100,7 +101,7 @@ inline float split_row(const float *w, int n, uint16_t *hi, uint16_t *lo)
         std::fill(lo, lo + n, (uint16_t)0);
         return 0.f;
     }
-    const int e = mb ? std::min(60, std::max(-60, -std::ilogb(mx))) : 0;
+    const int e = mb ? std::min(60, std::max(-60, 14 - std::ilogb(mx))) : 0;
     const float up = std::ldexp(1.f, e);
     for (int k = 0; k < n; ++k) {
         const float ws = w[k] * up;
