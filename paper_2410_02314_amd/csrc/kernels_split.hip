@@ -70,6 +70,20 @@ namespace {
 
 constexpr int TC = 32, PW = TC + 2, NTH = 256;
 
+// A tile of 4 rows takes the power of two of the tile of 8 rows it is half of, so
+// that a frame gives the same bits with either (the rows depend on the batch, the
+// config and the autotuner): it also reads the other half's rows, four more of
+// each group, for their largest magnitude alone (4 x 128^2, net A: 91.0 -> 93.4 us
+// a graph replay, against 102 with tiles of 8 rows).  extra_point: point e of these
+// as row and column of its own halo (row 0: the first halo row).
+constexpr int NEXTRA = 4 * PW;
+__device__ __forceinline__ void extra_point(int e, bool odd, int &row, int &col)
+{
+    const int r = e / PW;
+    col = e - r * PW;
+    row = r + (odd ? -4 : 6);
+}
+
 // K plan: per tap row u, 3 taps x C channels in chunks of 8 (tap column major),
 // taken four at a time; with 2 chunks left over (C = 16 or 48) two closing
 // steps share them among the tap rows: step 0 holds those of u = 0 (lane
@@ -185,6 +199,8 @@ k_split(ConvArgs a, Geometry geo)
     constexpr int NQ = NPT * 4;              // 16-byte chunks of 16 channels of the tile's points
     constexpr int NPF = (NQ + NTH - 1) / NTH;
     v4f pf[NB][NPF];
+    constexpr int NPE = TR == 4 ? (NEXTRA * 4 + NTH - 1) / NTH : 0;
+    v4f pe[NB][NPE > 0 ? NPE : 1];           // [TR 4] the other half's rows
     TileWalk walk;
     auto decode = [&](int64_t ti) { return walk.tile(a, geo, nfr, TR, TC, ti); };
     // byte offsets of this thread's chunks from the tile's first halo point:
@@ -201,7 +217,8 @@ k_split(ConvArgs a, Geometry geo)
         }
         // from the frame's first point, or, an interior tile's points all lying in
         // the frame, from the first of them
-        char *p = const_cast<char *>(static_cast<const char *>(a.in)) + r.act * a.pstride;
+        char *const frame = const_cast<char *>(static_cast<const char *>(a.in)) + r.act * a.pstride;
+        char *p = frame;
         const uint32_t start = halo_start(r.a0, r.rs, r.cs, (uint32_t)a.pstride);
         const bool inside = !GATED && r.y0 >= dd && r.y0 + dd * TR < r.h && r.x0 >= dd && r.x0 + dd * TC < r.w;
         int o[NPF];
@@ -226,6 +243,23 @@ k_split(ConvArgs a, Geometry geo)
             for (int k = 0; k < NPF; ++k)
                 pf[g][k] = __builtin_bit_cast(
                     v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(p + g * a.gstride, 0x7FFFFFFFu), o[k], 0, 0));
+        if constexpr (NPE > 0) {
+            const bool odd = walk.dd.div((uint32_t)r.y0) & 4u;
+#pragma unroll
+            for (int k = 0; k < NPE; ++k) {
+                const int q = tid + k * NTH;
+                int row, col;
+                extra_point(q >> 2, odd, row, col);
+                const int y = r.y0 + dd * (row - 1), x = r.x0 + dd * (col - 1);
+                bool ok = (q < NEXTRA * 4) & ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
+                if constexpr (GATED) ok = ok && computed(a, r, y, x);
+                const int oe = ok ? (int)(start + halo_point(row, col, r.rs, r.cs, (uint32_t)a.pstride)) + (q & 3) * 16 : BUF_OOB;
+#pragma unroll
+                for (int g = 0; g < NB; ++g)
+                    pe[g][k] = __builtin_bit_cast(
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(frame + g * a.gstride, 0x7FFFFFFFu), oe, 0, 0));
+            }
+        }
     };
 
     // n: the current tile; nx: the next one (past the last, the current one
@@ -265,6 +299,12 @@ k_split(ConvArgs a, Geometry geo)
             for (int k = 0; k < NPF; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pf[g][k][r]));
+#pragma unroll
+        for (int g = 0; g < NB; ++g)
+#pragma unroll
+            for (int k = 0; k < NPE; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pe[g][k][r]));
         mx = wave_max(mx);
         if (lane == 0) sM[wave] = mx;
         __syncthreads();   // the previous tile's LDS reads are done (and weights staged, maxima written)
@@ -479,6 +519,8 @@ k_pipe(ConvArgs a, Geometry geo)
     // first halo point (which change with the frame's row stride)
     constexpr int NQ = NPT * 4, NPF = (NQ + NTH - 1) / NTH;
     v4f pf[3][NPF];
+    constexpr int NPE = TR == 4 ? (NEXTRA * 4 + NTH - 1) / NTH : 0;
+    v4f pe[NPE > 0 ? NPE : 1];             // [TR 4] the other half's rows of one group
     int off[NPF], dy[NPF], dx[NPF], off_rs = -1;
     char *stage = sT + (tid >> 2) * 32 + (tid & 3) * 8;
 #pragma unroll
@@ -502,18 +544,46 @@ k_pipe(ConvArgs a, Geometry geo)
         char *p;                           // the frame's first point, group 0
         uint32_t start;                    // offset of the tile's first halo point
         uint32_t ok;                       // bit k: this thread's point k has a value (else it reads zero)
+        int rs;                            // [TR 4] row stride, and which half the tile is
+        bool odd;
     };
     auto source = [&](const TileDec &r) {
         Src s{const_cast<char *>(static_cast<const char *>(a.in)) + r.act * a.pstride,
-              halo_start(r.a0, r.rs, r.cs, (uint32_t)a.pstride), 0u};
-#pragma unroll
-        for (int k = 0; k < NPF; ++k) {
-            const int y = r.y0 - dd + dy[k], x = r.x0 - dd + dx[k];
+              halo_start(r.a0, r.rs, r.cs, (uint32_t)a.pstride), 0u, r.rs,
+              NPE > 0 && (walk.dd.div((uint32_t)r.y0) & 4u)};
+        auto has_value = [&](int y, int x) {
             bool ok = ((unsigned)y < (unsigned)r.h) & ((unsigned)x < (unsigned)r.w);
             if constexpr (GATED) ok = ok && computed(a, r, y, x);
-            s.ok |= ok ? 1u << k : 0u;
+            return ok;
+        };
+#pragma unroll
+        for (int k = 0; k < NPF; ++k) s.ok |= has_value(r.y0 - dd + dy[k], r.x0 - dd + dx[k]) ? 1u << k : 0u;
+#pragma unroll
+        for (int k = 0; k < NPE; ++k) {
+            const int q = tid + k * NTH;
+            int row, col;
+            extra_point(q >> 2, s.odd, row, col);
+            s.ok |= q < NEXTRA * 4 && has_value(r.y0 + dd * (row - 1), r.x0 + dd * (col - 1)) ? 1u << (NPF + k) : 0u;
         }
         return s;
+    };
+    auto load_extra = [&](const Src &s, int g) {
+#pragma unroll
+        for (int k = 0; k < NPE; ++k) {
+            const int q = tid + k * NTH;
+            int row, col;
+            extra_point(q >> 2, s.odd, row, col);
+            const uint32_t o = s.start + halo_point(row, col, s.rs, a.in_phase ? 1 : dd, (uint32_t)a.pstride) + (q & 3) * 16;
+            pe[k] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(s.p + g * a.gstride, 0x7FFFFFFFu),
+                                                                                   s.ok >> (NPF + k) & 1u ? (int)o : BUF_OOB, 0, 0));
+        }
+    };
+    auto extra_max = [&](float m) {
+#pragma unroll
+        for (int k = 0; k < NPE; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m = fmaxf(m, fabsf(pe[k][r]));
+        return m;
     };
     auto load = [&](const Src &s, int g, int k) {
         return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(s.p + g * a.gstride, 0x7FFFFFFFu),
@@ -525,7 +595,7 @@ k_pipe(ConvArgs a, Geometry geo)
         for (int k = 0; k < NPF; ++k)
 #pragma unroll
             for (int r = 0; r < 4; ++r) m = fmaxf(m, fabsf(p[k][r]));
-        return wave_max(m);
+        return wave_max(extra_max(m));
     };
     auto group_max = [&](int b) {
         const v4f *p = reinterpret_cast<const v4f *>(sM + 8 * b);
@@ -547,10 +617,12 @@ k_pipe(ConvArgs a, Geometry geo)
 #pragma unroll
         for (int k = 0; k < NPF; ++k) pf[g][k] = load(s1, g, k);
     // group 0 of the first tile into buffer 0, the maxima of groups 0 and 1
+    load_extra(s1, 0);
     {
         const float m0 = largest(pf[0]);
         if (lane == 0) sM[wave] = m0;
     }
+    load_extra(s1, 1);
     __syncthreads();
     uint32_t tmax = group_max(0);          // largest magnitude bits of the tile so far
     int sexp = split_exp(tmax);
@@ -561,6 +633,7 @@ k_pipe(ConvArgs a, Geometry geo)
             split_store(pf[0][k] * sc, L::PLANE, stage + k * (NTH / 4 * 32));
     }
     offsets(n1);
+    Src s0 = s1;                           // [TR 4] the tile in progress
     s1 = source(n1);
 #pragma unroll
     for (int k = 0; k < NPF; ++k) pf[0][k] = load(s1, 0, k);
@@ -640,6 +713,7 @@ k_pipe(ConvArgs a, Geometry geo)
             read_w(0);
             read_x(0, xp + kh * 32, R + 2);
             float mx = 0.f;
+            if constexpr (NPE > 0) load_extra(g == 0 ? s0 : s1, (g + 2) % G);      // of the group after the next
 #pragma unroll
             for (int c = 0; c < 15; ++c) {
                 const int st = c / 3, t = c % 3;
@@ -669,7 +743,7 @@ k_pipe(ConvArgs a, Geometry geo)
                         for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf(pf[(g + 2) % 3][k][r]));
                 }
                 if (c == 14) {
-                    mx = wave_max(mx);
+                    mx = wave_max(extra_max(mx));
                     if (lane == 0) sM[8 * buf + wave] = mx;
                 }
 #pragma unroll
@@ -751,6 +825,7 @@ k_pipe(ConvArgs a, Geometry geo)
         }
         n = n1;
         n1 = n2;
+        s0 = s1;
         s1 = s2;
         sexp = nexp;
         tmax = nmax;
