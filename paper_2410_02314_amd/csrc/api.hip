@@ -299,12 +299,15 @@ bool frame_act_fits(const dl_net *net, int h, int w)
 }
 
 // Rows of the FP32 pair kernels' tiles where neither the config nor the autotuner
-// chose them: 4 instead of 8 while a block's tiles of 8 rows are at most one and a
-// half per CU.  A pass is then a chain of tiles one after another, and a tile of
-// half the size takes less of it (net A: 64^2 82 -> 71 us, 300^2 with 380 tiles
-// 140 -> 123 us; 4 x 256^2 with 1024: 184 -> 188 us).  Not at 48 channels, whose
-// tile of 4 rows costs as much as one of 8, and not with the gate, whose lists the
-// workspace holds per tile.
+// chose them: 4 instead of 8 while a block's tiles of 8 rows are few.  A pass is
+// then a chain of tiles one after another, and a tile of half the size takes less
+// of it.  Graph replays at 8 | 4 rows, us: 32 channels 64^2 74 | 66, 256 tiles 102 |
+// 97, 300^2 (380 tiles) 135 | 122, then mixed (320^2, 400 tiles, 128 | 129; 350^2,
+// 528, 149 | 137), 400^2 (700) 154 | 159: to one and a half per CU.  16 channels,
+// whose tiles are short beside their staging: 128 tiles 64 | 61, 192 68 | 70, 256
+// 69 | 70, 380 88 | 95: to one for two CUs.  Not at 48 channels, whose tile of 4
+// rows costs as much as one of 8, and not with the gate, whose lists the workspace
+// holds per tile.
 void small_tiles(const dl_net *net, int n, const int *hs, const int *ws_, Geometry &g)
 {
     if (net->dL || net->cfg.tile_rows || net->C > 32 || !conv_planar(net->C, net->cfg.precision) || gated_run(net)) return;
@@ -312,7 +315,7 @@ void small_tiles(const dl_net *net, int n, const int *hs, const int *ws_, Geomet
         if (net->tune_rows[b]) continue;
         int64_t tiles = 0;
         for (int f = 0; f < n; ++f) tiles += conv_tiles(hs[f], ws_[f], net->dil[b], g.trb[b], g.tc);
-        if (2 * tiles <= 3 * (int64_t)net->ncu) g.trb[b] = 4;
+        if (2 * tiles <= (net->C == 16 ? 1 : 3) * (int64_t)net->ncu) g.trb[b] = 4;
     }
 }
 
