@@ -473,8 +473,9 @@ int dl_set_gate(dl_net *net, const float *theta, float threshold);
 int dl_gate_keep_map(dl_net *net, void *stream, uint8_t *d_keep, size_t cap, size_t *ntiles);
 
 /* Autotuner over the conv tiling, with a cache (the tiling is this library's
- * choice; the paper fixes none).  Starting from the form's default (8-row
- * tiles, tile order in column strips 8 regions wide) it times the network on
+ * choice; the paper fixes none).  Starting from the untuned tiling (8-row
+ * tiles, 4-row ones for FP32 batches of few tiles to 32 channels; tile order
+ * in column strips 8 regions wide) it times the network on
  * the caller's batch (`reps` passes after one warm-up, HIP events on
  * `stream`) for strip widths 4, 16 and 32, keeping one only when 1% faster,
  * then toggles each block's tile rows between 8 and 4 in turn under the same

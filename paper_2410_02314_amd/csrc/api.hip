@@ -3091,12 +3091,15 @@ int dl_autotune_ex(dl_net *net, const uint16_t *d_frames, int n, int h, int w, v
         ++res->configs_timed;
         return e;
     };
-    // start from the form's default rows and strip 8; pick the strip width,
-    // then each block's rows in turn (kept only when 1% faster)
-    for (int b = 0; b < net->nb; ++b) {
-        int tr = 0, tc = 0;
-        conv_tile_shape(net->C, net->cfg.precision, 0, &tr, &tc);
-        rows[b] = tr;
+    // start from the rows this batch takes untuned and strip 8; pick the strip
+    // width, then each block's rows in turn (kept only when 1% faster)
+    {
+        net->cfg.tile_rows = 0;
+        std::memset(net->tune_rows, 0, sizeof net->tune_rows);
+        std::vector<FrameDesc> fd;
+        Geometry g;
+        uniform_geometry(net, d_frames, n, h, w, fd, g);
+        for (int b = 0; b < net->nb; ++b) rows[b] = g.trb[b];
     }
     float best = 0.f, t = 0.f;
     rc = time_cfg(rows, strip, &best);
