@@ -8,6 +8,7 @@
 //   detect (threshold + 3x3 local max, 64-bit masks + per-row counts) ->
 //   scan (row offsets, per-frame counts) -> emit (ordered records).
 #include "conv_common.h"
+#include "split_common.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -643,16 +644,60 @@ bool balance_channels(const std::vector<BalanceConv *> &makers, const BalanceRea
     return any;
 }
 
+// Is some input channel of this conv below 2^-8 of its row's largest weight in
+// every row?  Usually the first row shows that none is.
+bool faint_channel(const float *w, int cout, int cin, int taps)
+{
+    std::vector<char> seen(cin, 0);
+    std::vector<float> m(cin);
+    int left = cin;
+    for (int o = 0; o < cout && left; ++o) {
+        float r = 0.f;
+        for (int c = 0; c < cin; ++c) {
+            m[c] = 0.f;
+            for (int t = 0; t < taps; ++t, ++w) m[c] = std::max(m[c], std::fabs(*w));
+            r = std::max(r, m[c]);
+        }
+        const float inv = r >= 0x1p-100f && r < 0x1p100f ? 1.f / r : 0.f;
+        for (int c = 0; c < cin; ++c)
+            if (!seen[c] && m[c] * inv >= 0x1p-8f) {
+                seen[c] = 1;
+                --left;
+            }
+    }
+    return left > 0;
+}
+
+// May balance_params change anything?  (A balanced channel is faint in all its readers.)
+bool may_balance(const dl_net *net)
+{
+    const int C = net->C, L = net->dL, G = net->dG;
+    const float *p = net->params.data() + (size_t)C * 10;      // (the stem reads the frame)
+    bool any = false;
+    auto conv = [&](int cout, int cin, int taps) {
+        any = any || faint_channel(p, cout, cin, taps);
+        p += (size_t)cout * cin * taps + cout;
+    };
+    for (int b = 0; b < net->nb; ++b) {
+        for (int i = 0; i < (L ? L : 2); ++i) conv(L ? G : C, C + i * (L ? G : 0), 9);
+        if (L) conv(C, C + L * G, 1);
+    }
+    for (int i = 0; i < (net->unet ? 4 : 0); ++i) conv(C, i < 2 ? C : 2 * C, 9);
+    conv(net->nh, C, 1);
+    return any;
+}
+
 // net->params with every channel balanced; *any: whether they differ
 std::vector<float> balance_params(const dl_net *net, bool *any)
 {
+    *any = false;
+    if (!may_balance(net)) return {};
     std::vector<float> q = net->params;
     const int C = net->C, L = net->dL, G = net->dG, nb = net->nb;
     float *p = q.data();
     std::vector<BalanceConv> k;
     k.reserve((size_t)nb * (L ? L + 1 : 2) + 6);
     k.emplace_back(p, C, 1, 9);
-    *any = false;
     if (!L) {
         for (int i = 0; i < 2 * nb; ++i) k.emplace_back(p, C, C, 9);
         k.emplace_back(p, net->nh, C, 1);
@@ -697,55 +742,62 @@ std::vector<float> balance_params(const dl_net *net, bool *any)
     return q;
 }
 
-// The parameters to pack for the net's precision; the small weights on the
-// device become theirs as well.
-int params_to_pack(dl_net *net, std::vector<float> &q)
+// The parameters to pack for the net's precision (net->params, or own); the small
+// weights on the device become theirs as well.
+int params_to_pack(dl_net *net, std::vector<float> &own, const std::vector<float> *&out)
 {
     bool any = false;
-    if (net->dL || conv_planar(net->C, net->cfg.precision)) q = balance_params(net, &any);
-    if (!any) q = net->params;
+    if (net->dL || conv_planar(net->C, net->cfg.precision)) own = balance_params(net, &any);
+    out = any ? &own : &net->params;
     if (any || net->balanced) {
         HIPCHK(net, hipDeviceSynchronize());           // kernels still queued on any stream may read the old ones
-        if (int rc = upload_small_weights(net, q)) return rc;
+        if (int rc = upload_small_weights(net, *out)) return rc;
     }
     net->balanced = any;
     return DL_OK;
 }
 
-// Dense networks: every conv's weights in the layouts of k_dpipe and its bias,
-// in run order, in one device buffer (FP32; packed once).
+// Dense networks, in one device buffer: the parameters as they are, the FP32 packs
+// of the transitions' last inputs and of the head, and, made from them on the
+// device, every conv's pairs and scales for k_dpipe, in run order.
 int pack_dense(dl_net *net)
 {
     const int C = net->C, L = net->dL, G = net->dG, CT = C + L * G;
-    std::vector<float> host, prm;
-    if (int rc = params_to_pack(net, prm)) return rc;
-    net->dense.clear();
-    const float *p = prm.data() + (size_t)C * 9 + C;
+    std::vector<float> own;
+    const std::vector<float> *prm = nullptr;
+    net->packed_precision = -1;     // not packed until the new buffer holds the weights
+    if (int rc = params_to_pack(net, own, prm)) return rc;
+    const float *const p0 = prm->data(), *p = p0 + (size_t)C * 9 + C;
+    std::vector<float> small;       // the FP32 packs
+    struct Pairs { size_t w; int cout, cin, ld, taps; };
+    std::vector<Pairs> pairs;
+    size_t total = 0;
     auto room = [&](size_t n) {
-        const size_t o = (host.size() + 63) / 64 * 64;
-        host.resize(o + n);
+        const size_t o = total;
+        total = (total + n + 63) / 64 * 64;
         return o;
     };
-    // own: outputs of the block's last layer among a transition's inputs
-    auto put = [&](int cout, int cin, int taps, int own) {
+    auto small_pack = [&](int cout, int cin, const float *W) {
+        const size_t o = small.size();
+        small.resize(o + (size_t)cout * cin);            // (multiples of 16 x 16)
+        pack_dense_weights(cout, cin, 1, W, small.data() + o);
+        return o;
+    };
+    net->dense.clear();
+    // last: outputs of the block's last layer among a transition's inputs
+    auto put = [&](int cout, int cin, int taps, int last) {
         const size_t nw = (size_t)cout * cin * taps;
         dl_net::DenseConv c{};
-        c.w = room(dpipe_weight_bytes(cout, cin - own, taps) / 4);
-        c.s = room(cout);
-        dpipe_pack(cout, cin - own, cin, taps, p, host.data() + c.w, host.data() + c.s);
-        c.raw = room(nw);
-        std::memcpy(host.data() + c.raw, p, sizeof(float) * nw);
-        if (own) {
-            std::vector<float> wo((size_t)cout * own);
+        c.raw = (size_t)(p - p0);
+        c.b = c.raw + nw;
+        pairs.push_back({c.raw, cout, cin - last, cin, taps});
+        if (last) {
+            std::vector<float> wo((size_t)cout * last);
             for (int oc = 0; oc < cout; ++oc)
-                std::memcpy(&wo[(size_t)oc * own], p + (size_t)oc * cin + cin - own, sizeof(float) * own);
-            c.own = room(wo.size());
-            pack_dense_weights(cout, own, 1, wo.data(), host.data() + c.own);
+                std::memcpy(&wo[(size_t)oc * last], p + (size_t)oc * cin + cin - last, sizeof(float) * last);
+            c.own = small_pack(cout, last, wo.data());
         }
-        p += nw;
-        c.b = room(cout);
-        std::memcpy(host.data() + c.b, p, sizeof(float) * cout);
-        p += cout;
+        p += nw + cout;
         net->dense.push_back(c);
     };
     for (int b = 0; b < net->nb; ++b) {
@@ -761,19 +813,43 @@ int pack_dense(dl_net *net)
     // the head (fused into the last block's last layer) as a 16-row 1x1 conv
     std::vector<float> head16((size_t)16 * C, 0.f);
     std::memcpy(head16.data(), p, sizeof(float) * net->nh * C);
-    net->dense_head_w = (host.size() + 63) / 64 * 64;
-    host.resize(net->dense_head_w + head16.size());
-    pack_dense_weights(16, C, 1, head16.data(), host.data() + net->dense_head_w);
-    net->packed_precision = -1;     // not packed until the new buffer holds the weights
+    net->dense_head_w = small_pack(16, C, head16.data());
+    const size_t o_small = room(small.size()), o_prm = room(prm->size());
+    net->dense_head_w += o_small;
+    for (size_t k = 0; k < pairs.size(); ++k) {
+        dl_net::DenseConv &c = net->dense[k];
+        c.own += o_small;
+        c.raw += o_prm;
+        c.b += o_prm;
+        c.s = room(pairs[k].cout);
+        c.w = room(pair_packed_bytes(pairs[k].cout, pairs[k].cin, pairs[k].taps, 16) / 4);
+    }
+    ++net->packed_gen;              // (graphs over the old buffer end here)
     if (net->d_dense) {             // a repack (trained weights): kernels still queued may read the old buffer
         HIPCHK(net, hipDeviceSynchronize());
         HIPCHK(net, free_dev(net->d_dense));
     }
-    HIPCHK(net, hipMalloc(&net->d_dense, host.size() * sizeof(float)));
-    HIPCHK(net, hipMemcpy(net->d_dense, host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice));
+    HIPCHK(net, hipMalloc(&net->d_dense, total * sizeof(float)));
+    HIPCHK(net, hipMemcpy(net->d_dense + o_small, small.data(), small.size() * sizeof(float), hipMemcpyHostToDevice));
+    HIPCHK(net, hipMemcpy(net->d_dense + o_prm, p0, prm->size() * sizeof(float), hipMemcpyHostToDevice));
+    std::vector<PairJob> jobs;
+    for (size_t k = 0; k < pairs.size(); ++k) {
+        const Pairs &q = pairs[k];
+        const dl_net::DenseConv &c = net->dense[k];
+        jobs.push_back({net->d_dense + c.raw, q.cout, q.cin, q.ld, q.taps, 16, net->d_dense + c.w, net->d_dense + c.s, nullptr});
+    }
+    HIPCHK(net, launch_pack_pairs(jobs.data(), (int)jobs.size(), nullptr));
+    HIPCHK(net, hipStreamSynchronize(nullptr));
     net->packed_precision = DL_FP32;
-    ++net->packed_gen;
     return DL_OK;
+}
+
+// one residual layer's pairs: weights at w (device), into the layout of split_packed_bytes at dst
+PairJob layer_pairs(int C, const float *w, void *dst, float *scale)
+{
+    const int group = split_pack_group(C);
+    char *d = static_cast<char *>(dst);
+    return {w, C, C, C, 9, group, d, scale, reinterpret_cast<float *>(d + pair_packed_bytes(C, C, 9, group))};
 }
 
 int ensure_packed(dl_net *net)
@@ -783,27 +859,42 @@ int ensure_packed(dl_net *net)
     if (net->dL) return pack_dense(net);
     const int C = net->C;
     const size_t per = conv_packed_bytes(C, net->cfg.precision);
-    const size_t stride = align_up(per);
-    std::vector<char> host(stride * net->nb * 2);
-    std::vector<float> wscale((size_t)net->nb * 2 * C, 0.f), prm;
-    if (int rc = params_to_pack(net, prm)) return rc;
-    const float *p = prm.data() + (size_t)C * 9 + C;
-    for (int b = 0; b < net->nb; ++b)
-        for (int k = 0; k < 2; ++k) {
-            pack_conv_weights(C, net->cfg.precision, p, host.data() + (size_t)(b * 2 + k) * stride,
-                              wscale.data() + (size_t)(b * 2 + k) * C);
-            p += (size_t)C * C * 9 + C;
-        }
+    const size_t stride = align_up(per), layers = (size_t)net->nb * 2;
+    const bool pairs = split_takes(C, net->cfg.precision);
+    std::vector<float> own;
+    const std::vector<float> *prm = nullptr;
+    net->packed_precision = -1;
+    if (int rc = params_to_pack(net, own, prm)) return rc;
+    const float *p = prm->data() + (size_t)C * 9 + C;
+    const size_t step = (size_t)C * C * 9 + C;           // a layer's weights and bias
+    // what goes to d_wpk: the layers as packed here, or (pairs) after their room the
+    // parameters, from which the device packs
+    std::vector<char> host(pairs ? 0 : stride * layers);
+    std::vector<float> wscale(layers * C, 0.f);
+    if (!pairs)
+        for (size_t k = 0; k < layers; ++k)
+            pack_conv_weights(C, net->cfg.precision, p + k * step, host.data() + k * stride, wscale.data() + k * C);
     // kernels still queued on any stream may read the old weights and scales
     HIPCHK(net, hipDeviceSynchronize());
     if (!net->d_wscale) HIPCHK(net, hipMalloc(&net->d_wscale, wscale.size() * sizeof(float)));
-    HIPCHK(net, hipMemcpy(net->d_wscale, wscale.data(), wscale.size() * sizeof(float), hipMemcpyHostToDevice));
+    ++net->packed_gen;              // (graphs over the old buffer end here)
     HIPCHK(net, free_dev(net->d_wpk));
-    HIPCHK(net, hipMalloc(&net->d_wpk, host.size()));
-    HIPCHK(net, hipMemcpy(net->d_wpk, host.data(), host.size(), hipMemcpyHostToDevice));
+    HIPCHK(net, hipMalloc(&net->d_wpk, stride * layers + (pairs ? layers * step * 4 : 0)));
+    char *d = static_cast<char *>(net->d_wpk);
+    if (pairs) {
+        float *dp = reinterpret_cast<float *>(d + stride * layers);
+        HIPCHK(net, hipMemcpy(dp, p, layers * step * 4, hipMemcpyHostToDevice));
+        std::vector<PairJob> jobs;
+        for (size_t k = 0; k < layers; ++k)
+            jobs.push_back(layer_pairs(C, dp + k * step, d + k * stride, net->d_wscale + k * C));
+        HIPCHK(net, launch_pack_pairs(jobs.data(), (int)layers, nullptr));
+        HIPCHK(net, hipStreamSynchronize(nullptr));
+    } else {
+        HIPCHK(net, hipMemcpy(net->d_wscale, wscale.data(), wscale.size() * sizeof(float), hipMemcpyHostToDevice));
+        HIPCHK(net, hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice));
+    }
     net->wpk_stride = stride;
     net->packed_precision = net->cfg.precision;
-    ++net->packed_gen;
     return DL_OK;
 }
 
@@ -2796,14 +2887,14 @@ int dl_debug_conv_layer(dl_net *net, const float *d_in, const float *d_res, int 
         const int C = net->C;
         const size_t nw = (size_t)C * C * 9, per = align_up(conv_packed_bytes(C, net->cfg.precision));
         const float *w = net->params.data() + (size_t)C * 10 + (size_t)(blk * 2 + which) * (nw + C);
-        std::vector<char> host(per + 8 * C);
-        pack_conv_weights(C, net->cfg.precision, w, host.data(), reinterpret_cast<float *>(host.data() + per));
-        std::memcpy(host.data() + per + 4 * C, w + nw, 4 * C);
-        HIPCHK(net, hipMalloc(&own.p, host.size()));
-        HIPCHK(net, hipMemcpy(own.p, host.data(), host.size(), hipMemcpyHostToDevice));
+        HIPCHK(net, hipMalloc(&own.p, per + (nw + 2 * C) * 4));
+        float *dw = reinterpret_cast<float *>(own.p + per), *dscale = dw + nw + C;
+        HIPCHK(net, hipMemcpy(dw, w, (nw + C) * 4, hipMemcpyHostToDevice));
+        const PairJob job = layer_pairs(C, dw, own.p, dscale);
+        HIPCHK(net, launch_pack_pairs(&job, 1, s));
         a.wpk = own.p;
-        a.wscale = reinterpret_cast<float *>(own.p + per);
-        a.bias = a.wscale + C;
+        a.wscale = dscale;
+        a.bias = dw + nw;
     }
     a.tr = g.trb[blk];
     a.pstride = 4 * net->C;              // the caller's plain NHWC

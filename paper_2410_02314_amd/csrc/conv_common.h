@@ -280,9 +280,8 @@ struct TileWalk {
 
 // ---- the FP32 form's layers of up to 48 channels (kernels_split.hip) ----
 bool split_takes(int C, int precision);
-size_t split_packed_bytes(int C);
-// fragments, then the FP32 weights; scale[C]: the output channels' powers of two (0: outside the FP16 halves' range)
-void split_pack_weights(int C, const float *W, void *dst, float *scale);
+size_t split_packed_bytes(int C);       // a layer's fragments (split_pack_group: channels of a K group), then its FP32 weights
+inline int split_pack_group(int C) { return C == 32 ? 32 : 16; }
 int split_max_grid(int C, int tr, int ncu);
 hipError_t launch_split(int C, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s);
 

@@ -280,7 +280,8 @@ bool conv_planar(int C, int precision);
 // does the conv kernel of this channel count and form fit in LDS (both tile heights)?
 bool conv_supported(int C, int precision, int nh);
 size_t conv_packed_bytes(int C, int precision);
-// pack one 3x3 C->C layer W [C][C][3][3]; FP8 and FP32 (to 48 channels) also write scale[C]
+// pack one 3x3 C->C layer W [C][C][3][3]; FP8 also writes scale[C].  (FP32 to 48
+// channels is packed on the device: launch_pack_pairs)
 void pack_conv_weights(int C, int precision, const float *W, void *dst, float *scale);
 
 // ---- dense-connection networks: training (kernels_dense.hip) ----
@@ -329,11 +330,11 @@ struct DensePipeArgs {
     int ngroups;             // input channels / 16
     float *out;
     int64_t ogs;
-    const void *w;           // dpipe_pack of the layer (9 taps) ...
+    const void *w;           // pairs of the layer's weights (PairJob, 9 taps) ...
     const float *bias, *scale, *raw;     // ... its bias and scales [16 NB], its weights as they are
     const FrameDesc *fd;
     int d, blk;
-    // fused transition: dpipe_pack (1 tap) of its first 16 ngroups inputs, bias
+    // fused transition: the pairs (1 tap) of its first 16 ngroups inputs, bias
     // and scales [16 NT], its weights as they are, and pack_dense_weights of its
     // last 16 NB inputs
     const void *wt;
@@ -357,10 +358,6 @@ struct DensePipeArgs {
 };
 hipError_t launch_dpipe(int nb_out, int fuse, int nt, const DensePipeArgs &a, const Geometry &g, int ncu,
                         hipStream_t s);
-// W [cout][ld][taps], its first cin inputs -> the fragments of k_dpipe; scale
-// [cout]: powers of two (all 0: outside the FP16 halves' range)
-size_t dpipe_weight_bytes(int cout, int cin, int taps);
-void dpipe_pack(int cout, int cin, int ld, int taps, const float *W, void *dst, float *scale);
 // ---- training (kernels_train.hip) ----
 // count square 3x3 convs' flat weights [C][C][9], the i-th at W0 + i src_stride,
 // into the conv kernel's layout, each as itself (dst + 2 i 9 C^2) and as the

@@ -980,7 +980,6 @@ size_t conv_packed_bytes(int C, int precision)
 
 void pack_conv_weights(int C, int precision, const float *W, void *dst, float *scale)
 {
-    if (split_takes(C, precision)) return split_pack_weights(C, W, dst, scale);
     const int NB = C / 16;
     auto wt = [&](int oc, int c, int tap) { return W[((size_t)oc * C + c) * 9 + tap]; };
     if (precision == DL_FP32) {

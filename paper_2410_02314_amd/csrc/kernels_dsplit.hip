@@ -25,8 +25,6 @@
 // FP32 matrix cores -> FP16 pairs: a layer 2.09 -> 1.01 ms (3.5 TB/s), a last
 // layer with its transition 3.98 -> 2.80 ms, with the head 4.27 -> 3.10 ms.
 #include <algorithm>
-#include <cmath>
-#include <vector>
 
 #include "conv_common.h"
 #include "split_common.h"
@@ -565,45 +563,6 @@ hipError_t launch_dpipe(int nb_out, int fuse, int nt, const DensePipeArgs &a, co
     case 3: return nb_out == 1 ? launch_t<1, 1, 3>(a, g, ncu, s) : launch_t<2, 1, 3>(a, g, ncu, s);
     default: return hipErrorInvalidValue;
     }
-}
-
-size_t dpipe_weight_bytes(int cout, int cin, int taps)
-{
-    return (size_t)(cin / 16) * (cout / 16) * (taps == 9 ? 5 : 1) * 2048;
-}
-
-void dpipe_pack(int cout, int cin, int ld, int taps, const float *W, void *dst, float *scale)
-{
-    const int NB = cout / 16, NS = taps == 9 ? 5 : 1;
-    uint16_t *o = static_cast<uint16_t *>(dst);
-    const int row = cin * taps;
-    std::vector<uint16_t> half((size_t)2 * cout * row);    // [oc][hi, lo][weight]
-    bool fit = true;
-    for (int oc = 0; oc < cout; ++oc) {
-        uint16_t *h = half.data() + (size_t)2 * oc * row;
-        scale[oc] = split_row(W + (size_t)oc * ld * taps, row, h, h + row);
-        fit &= scale[oc] != 0.f;
-    }
-    if (!fit) std::fill(scale, scale + cout, 0.f);         // every tile in plain FP32
-    for (int g = 0; g < cin / 16; ++g)
-        for (int st = 0; st < NS; ++st)
-            for (int kq = 0; kq < 4; ++kq) {
-                // the lanes' tap (-1: zero weights) and 8 channels
-                int tap;
-                if (taps == 1) tap = kq < 2 ? -1 : 0;                            // the centre half of the last closing step
-                else if (st < 3) tap = 3 * st + (kq >> 1);
-                else if (st == 3) tap = 3 * (kq >> 1) + 2;
-                else tap = kq < 2 ? 8 : -1;
-                const int c0 = g * 16 + (kq & 1) * 8;
-                for (int oc = 0; oc < cout; ++oc) {
-                    uint16_t *f = o + ((size_t)(((g * NS + st) * NB + oc / 16) * 2) * 64 + kq * 16 + oc % 16) * 8;
-                    const uint16_t *h = half.data() + (size_t)2 * oc * row + c0 * taps + std::max(tap, 0);
-                    for (int e = 0; e < 8; ++e) {
-                        f[e] = tap >= 0 ? h[e * taps] : 0;
-                        f[512 + e] = tap >= 0 ? h[row + e * taps] : 0;
-                    }
-                }
-            }
 }
 
 }  // namespace dloc

@@ -56,10 +56,7 @@
 // sustain with two waves per SIMD (24 cycles each, not 16), and the clock falls
 // from 2.4 to 1.9 GHz under them.
 #include <algorithm>
-#include <cmath>
-#include <cstring>
 #include <type_traits>
-#include <vector>
 
 #include "conv_common.h"
 #include "split_common.h"
@@ -85,7 +82,7 @@ __device__ __forceinline__ void extra_point(int e, bool odd, int &row, int &col)
 }
 
 // K plan: per tap row u, 3 taps x C channels in chunks of 8 (tap column major),
-// taken four at a time; with 2 chunks left over (C = 16 or 48) two closing
+// taken four at a time; with 2 chunks left over (16 channels) two closing
 // steps share them among the tap rows: step 0 holds those of u = 0 (lane
 // groups 0, 1) and u = 1 (2, 3), step 1 those of u = 2 and zero weights
 template <int C> struct SPlan {
@@ -832,6 +829,80 @@ k_pipe(ConvArgs a, Geometry geo)
     }
 }
 
+// ---- packing ----
+// A workgroup takes one convolution of the batch: its waves the rows' largest
+// magnitudes, then each thread 16-byte pieces of the fragments, hi and lo.  (On
+// the host this took 78 us a layer of 48 channels.)
+struct PackBatch {
+    static constexpr int MAX = 32, THREADS = 1024, ROWS = 64;
+    PairJob job[MAX];
+};
+
+__global__ void __launch_bounds__(PackBatch::THREADS)
+k_pack_pairs(PackBatch b)
+{
+    const PairJob &j = b.job[blockIdx.x];
+    __shared__ float up[PackBatch::ROWS];
+    __shared__ int misfit;
+    const int tid = threadIdx.x, lane = tid & 63, row = j.cin * j.taps;
+    if (tid == 0) misfit = 0;
+    __syncthreads();
+    for (int oc = tid >> 6; oc < j.cout; oc += PackBatch::THREADS / 64) {
+        const float *w = j.w + (size_t)oc * j.ld * j.taps;
+        uint32_t mb = 0;                               // magnitudes order as integers, NaNs last
+        for (int k = lane; k < row; k += 64) mb = max(mb, __float_as_uint(w[k]) & 0x7FFFFFFFu);
+#pragma unroll
+        for (int d = 32; d; d >>= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, d));
+        const int e = (int)(mb >> 23) - 127;           // the largest weight lies in [2^e, 2^(e + 1))
+        const int s = mb ? min(60, max(-60, 14 - e)) : 0;
+        if (lane == 0) {
+            up[oc] = __int_as_float((127 + s) << 23);
+            j.scale[oc] = __int_as_float((127 - s) << 23);
+            if (mb && (e < -60 || e >= 75)) misfit = 1;
+        }
+    }
+    __syncthreads();
+    if (misfit)
+        for (int oc = tid; oc < j.cout; oc += PackBatch::THREADS) j.scale[oc] = 0.f;
+    if (j.raw)
+        for (int k = tid; k < j.cout * row; k += PackBatch::THREADS) j.raw[k] = j.w[k];      // (ld = cin)
+    const int NB = j.cout / 16, NS = pair_steps(j.taps, j.group), CH8 = j.group / 8, FULL = 3 * CH8 / 4;
+    const int pieces = j.cin / j.group * NS * NB * 64;
+    uint4 *dst = static_cast<uint4 *>(j.dst);
+    for (int p = tid; p < pieces; p += PackBatch::THREADS) {
+        const int i = p & 15, kq = p >> 4 & 3, nb = (p >> 6) % NB, st = (p >> 6) / NB;
+        const int g = st / NS, sg = st - g * NS, oc = nb * 16 + i;
+        // the lanes' tap (-1: zero weights) and 8 channels: steps of a tap row u take
+        // chunks of 8 channels, tap column major, four at a time; the closing two the
+        // chunks left over (SPlan).  1x1: the centre half of the second closing step.
+        int tap, c0 = g * j.group;
+        if (j.taps == 1) {
+            tap = kq < 2 ? -1 : 0;
+            c0 += (kq & 1) * 8;
+        } else {
+            const bool closing = sg >= 3 * FULL;
+            const int u = !closing ? sg % 3 : sg == 3 * FULL ? kq >> 1 : kq < 2 ? 2 : 3;
+            const int chunk = closing ? 4 * FULL + (kq & 1) : 4 * (sg / 3) + kq;
+            tap = u < 3 ? 3 * u + chunk / CH8 : -1;
+            c0 += chunk % CH8 * 8;
+        }
+        uint32_t hi[4] = {}, lo[4] = {};
+        if (tap >= 0 && !misfit) {
+            const float *w = j.w + ((size_t)oc * j.ld + c0) * j.taps + tap;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float a = w[2 * e * j.taps] * up[oc], c = w[(2 * e + 1) * j.taps] * up[oc];
+                const float ah = (float)(_Float16)a, ch = (float)(_Float16)c;
+                hi[e] = pack_h2(ah, ch);
+                lo[e] = pack_h2((a - ah) * 2048.f, (c - ch) * 2048.f);
+            }
+        }
+        uint4 *f = dst + (size_t)(st * NB + nb) * 128 + kq * 16 + i;
+        f[0] = uint4{hi[0], hi[1], hi[2], hi[3]};
+        f[64] = uint4{lo[0], lo[1], lo[2], lo[3]};
+    }
+}
+
 // ------------------------------------------------------------- launchers
 template <int C, int TR> constexpr int split_threads() { return C == 48 ? TR * 64 : NTH; }
 
@@ -890,51 +961,23 @@ int blocks_per_cu()
 
 bool split_takes(int C, int precision) { return C <= 48 && precision == DL_FP32; }
 
-// the fragments, then the layer's FP32 weights as they are
-size_t split_packed_bytes(int C)
-{
-    const size_t w = C == 16 ? SPlan<16>::WBYTES : C == 32 ? SPlan<32>::WBYTES : PLds<48, 8, 5>::WBYTES;
-    return w + (size_t)9 * C * C * 4;
-}
+size_t split_packed_bytes(int C) { return pair_packed_bytes(C, C, 9, split_pack_group(C)) + (size_t)9 * C * C * 4; }
 
-void split_pack_weights(int C, const float *W, void *dst, float *scale)
+hipError_t launch_pack_pairs(const PairJob *jobs, int n, hipStream_t s)
 {
-    // k_pipe takes K by groups of 16 channels, each with closing steps of its own
-    const int NG = C == 48 ? 3 : 1, CG = C / NG, CH8 = CG / 8, NB = C / 16;
-    const int FULL = 3 * CH8 / 4, NS = 3 * FULL + (3 * CH8 % 4 ? 2 : 0), NSTEP = NG * NS;
-    const int row = C * 9;
-    uint16_t *o = static_cast<uint16_t *>(dst);
-    std::vector<uint16_t> half((size_t)2 * C * row);       // [oc][hi, lo][weight]
-    bool fit = true;
-    for (int oc = 0; oc < C; ++oc) {
-        uint16_t *h = half.data() + (size_t)2 * oc * row;
-        scale[oc] = split_row(W + (size_t)oc * row, row, h, h + row);
-        fit &= scale[oc] != 0.f;
-    }
-    if (!fit) std::fill(scale, scale + C, 0.f);    // every tile in plain FP32
-    for (int st = 0; st < NSTEP; ++st)
-        for (int kq = 0; kq < 4; ++kq) {
-            // tap row and chunk (of that row's 3 CG / 8) of these lanes' 8 values; u = 3: zero weights
-            const int g = st / NS, sg = st - g * NS;
-            int u, i;
-            if (sg < 3 * FULL) {
-                u = sg % 3;
-                i = 4 * (sg / 3) + kq;
-            } else {
-                u = sg == 3 * FULL ? kq >> 1 : kq < 2 ? 2 : 3;
-                i = 4 * FULL + (kq & 1);
-            }
-            const int v = i / CH8, c0 = g * CG + (i % CH8) * 8;
-            for (int oc = 0; oc < C; ++oc) {
-                uint16_t *f = o + ((size_t)((st * NB + oc / 16) * 2) * 64 + kq * 16 + oc % 16) * 8;
-                const uint16_t *h = half.data() + (size_t)2 * oc * row + c0 * 9 + 3 * (u < 3 ? u : 0) + v;
-                for (int e = 0; e < 8; ++e) {
-                    f[e] = u < 3 ? h[9 * e] : 0;
-                    f[512 + e] = u < 3 ? h[row + 9 * e] : 0;
-                }
-            }
+    for (int i = 0; i < n; i += PackBatch::MAX) {
+        PackBatch b{};
+        const int m = std::min(n - i, PackBatch::MAX);
+        for (int k = 0; k < m; ++k) {
+            const PairJob &j = b.job[k] = jobs[i + k];
+            if (j.cout % 16 || j.cout > PackBatch::ROWS || j.group % 16 || j.cin % j.group || j.ld < j.cin ||
+                !(j.taps == 9 ? j.group <= 32 : j.taps == 1 && j.group == 16))
+                return hipErrorInvalidValue;
         }
-    std::memcpy(o + (size_t)NSTEP * NB * 1024, W, (size_t)9 * C * C * 4);
+        hipLaunchKernelGGL(k_pack_pairs, dim3(m), dim3(PackBatch::THREADS), 0, s, b);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 int split_max_grid(int C, int tr, int ncu)

@@ -2,10 +2,6 @@
 // kernels_dsplit.hip): v 2^s = hi + lo 2^-11, hi = f16(v 2^s), lo = f16((v 2^s -
 // hi) 2^11).
 #pragma once
-#include <algorithm>
-#include <cmath>
-#include <cstring>
-
 #include "dloc_internal.h"
 
 namespace dloc {
@@ -60,56 +56,24 @@ __device__ __forceinline__ bool split_misfit(uint32_t mb)
     return (e >= 75) | ((e < -65) & (mb != 0));
 }
 
-// an FP16 value's bits (round to nearest even; |f| < 2^15) and the value of such
-// bits, both without branches: loops over them become vector code
-inline uint16_t f16_bits(float f)
+// ---- weights as pairs (kernels_split.hip: k_pack_pairs) ----
+// A convolution's weights [cout][ld][taps], its first cin inputs of them, into the
+// kernels' MFMA fragments; scale [cout] takes the rows' powers of two (all 0: the
+// halves cannot hold the rows' magnitudes, every tile goes through plain FP32);
+// raw (or null) a copy of the weights.  K is taken in groups of 16 or 32 channels
+// (group; 1x1: 16).  All pointers are device memory.
+struct PairJob {
+    const float *w;
+    int cout, cin, ld, taps, group;
+    void *dst;
+    float *scale, *raw;
+};
+// weight steps (32 values of K) of one group
+__host__ __device__ constexpr int pair_steps(int taps, int group) { return taps == 1 ? 1 : group == 32 ? 9 : 5; }
+inline size_t pair_packed_bytes(int cout, int cin, int taps, int group)
 {
-    uint32_t u, v;
-    std::memcpy(&u, &f, 4);
-    const uint32_t sign = (u >> 16) & 0x8000u;
-    u &= 0x7FFFFFFFu;
-    float t;                                   // below 2^-14: steps of 2^-24, as those of 0.5 + |f|
-    std::memcpy(&t, &u, 4);
-    t += 0.5f;
-    std::memcpy(&v, &t, 4);
-    const uint32_t n = ((u + 0xFFFu + ((u >> 13) & 1u)) >> 13) - (112u << 10);
-    return (uint16_t)(sign | (u >= 0x38800000u ? n : v - 0x3F000000u));
+    return (size_t)(cin / group) * pair_steps(taps, group) * (cout / 16) * 2048;
 }
-inline float f16_value(uint16_t h)
-{
-    const uint32_t u = (uint32_t)(h & 0x7FFFu) << 13 | (uint32_t)(h & 0x8000u) << 16;
-    float f;
-    std::memcpy(&f, &u, 4);
-    return f * 0x1p112f;                       // the exponents' biases differ by 112
-}
-
-// A row of n weights as halves of w up, up the power of two in 2^-60 .. 2^60
-// that brings the largest into [2^14, 2^15).  Returns 1 / up; 0 (the row's tiles go
-// through plain FP32) where the halves cannot hold it.
-inline float split_row(const float *w, int n, uint16_t *hi, uint16_t *lo)
-{
-    int32_t mb = 0;
-    for (int k = 0; k < n; ++k) {
-        int32_t u;
-        std::memcpy(&u, w + k, 4);
-        mb = std::max(mb, u & 0x7FFFFFFF);
-    }
-    float mx;
-    std::memcpy(&mx, &mb, 4);
-    if (mb && !(mx >= 0x1p-60f && mx < 0x1p75f)) {
-        std::fill(hi, hi + n, (uint16_t)0);
-        std::fill(lo, lo + n, (uint16_t)0);
-        return 0.f;
-    }
-    const int e = mb ? std::min(60, std::max(-60, 14 - std::ilogb(mx))) : 0;
-    const float up = std::ldexp(1.f, e);
-    for (int k = 0; k < n; ++k) {
-        const float ws = w[k] * up;
-        const uint16_t h = f16_bits(ws);
-        hi[k] = h;
-        lo[k] = f16_bits((ws - f16_value(h)) * 2048.f);
-    }
-    return std::ldexp(1.f, -e);
-}
+hipError_t launch_pack_pairs(const PairJob *jobs, int n, hipStream_t s);
 
 }  // namespace dloc
