@@ -375,7 +375,6 @@ def conv_roofline(args, precision, spec, prof, total_px):
     # all nine, + the residual for the four second convolutions of blocks 1-4
     bytes_launch = total_px * pt_bytes * (2 if blocks else (2 * n_conv + (nb - 1)) / n_conv)
     gbs = bytes_launch / avg_s / 1e9
-    key = f"k_conv {precision} C={C} {n}x{side}x{side}"
     peak, products = inference_peak(precision, C)
     if products == 1 and precision == "fp32":
         roofline = {"bound": "mfma", "achieved": round(tflops, 2), "peak": peak, "unit": "TFLOP/s",
@@ -385,7 +384,8 @@ def conv_roofline(args, precision, spec, prof, total_px):
                     "frac": round(gbs / HBM_PEAK_GBS, 4),
                     "mfma_frac": round(products * tflops / peak, 4), "tflop_s": round(tflops, 2)}
     name = "k_block" if blocks else "k_conv" if precision != "fp32" or C > 48 else "k_pipe" if C == 48 else "k_split"
-    roofline.update({"traffic": measured_traffic(key, SPLIT_SOURCES if name in ("k_pipe", "k_split") else CONV_SOURCES),
+    sources = {"k_block": BLOCK_SOURCES, "k_conv": CONV_SOURCES}.get(name, SPLIT_SOURCES)
+    roofline.update({"traffic": measured_traffic(f"{name} {precision} C={C} {n}x{side}x{side}", sources),
                      "kernel": f"{name} {precision} (3x3 dilated conv, C={C}; mean of the "
                                f"{conv_n // args.steps} non-head launches)",
                      "avg_launch_ms": round(avg_s * 1e3, 3), "flop_per_launch": flop_launch,
@@ -458,6 +458,7 @@ def map_errors_on_sample(net, d_frames, ref, torch, dev):
 
 
 CONV_SOURCES = ("kernels_conv.hip", "conv_common.h", "dloc_internal.h")
+BLOCK_SOURCES = ("kernels_block.hip", "conv_common.h", "dloc_internal.h")
 SPLIT_SOURCES = ("kernels_split.hip", "split_common.h", "conv_common.h", "dloc_internal.h")
 DENSE_SOURCES = ("kernels_dsplit.hip", "split_common.h", "conv_common.h", "dloc_internal.h")
 
