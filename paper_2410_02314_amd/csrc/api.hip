@@ -276,7 +276,7 @@ void set_tiling(const dl_net *net, Geometry &g)
 // for the first block (the stem writes plain rows) and other dilations.
 int block_layout(const dl_net *net, int b)
 {
-    if (net->dL) return 1;              // dense networks: plain NHWC throughout
+    if (net->dL) return 1;              // dense networks: h w points in any layout (dense_shift)
     const int d = net->dil[b];
     return b > 0 && d > 1 && (d & (d - 1)) == 0 ? d : 1;
 }
@@ -311,7 +311,7 @@ bool frame_act_fits(const dl_net *net, int h, int w)
 // holds per tile.
 void small_tiles(const dl_net *net, int n, const int *hs, const int *ws_, Geometry &g)
 {
-    if (net->dL || net->cfg.tile_rows || net->C > 32 || !conv_planar(net->C, net->cfg.precision) || gated_run(net)) return;
+    if (net->dL || net->cfg.tile_rows || net->C > 32 || !split_takes(net->C, net->cfg.precision) || gated_run(net)) return;
     for (int b = 0; b < net->nb; ++b) {
         if (net->tune_rows[b]) continue;
         int64_t tiles = 0;
@@ -417,6 +417,8 @@ Plan make_plan(const dl_net *net, const Geometry &g, bool ext_maps)
     Plan p;
     size_t o = 0;
     p.act0 = o; o = align_up(o + (size_t)g.total_act * pt_bytes);
+    // (act1 also where k_block keeps the tensor between a block's layers on the chip:
+    // what fits a workspace does not depend on the tiling)
     p.act1 = o; if (!net->dL) o = align_up(o + (size_t)g.total_act * pt_bytes);
     p.act2 = o; o = align_up(o + (size_t)g.total_act * pt_bytes);
     p.maps = o; if (!ext_maps) o = align_up(o + (size_t)g.total_px * net->nh * 4);
@@ -747,7 +749,7 @@ std::vector<float> balance_params(const dl_net *net, bool *any)
 int params_to_pack(dl_net *net, std::vector<float> &own, const std::vector<float> *&out)
 {
     bool any = false;
-    if (net->dL || conv_planar(net->C, net->cfg.precision)) own = balance_params(net, &any);
+    if (net->dL || split_takes(net->C, net->cfg.precision)) own = balance_params(net, &any);
     out = any ? &own : &net->params;
     if (any || net->balanced) {
         HIPCHK(net, hipDeviceSynchronize());           // kernels still queued on any stream may read the old ones
@@ -1104,7 +1106,7 @@ int run_net(dl_net *net, const FrameDesc *d_fd, const Geometry &g, const Plan &p
     {
         StageTimer t(net, DL_STAGE_STEM, s);
         HIPCHK(net, launch_stem(C, d_fd, g, net->d_stem, net->d_stem + C * 9, net->cfg.offset, scale, net->d_cam,
-                                a0, net->cfg.precision, conv_planar(C, net->cfg.precision), 0, keep, stem_r, s));
+                                a0, net->cfg.precision, split_takes(C, net->cfg.precision), 0, keep, stem_r, s));
     }
     void *x = a0, *xn = p.ws + p.act2;      // block input, block output (alternating)
     int in_r = stem_r;                      // radius of the next layer's input around kept gate tiles

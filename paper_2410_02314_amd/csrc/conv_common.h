@@ -278,7 +278,7 @@ struct TileWalk {
     }
 };
 
-// ---- the FP32 form's layers of up to 48 channels (kernels_split.hip) ----
+// ---- the FP32 form's layers of up to 48 channels (kernels_split.hip): activations in planes of 16 channels ----
 bool split_takes(int C, int precision);
 size_t split_packed_bytes(int C);       // a layer's fragments (split_pack_group: channels of a K group), then its FP32 weights
 inline int split_pack_group(int C) { return C == 32 ? 32 : 16; }

@@ -275,8 +275,6 @@ hipError_t launch_conv(int C, int precision, const ConvArgs &a, const Geometry &
 // (8, except FP32 with C > 48: 4)
 void conv_tile_shape(int C, int precision, int rows, int *tr, int *tc);
 int conv_max_grid(int C, int precision, int tr, int ncu);
-// does the net keep this form's activations in planes of 16 channels?
-bool conv_planar(int C, int precision);
 // does the conv kernel of this channel count and form fit in LDS (both tile heights)?
 bool conv_supported(int C, int precision, int nh);
 size_t conv_packed_bytes(int C, int precision);

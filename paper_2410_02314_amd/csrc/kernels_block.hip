@@ -367,11 +367,13 @@ hipError_t launch_c(const BlockArgs &a, const Geometry &g, int ncu, hipStream_t 
 }  // namespace
 
 // Up to 32 channels always (net A, 4 x 2048^2: the two layers of a block 1164 us,
-// the block 904; one 64^2 frame: 71 -> 52 us a pass).  At 48 channels the second
-// weights leave no room for a second workgroup's overlap and a full chip is
-// slower this way (net B, 4 x 2048^2: 1733 us against 1941); while the tiles are
-// at most two rounds of one workgroup per CU, one launch less counts for more
-// (500^2: 291 -> 251 us a pass, 750^2: 485 -> 495).
+// the block 904; passes, two layers | block, us: 64^2 68 | 54, 600^2 160 | 131, 901 x
+// 1400 357 | 294; 16 channels 64^2 53 | 42, 600^2 108 | 93, 901 x 1400 193 | 185).  At
+// 48 channels the second weights leave no room for a second workgroup's overlap and
+// a full chip is slower this way (net B, 4 x 2048^2: 1733 us against 1941); while the
+// tiles are at most two rounds of one workgroup per CU, one launch less counts for
+// more (passes: 4 x 128^2 187 | 172, 500^2, 512 tiles, 273 | 246; 600^2, 750 to 1280,
+// 365 | 368; 700^2 439 | 460).
 bool block_takes(int C, int precision, int tr, int64_t tiles, int ncu)
 {
     return precision == DL_BF16 && tr == TR && (C <= 32 || (C == 48 && tiles <= 2 * (int64_t)ncu));

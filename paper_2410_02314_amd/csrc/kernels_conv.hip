@@ -727,18 +727,10 @@ k_conv(ConvArgs a, Geometry geo)
                     v += Store<P>::unpack(rr[nb][EARLY_RES ? p : 0]);
                 }
                 v = relu4(v);
-                // BF16: what is stored, and what the head reads, is BF16
-                uint2 pk{0u, 0u};
-                if constexpr (P == DL_BF16) {
-                    pk = uint2{bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3])};
-                    if constexpr (HEAD)
-                        v = v4f{__uint_as_float(pk.x << 16), __uint_as_float(pk.x & 0xFFFF0000u),
-                                __uint_as_float(pk.y << 16), __uint_as_float(pk.y & 0xFFFF0000u)};
-                }
                 if constexpr (STAGE && P == DL_FP8) {
                     vs[nb] = v;
                 } else if constexpr (STAGE) {
-                    *so = pk;
+                    *so = uint2{bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3])};
                 } else if constexpr (!HEAD) {
                     Store<P>::bstore4(orow, ok && row_ok ? (out_point(xo) * C + oc) * ESZ : BUF_OOB, v);
                 } else {
@@ -864,6 +856,7 @@ int blocks_per_cu()
 template <int P, int NHL>
 bool fits_pn(int C)
 {
+    if constexpr (P == DL_FP32) return C == 64 && Lds<64, P, 4, NHL>::FITS && Lds<64, P, 8, NHL>::FITS;
     switch (C) {
     case 16: return Lds<16, P, 4, NHL>::FITS && Lds<16, P, 8, NHL>::FITS;
     case 32: return Lds<32, P, 4, NHL>::FITS && Lds<32, P, 8, NHL>::FITS;
@@ -1063,8 +1056,6 @@ int conv_max_grid(int C, int precision, int tr, int ncu)
     else b = bpc_p<DL_FP8>(C, tr);
     return b * ncu;
 }
-
-bool conv_planar(int C, int precision) { return split_takes(C, precision); }
 
 hipError_t launch_conv(int C, int precision, const ConvArgs &a, const Geometry &g, int grid, hipStream_t s)
 {

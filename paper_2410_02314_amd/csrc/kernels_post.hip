@@ -14,11 +14,11 @@ namespace {
 // ---------------------------------------------------------------- stem
 // x = (ADU - offset) * scale (scale = gain * in_scale), then
 // a = ReLU(b + sum_tap w * x) for C channels, 3x3, d = 1, zero padding,
-// stored as plain NHWC rows.  Each workgroup takes a contiguous range of the
+// stored as plain NHWC rows, or (PLANAR) in planes of 16 channels.  Each workgroup takes a contiguous range of the
 // batch's rows; a row is done in segments of SSEG pixels whose three input rows (preprocessed,
 // with a one-pixel zero border) are staged in LDS.  A thread item is one
 // 16-byte piece of a pixel's output (8 BF16 or 4 FP32 channels), so
-// consecutive threads store consecutive 16 bytes of the row.  In FP8 storage
+// consecutive threads store consecutive 16 bytes of the row (of a plane's row).  In FP8 storage
 // a pixel has four 16-channel items in adjacent lanes (items past C idle):
 // each 32-channel group's max comes from its two items by one lane shuffle,
 // then each item stores its 16 e4m3 codes and the group's first item its
@@ -628,9 +628,10 @@ hipError_t launch_detect_mask(const float *maps, int planes, const FrameDesc *fd
                               float u_max, const uint8_t *keep, uint64_t *mask, uint32_t *row_counts,
                               hipStream_t s)
 {
-    // bands of 8 rows, or of 2 while those of 8 are fewer than half the CUs: the
-    // rows of a band are one wave's chain (4 x 128^2, 64 bands of 8: 8.5 us, 256
-    // bands of 2: 4.4)
+    // bands of 8 rows, or of 2 while those of 8 are at most 128, half the chip's 256
+    // CUs: the rows of a band are one wave's chain (4 x 128^2, 64 bands of 8: 8.5
+    // us, 256 bands of 2: 4.4; with the pass that unpacks the mask, 88 bands of 8
+    // 24.0 | 19.6, 128 24.3 | 19.6, 512 25.3 | 21.7)
     const int64_t blocks8 = (int64_t)((g.maxh + 7) / 8) * g.nf;
     const int band = blocks8 <= 128 ? 2 : 8, bands = (g.maxh + band - 1) / band;
     const int64_t blocks = (int64_t)bands * g.nf;
