@@ -60,10 +60,17 @@ typedef enum {
 
 /* Arithmetic of the 3x3 block convolutions (preprocessing, stem, head,
  * sigmoid and detection are FP32 in every form):
- *   DL_FP32  FP32 weights, activations and accumulation (the exact form; to
- *            48 channels a product is taken on the FP16 matrix cores from
- *            pairs of halves, 22 bits each: nearer to the exact sums than
- *            FP32 products added one by one);
+ *   DL_FP32  FP32 weights, stored activations and accumulation (the exact
+ *            form).  With 64 channels products are FP32's own.  To 48
+ *            channels, and in the dense nets' inference, a product is taken
+ *            on the FP16 matrix cores from pairs of halves that hold 22 bits
+ *            of every input within 2^28 of the largest in its tile (10 x 34
+ *            points of its layer) and of every weight within 2^28 of its
+ *            output channel's largest, smaller ones to 2^-50 of that; fewer
+ *            roundings of the sums more than make up for the two bits (whole
+ *            nets: 0.6 to 0.95 of the FP32 products' error).  A sum of inputs
+ *            all more than 2^28 below another value of the tile keeps fewer
+ *            bits than FP32 products would;
  *   DL_BF16  BF16 weights and stored activations (round to nearest even),
  *            FP32 accumulation, bias, residual and ReLU;
  *   DL_FP8   OCP e4m3 weights with one scale per output channel, and stored

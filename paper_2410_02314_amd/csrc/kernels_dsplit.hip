@@ -3,8 +3,9 @@
 // concatenation, with the block's 1x1 transition and the 1x1 head fused into
 // its last layer, and the U-Net's convolutions (gfx950).
 //
-// Operands, products, scaling and the plain-FP32 tile of values outside the
-// FP16 halves' range are those of kernels_split.hip; so is the walk over K in
+// Operands, products, scaling (22 bits of what is within 2^28 of a tile's or a
+// row's largest) and the plain-FP32 tile of values outside the FP16 halves' range
+// are those of kernels_split.hip; so is the walk over K in
 // groups of 16 channels (k_pipe), here over as many groups as the
 // concatenation has: every group's tile goes through one of two LDS buffers
 // while the next one is converted into the other and the loads of the two
@@ -22,8 +23,8 @@
 // What bounds it: the issue slots of a step whose 16 outputs leave few MFMAs
 // (27 a wave and group of 64 points) beside the conversion of the group's tile,
 // then HBM (64 bytes a point and group read, 64 written).  Net D at 4 x 2048^2,
-// FP32 matrix cores -> FP16 pairs: a layer 2.09 -> 1.01 ms (3.5 TB/s), a last
-// layer with its transition 3.98 -> 2.80 ms, with the head 4.27 -> 3.10 ms.
+// FP32 matrix cores -> FP16 pairs: a layer 2.09 -> 1.07 ms (4.4 TB/s), a last
+// layer with its transition 3.98 -> 2.50 ms, with the head 4.27 -> 2.78 ms.
 #include <algorithm>
 
 #include "conv_common.h"
