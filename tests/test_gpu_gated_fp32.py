@@ -39,10 +39,19 @@ def _maps(net, frames):
 @pytest.mark.parametrize("rows", [0, 4])
 @pytest.mark.parametrize("before", ["scaled", "fp8", "bf16"])
 def test_kept_tiles_do_not_depend_on_earlier_calls(name, seed, rows, before):
+    _check(*S.make_net(name, seed), rows, before)
+
+
+@pytest.mark.parametrize("C,dil", [(16, (64, 40)), (48, (3, 64))])
+def test_radius_of_more_than_half_a_gate_tile(C, dil):
+    spec = S.NetSpec("X", C, dil)
+    _check(spec, S.he_normal_weights(spec, 4048, bias_std=0.1), 0, "scaled")
+
+
+def _check(spec, w, rows, before):
     import paper_2410_02314_amd as dl
     from tests.parity import map_rel_err
     from tests.test_gpu_gated import brightness_gate
-    spec, w = S.make_net(name, seed)
     blob = S.serialize_weights(spec, w)
     frames = _frames()
     theta = brightness_gate(6.0).astype(np.float32)
