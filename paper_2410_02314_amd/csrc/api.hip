@@ -302,11 +302,11 @@ bool frame_act_fits(const dl_net *net, int h, int w)
 // Rows of the FP32 pair kernels' tiles where neither the config nor the autotuner
 // chose them: 4 instead of 8 while a block's tiles of 8 rows are few.  A pass is
 // then a chain of tiles one after another, and a tile of half the size takes less
-// of it.  Graph replays at 8 | 4 rows, us: 32 channels 64^2 74 | 66, 256 tiles 102 |
-// 97, 300^2 (380 tiles) 135 | 122, then mixed (320^2, 400 tiles, 128 | 129; 350^2,
-// 528, 149 | 137), 400^2 (700) 154 | 159: to one and a half per CU.  16 channels,
-// whose tiles are short beside their staging: 128 tiles 64 | 61, 192 68 | 70, 256
-// 69 | 70, 380 88 | 95: to one for two CUs.  Not at 48 channels, whose tile of 4
+// of it.  Graph replays at 8 | 4 rows, us: 32 channels 64^2 72 | 62, 256 tiles 97 |
+// 93, 300^2 (380 tiles) 128 | 119, then mixed (320^2, 400 tiles, 119 | 124; 350^2,
+// 528, 138 | 133), 400^2 (700) 149 | 154: to one and a half per CU.  16 channels,
+// whose tiles are short beside their staging: 128 tiles 61.5 | 57.5, 192 64.9 |
+// 65.2, 256 65.6 | 66.0, 380 86 | 89: to one for two CUs.  Not at 48 channels, whose tile of 4
 // rows costs as much as one of 8, and not with the gate, whose lists the workspace
 // holds per tile.
 void small_tiles(const dl_net *net, int n, const int *hs, const int *ws_, Geometry &g)

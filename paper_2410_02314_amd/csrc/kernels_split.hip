@@ -72,8 +72,8 @@ constexpr int TC = 32, PW = TC + 2, NTH = 256;
 // A tile of 4 rows takes the power of two of the tile of 8 rows it is half of, so
 // that a frame gives the same bits with either (the rows depend on the batch, the
 // config and the autotuner): it also reads the other half's rows, four more of
-// each group, for their largest magnitude alone (4 x 128^2, net A: 91.0 -> 93.4 us
-// a graph replay, against 102 with tiles of 8 rows).  extra_point: point e of these
+// each group, for their largest magnitude alone (4 x 128^2, net A: 2.4 us of a
+// graph replay's 93).  extra_point: point e of these
 // as row and column of its own halo (row 0: the first halo row).
 constexpr int NEXTRA = 4 * PW;
 __device__ __forceinline__ void extra_point(int e, bool odd, int &row, int &col)
@@ -208,9 +208,11 @@ k_split(ConvArgs a, Geometry geo)
     auto issue = [&](const TileDec &r) {
         if (r.rs != off_rs) {
             off_rs = r.rs;
+            int tv = tid;
+            asm volatile("" : "+v"(tv));     // (worked out here, its parts not kept over the whole loop)
 #pragma unroll
             for (int k = 0; k < NPF; ++k) {
-                const int q = tid + k * NTH, pt = q >> 2;
+                const int q = tv + k * NTH, pt = q >> 2;
                 off[k] = (int)halo_point(pt / PW, pt - pt / PW * PW, r.rs, r.cs, (uint32_t)a.pstride) + (q & 3) * 16;
             }
         }
@@ -261,8 +263,7 @@ k_split(ConvArgs a, Geometry geo)
         }
     };
 
-    // n: the current tile; nx: the next one (past the last, the current one
-    // again: its input is loaded and not used)
+    // n: the current tile; nx: the next one
     TileDec n{}, nx{};
     int64_t ti = t0 + slot;
     if (ti < t1) {
@@ -287,7 +288,7 @@ k_split(ConvArgs a, Geometry geo)
 
     for (; ti < t1; ti += nslot) {
         n = nx;
-        nx = decode(ti + nslot < t1 ? ti + nslot : ti);
+        if (ti + nslot < t1) nx = decode(ti + nslot);
         const int Y0 = n.y0, X0 = n.x0, H = n.h, W = n.w;
 
         // the tile's largest magnitude sets its power of two
@@ -343,7 +344,10 @@ k_split(ConvArgs a, Geometry geo)
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        issue(nx);
+        // (past the last tile nothing is loaded: of a few tiles per workgroup such
+        // loads are a good part; net A, 4 x 128^2 90.0 -> 87.7 us, 517 x 600 205.7 ->
+        // 200.7, full frames as before)
+        if (ti + nslot < t1) issue(nx);
         __builtin_amdgcn_sched_barrier(0);
         if (slow) {
             slow_tile<C, TR, NH>(a, n, reinterpret_cast<const float *>(static_cast<const char *>(a.wpk) + K::WBYTES), sB, sH);
@@ -533,9 +537,11 @@ k_pipe(ConvArgs a, Geometry geo)
     auto offsets = [&](const TileDec &r) {
         if (r.rs == off_rs) return;
         off_rs = r.rs;
+        int tv = tid;
+        asm volatile("" : "+v"(tv));         // (as in k_split)
 #pragma unroll
         for (int k = 0; k < NPF; ++k) {
-            const int q = tid + k * NTH, pt = q >> 2;
+            const int q = tv + k * NTH, pt = q >> 2;
             off[k] = (int)halo_point(pt / PW, pt - pt / PW * PW, r.rs, r.cs, (uint32_t)a.pstride) + (q & 3) * 16;
         }
     };
